@@ -202,9 +202,9 @@ int geo_navigate_batched(geo_geometry *g, const geo_basket *baskets, int32_t nb,
  * Tracks whose step is 0 (outside the mother or inside a daughter) or that
  * never reach a boundary contribute 0. At a non-smooth point (an edge, a tie
  * between volumes) the gradient of the surface the forward pass picked is
- * used. With offsets and culling, a small kernel first writes the volume's
- * culling records moved by the offsets into a buffer of the handle, which
- * the forward pass's culling tests read. Calls on one handle share that
+ * used. With offsets and culling, a small kernel first writes the operands of
+ * the volume's culling tests, moved by the offsets, into a buffer of the
+ * handle, which the forward pass reads. Calls on one handle share that
  * buffer and a partial-sum buffer: they must be stream-ordered (no
  * concurrent backward calls on one handle). */
 int geo_navigate_backward(const geo_geometry *g, int32_t volume, geo_tracks t, const double *offsets,
@@ -216,8 +216,8 @@ int geo_navigate_backward(const geo_geometry *g, int32_t volume, geo_tracks t, c
  * same arguments and results (bit for bit), but the partial sums of the
  * offset gradient live in a static device buffer of the library (3 MiB, one
  * per GPU, held until the process ends) instead of the handle's, the
- * culling tests apply the offsets themselves (no shifted records are
- * written into the handle), and the call allocates nothing. The buffer holds 2048 * 3 * 64 doubles: any
+ * culling tests apply the offsets themselves (nothing is written into the
+ * handle), and the call allocates nothing. The buffer holds 2048 * 3 * 64 doubles: any
  * track count with up to 64 daughters; with more, a call whose partial sums
  * (min(ceil(n / 256), 2048) rows of 3 * ndaughters) do not fit fails with
  * GEO_ERR_INVALID_ARG before launching anything. Every call on one GPU shares
@@ -237,7 +237,8 @@ int geo_navigate_backward_noalloc(const geo_geometry *g, int32_t volume, geo_tra
  *                            (track, daughter) pair that passed the culling
  *                            test; without, every active lane of a
  *                            wavefront that evaluates the daughter,
- *   counts[14]               lane culling tests (0 with culling off),
+ *   counts[14]               lane culling tests (0 with culling off and for
+ *                            volumes that are not culled),
  *   counts[15]               tracks navigated (mother DistFromInside).
  * Synchronises the stream. */
 int geo_navigate_batched_census(geo_geometry *g, const geo_basket *baskets, int32_t nb, geo_tracks all,
@@ -273,13 +274,16 @@ int geo_get_batched_graph(const geo_geometry *g, int32_t *use_graph);
 int geo_set_batched_graph(geo_geometry *g, int32_t use_graph);
 
 /* Culling in the navigators (basket, batched, backward): a daughter is not
- * evaluated for a track whose line cannot enter the daughter's bounding
- * sphere (radius enlarged by 1e-6 relative + 1e-6) before the mother's exit.
- * The (track, daughter) pairs that pass are queued in LDS and evaluated one
- * pair per lane. A culled daughter could neither lower a step nor
+ * evaluated for a track whose line misses the daughter's bounding sphere
+ * (radius enlarged by 1e-6 relative + 1e-6, and by the rounding of the tests,
+ * which run in half precision on the matrix cores). The (track, daughter)
+ * pairs that pass are queued in LDS and evaluated one pair per lane. Volumes
+ * whose spheres most lines meet, and some calls on volumes of a few
+ * daughters, evaluate every daughter all the same. A culled daughter could neither lower a step nor
  * win a tie, so results are bit-identical with culling on or off; only the
  * work done changes. Applies likewise to geo_navigate_safety (a daughter
- * whose sphere is farther than the mother's safety) and geo_locate (a point
+ * whose sphere is farther than the mother's safety or than a bound of the
+ * nearest daughter's) and geo_locate (a point
  * outside the sphere). On by default. */
 int geo_set_culling(geo_geometry *g, int32_t enable);
 int geo_get_culling(const geo_geometry *g, int32_t *enabled);

@@ -59,11 +59,6 @@ static_assert(sizeof(ShapeRec) == 240, "ShapeRec layout");
 // j's nappes being r = ao[j] + bo[j] z (outer) and ai[j] + bi[j] z (inner,
 // present when bit j of hole_mask is set: not both inner radii 0).
 constexpr int kPconMax = 8;
-// The daughter and culling tables hold each volume's records padded to a
-// multiple of kCullChunk; padding records have q (culling record) and
-// cull_r2 (daughter record) = -infinity, so that
-// no culling test passes them.
-constexpr int kCullChunk = 4;
 struct alignas(16) PconRec {
     int32_t nz;
     int32_t hole_mask;
@@ -82,32 +77,25 @@ struct alignas(16) DaughterRec {
     double rot[9];   // R, row-major
     double tr[3];    // T
     double bound_r;  // radius of a sphere about the local origin holding the shape
-    // the culling radius (bound_r enlarged by 1e-6 relative + 1e-6) squared
-    // and itself, for the tests with offsets (which form w = p - T
-    // explicitly) and the safety's reach; -infinity and 0 in padding records
-    double cull_r2;
-    double cull_r;
+    double cull_r;   // the culling radius: bound_r enlarged by 1e-6 relative + 1e-6
+    double pad;
     const PconRec *pcon;  // the polycone's sections (device), or NULL
     ShapeRec shape;
 };
 static_assert(sizeof(DaughterRec) == 368, "DaughterRec layout");
 
-// Culling record of a daughter, in its own compact array (32 B, so the
-// records of a whole volume stay in the scalar cache during the daughter
-// loop, and a chunk of four is 128 contiguous bytes, two scalar loads): the
-// centre of the bounding sphere in the mother frame (T) and the threshold q
-// of the expanded test of the compacted navigator: that test evaluates the
-// squared distance from T to the track's half-line, less |T|^2, as
-// |p|^2 - 2 p.T - b^2 with b = min((p - T).e, 0) and e = d / |d| (1 / |d|
-// to a few ulp); every term is at most (|p| + |T|)^2, so the rounding error
-// is below 16 eps (2 R + 2 |T|)^2 for a track inside the mother (R the
-// mother's bounding radius); q = r2 - |T|^2 + 64 eps (3 R + 2 |T|)^2, r2
-// the square of the culling radius. The radius itself and r2 sit in the
-// daughter record.
-struct alignas(16) CullRec {
-    double tx, ty, tz, q;
+// Culling block: the daughters' operand of the culling tests, which run on
+// the matrix cores (see "Culling" below), for up to kCullBlock daughters of a
+// volume: 8 half-precision entries of each wavefront lane, in the layout of
+// the A operand of a 32 x 32 x 16 product. Written by cull_operand.
+constexpr int kCullBlock = 32;
+// the mother's bounding radius in the tests' units, the largest coordinate of
+// a daughter's centre they take, and a constant beyond every product
+constexpr float kCullR = 256.0f, kCullMax = 512.0f, kCullFar = 3.8e6f;
+struct alignas(16) CullBlock {
+    unsigned int a[64][4];
 };
-static_assert(sizeof(CullRec) == 32, "CullRec layout");
+static_assert(sizeof(CullBlock) == 1024, "CullBlock layout");
 
 struct alignas(16) VolumeRec {
     ShapeRec mother;
@@ -115,8 +103,21 @@ struct alignas(16) VolumeRec {
     int32_t first;  // index of daughter 0 in the daughter and culling tables
     const PconRec *pcon;  // the mother's polycone sections (device), or NULL
     double bound_r;       // radius of a sphere about the origin holding the mother
+    // the culling tests' coordinates: lengths times cull_s = kCullR / bound_r
+    // (0 when that is not a normal number), and the length, in those units,
+    // by which a track's start is moved back for its test
+    double cull_s;
+    float cull_back;
+    int32_t first_block;  // index of the volume's first culling block
+    int32_t dense;        // most lines meet most culling spheres: not culled
+    // the safety's bound from the nearest culling sphere (see the compacted
+    // safety), in the tests' units: of the daughters whose Safety at distance
+    // |w| > r is at most sqrt(|w|^2 + c), the largest r^2 + c; of the others,
+    // at most |w| + q, the largest r^2 and q (q < 0: none)
+    float safe_d, safe_r2, safe_q;
+    int32_t pad[2];
 };
-static_assert(sizeof(VolumeRec) == 272, "VolumeRec layout");
+static_assert(sizeof(VolumeRec) == 304, "VolumeRec layout");
 
 struct TracksDev {
     const double *x, *y, *z, *ux, *uy, *uz;
@@ -1101,7 +1102,6 @@ __device__ __forceinline__ void census_add(unsigned long long *census, int slot)
 
 template <bool HAS_OFFS, bool TRACK_SURF, bool COUNT = false, int KSET = kSetAll>
 __device__ __forceinline__ void nav_track(const VolumeRec &v, const DaughterRec *__restrict__ dau,
-                                          const CullRec *__restrict__ cul,
                                           const double *__restrict__ offs, double x, double y,
                                           double z, double ux, double uy, double uz, double &best,
                                           int &hit, int &bsid,
@@ -1113,14 +1113,13 @@ __device__ __forceinline__ void nav_track(const VolumeRec &v, const DaughterRec 
     bsid = sid;
     const int nd = v.nd;
     for (int k = 0; k < nd; ++k) {
-        const CullRec &Q = cul[k];
-        double wx = x - Q.tx, wy = y - Q.ty, wz = z - Q.tz;
+        const DaughterRec &D = dau[k];
+        double wx = x - D.tr[0], wy = y - D.tr[1], wz = z - D.tr[2];
         if (HAS_OFFS) {
             wx -= offs[3 * k + 0];
             wy -= offs[3 * k + 1];
             wz -= offs[3 * k + 2];
         }
-        const DaughterRec &D = dau[k];
         if (COUNT) census_add(census, 2 * D.shape.kind + D.shape.hole);
         const double *R = D.rot;
         // local = R^T w
@@ -1140,23 +1139,22 @@ __device__ __forceinline__ void nav_track(const VolumeRec &v, const DaughterRec 
 }
 
 // ------------------------------------------------ compacted navigator
-// Culling: a (track, daughter) pair needs evaluating only when the track's
+// A (track, daughter) pair needs evaluating only when the track's
 // half-line from p passes within the daughter's culling radius (its
 // bounding radius enlarged by 1e-6 relative + 1e-6) of the sphere's centre
 // T; otherwise the daughter cannot be entered at any t >= 0, so it could
 // neither lower the step nor win a tie. (The mother's exit would bound the
 // half-line further, but the daughters lie inside the mother and no line
 // comes back near them after leaving a convex mother: on the batched
-// workload that bound removes no pair, and leaving it out saves a min per
-// test.) Skipping a daughter for a whole wavefront unless some lane needs
-// it would leave all 64 lanes evaluating it for the one lane or two that do
-// (with random tracks about one lane in 64). The compacted form separates the
-// two: the wavefront first runs the culling tests of its tracks against
-// every daughter (lockstep: the culling record is uniform) and appends each
-// (track, daughter) pair that passes to a queue in LDS; then each lane takes
-// one queued pair and evaluates that daughter's DistFromOutside for that
-// track, so a batch of 64 pairs costs one pass (the lanes of different kinds
-// take their kinds' code in turn).
+// workload that bound removes no pair.) Skipping a daughter for a whole
+// wavefront unless some lane needs it would leave all 64 lanes evaluating it
+// for the one lane or two that do (with random tracks about one lane in 64).
+// The compacted form separates the two: the wavefront first runs the culling
+// tests of its tracks against every daughter (see "culling" below) and
+// appends each (track, daughter) pair that passes to a queue in LDS; then
+// each lane takes one queued pair and evaluates that daughter's
+// DistFromOutside for that track, so a batch of 64 pairs costs one pass (the
+// lanes of different kinds take their kinds' code in turn).
 //
 // The step of a track is the minimum over its candidates of (s, index),
 // compared lexicographically with the mother as index -1: the result of
@@ -1170,43 +1168,24 @@ __device__ __forceinline__ void nav_track(const VolumeRec &v, const DaughterRec 
 // the key). After every batch the slot holds the lexicographic minimum of
 // all candidates merged so far, whatever the order of the batches.
 //
-// At the end of its round, each track that queued a pair takes a slot of
-// the wavefront's track cache in LDS, which holds its six coordinates; the
-// batches read their tracks from there rather than from global memory,
-// where the six component arrays put each track on six cache lines, long
-// evicted from L2 by the time its batch runs. (Pairs flushed within their
-// own round, when the queue fills or the slots run out, read their track
-// from global memory while it is still cached.) A flush empties the queue
-// and the slots. The queue is flushed when a chunk's pairs could overflow
-// it, when a round's tracks would overflow the slots, and at the end of the
-// tile.
-//
-// Queue entries pack the daughter index (bits 10..31) and the track's index
-// within the tile, round * 64 + lane (bits 0..9). All LDS traffic of the
-// queue, the slots and the minima is the wavefront's own, whose LDS
-// instructions execute in program order, so no barrier is needed.
-constexpr int kQueueCap = 512;
-constexpr int kPoolMax = 128;
-constexpr int kSlots = 48;
-constexpr unsigned char kNoSlot = 255;
+// The queue holds 64 pairs, each with its track's six coordinates: a lane
+// that appends a pair has its track in registers, and the batch would
+// otherwise read it from global memory, where the six component arrays put
+// each track on six cache lines, long evicted from L2 by the time its batch
+// runs. A full queue is run at once (a batch of 64 pairs, every lane busy);
+// what is left at the end of the tile makes the last batch. All LDS traffic
+// of the queue and the minima is the wavefront's own, whose LDS instructions
+// execute in program order, so no barrier is needed.
+constexpr int kQueueCap = 64;
 template <int U>
 struct NavScratch {
     unsigned long long key[U * 64];   // running minimum per track: key of the step
     int hit[U * 64];                  // and the packed index of its candidate
-    unsigned char slot_of[U * 64];    // the track's slot, kNoSlot if none
-    double x[kSlots], y[kSlots], z[kSlots], ux[kSlots], uy[kSlots], uz[kSlots];
-    union {
-        unsigned int queue[kQueueCap];  // (daughter << 10) | round * 64 + lane
-        struct {                        // a pooled flush of at most kPoolMax pairs:
-            unsigned int entry[kPoolMax];          // the queue's entries
-            unsigned long long key[kPoolMax];      // each pair's step key
-            int hit[kPoolMax];                     // and packed hit
-        } pooled;
-    };
+    // the queued pairs: (daughter << 10) | round * 64 + lane, and the track
+    unsigned int pair[kQueueCap];
+    double x[kQueueCap], y[kQueueCap], z[kQueueCap], ux[kQueueCap], uy[kQueueCap], uz[kQueueCap];
     static_assert(U * 64 <= 1024, "track index within the tile: 10 bits");
-    static_assert(sizeof(pooled) <= sizeof(queue), "pooled results within the queue");
 };
-static_assert(kSlots < kNoSlot, "slot numbers");
 
 // Scratch of the compacted safety and localization (one round of 64 points
 // per wavefront): running minima per point and the queue of (point,
@@ -1214,7 +1193,7 @@ static_assert(kSlots < kNoSlot, "slot numbers");
 struct PointQueue {
     unsigned long long key[64];
     int hit[64];
-    unsigned int queue[kQueueCap];
+    unsigned int queue[512];
 };
 
 // A NaN daughter step never wins and a NaN mother step is never beaten, as
@@ -1229,7 +1208,7 @@ __device__ __forceinline__ double key_step(unsigned long long k) {
 }
 
 // Accesses to the running minima, which other lanes of the wavefront update
-// atomically, and to the slots, which other lanes read.
+// atomically.
 template <typename T>
 __device__ __forceinline__ T lds_load(const T *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
@@ -1245,15 +1224,15 @@ __device__ __forceinline__ int lanes_below(unsigned long long m) {
                                           __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
 
-// DistFromOutside of daughter k (records D, Q) for a mother-frame track;
+// DistFromOutside of daughter k (record D) for a mother-frame track;
 // sid receives the surface that set it. With a class cls >= 0 (uniform over
 // the wavefront), the daughter is known to be of that kind class.
 template <bool HAS_OFFS, int KSET>
-__device__ __forceinline__ double daughter_dist_out(const DaughterRec &D, const CullRec &Q,
+__device__ __forceinline__ double daughter_dist_out(const DaughterRec &D,
                                                     const double *__restrict__ offs, int k, double x,
                                                     double y, double z, double ux, double uy,
                                                     double uz, int &sid, int cls = -1) {
-    double wx = x - Q.tx, wy = y - Q.ty, wz = z - Q.tz;
+    double wx = x - D.tr[0], wy = y - D.tr[1], wz = z - D.tr[2];
     if (HAS_OFFS) {
         wx -= offs[3 * k + 0];
         wy -= offs[3 * k + 1];
@@ -1322,230 +1301,333 @@ __device__ __forceinline__ void merge_step(Scratch &S, int j, double s, int k, i
     merge_key(S, j, step_key(s), hit_pack(k, sid));
 }
 
-// Runs the qn queued pairs in batches of 64 (one pair per lane), each
-// reading its track from its slot, or from global memory if the track has
-// none (pairs flushed within their own round), then empties the queue and
-// the slots.
+// Runs the qn queued pairs as one batch, one pair per lane.
 template <int U, bool HAS_OFFS, bool COUNT, int KSET, bool SURF>
-__device__ __forceinline__ void nav_flush(const DaughterRec *__restrict__ dau,
-                                          const CullRec *__restrict__ cul,
-                                          const double *__restrict__ offs, const TracksDev &t,
-                                          int64_t base, NavScratch<U> &S, int &qn, int &ns, int lane,
+__device__ __forceinline__ void nav_batch(const DaughterRec *__restrict__ dau,
+                                          const double *__restrict__ offs, NavScratch<U> &S, int qn, int lane,
                                           unsigned long long *census) {
-    for (int e0 = 0; e0 < qn; e0 += 64) {
-        const int e = e0 + lane;
-        const bool on = e < qn;
-        const unsigned int q = on ? S.queue[e] : 0u;
-        const int j = (int)(q & 1023u);
-        const int k = (int)(q >> 10);
-        if (COUNT) {
-            const int c = 2 * dau[k].shape.kind + dau[k].shape.hole;
-            for (int cc = 0; cc < 2 * (kPcons + 1); ++cc) {
-                const unsigned long long m = __ballot(on && c == cc);
-                if (m != 0ull && lane == __ffsll(m) - 1) atomicAdd(&census[cc], (unsigned long long)__popcll(m));
-            }
-        }
-        if (on) {
-            const int sl = lds_load(&S.slot_of[j]);
-            double x, y, z, ux, uy, uz;
-            if (sl != kNoSlot) {
-                x = lds_load(&S.x[sl]);
-                y = lds_load(&S.y[sl]);
-                z = lds_load(&S.z[sl]);
-                ux = lds_load(&S.ux[sl]);
-                uy = lds_load(&S.uy[sl]);
-                uz = lds_load(&S.uz[sl]);
-            } else {
-                const TileTracks tt = tile_tracks(t, base);
-                const unsigned int ju = (unsigned int)j;
-                x = at32(tt.x, ju);
-                y = at32(tt.y, ju);
-                z = at32(tt.z, ju);
-                ux = at32(tt.ux, ju);
-                uy = at32(tt.uy, ju);
-                uz = at32(tt.uz, ju);
-            }
-            int sid;
-            const double s = daughter_dist_out<HAS_OFFS, KSET>(dau[k], cul[k], offs, k, x, y, z, ux, uy, uz, sid);
-            merge_step(S, j, s, k, SURF ? sid : -1);  // (a surface not wanted is not tracked)
+    const bool on = lane < qn;
+    const unsigned int q = on ? S.pair[lane] : 0u;
+    const int j = (int)(q & 1023u);
+    const int k = (int)(q >> 10);
+    if (COUNT) {
+        const int c = 2 * dau[k].shape.kind + dau[k].shape.hole;
+        for (int cc = 0; cc < 2 * (kPcons + 1); ++cc) {
+            const unsigned long long m = __ballot(on && c == cc);
+            if (m != 0ull && lane == __ffsll(m) - 1) atomicAdd(&census[cc], (unsigned long long)__popcll(m));
         }
     }
-    qn = 0;
-    ns = 0;
+    if (on) {
+        int sid;
+        const double s = daughter_dist_out<HAS_OFFS, KSET>(dau[k], offs, k, S.x[lane], S.y[lane], S.z[lane],
+                                                           S.ux[lane], S.uy[lane], S.uz[lane], sid);
+        merge_step(S, j, s, k, SURF ? sid : -1);  // (a surface not wanted is not tracked)
+    }
 }
 
-// Per-track constants of the culling test: the unit direction e (as -e),
-// and for the expanded form (no offsets) |p|^2, p.e, -2 p; a zero
-// direction, or one whose |d|^2 overflows, gives e = 0 (the test then
-// takes the start point).
-__device__ __forceinline__ void cull_constants(double x, double y, double z, double ux, double uy, double uz,
-                                               double &pp, double &pe, double &mpx, double &mpy, double &mpz,
-                                               double &mex, double &mey, double &mez) {
-    const double dd = fma(uz, uz, fma(uy, uy, ux * ux));
-    const double il = (dd > 0.0 && dd < __builtin_inf()) ? rsqrt_fine(dd) : 0.0;
-    pp = fma(z, z, fma(y, y, x * x));
-    pe = fma(z, uz, fma(y, uy, x * ux)) * il;
-    mpx = -2.0 * x;
-    mpy = -2.0 * y;
-    mpz = -2.0 * z;
-    mex = -ux * il;
-    mey = -uy * il;
-    mez = -uz * il;
+// ------------------------------------------------------------- culling
+// The tests ask, for the 64 tracks of a wavefront and a block of 32
+// daughters, which half-lines pass within a daughter's culling radius r of
+// its centre T. With w = p - T and e = d / |d|, that is |w|^2 - r^2 <=
+// min(w.e, 0)^2, two inner products per pair: a contraction over K = 16,
+// run as two v_mfma_f32_32x32x16_f16 per 32 tracks (one for |w|^2 - r^2, one
+// for w.e), daughters along the rows, tracks along the columns. What is left
+// per pair is one fma and one v_alignbit that shifts the sign into the
+// lane's mask: two VALU instructions, where the tests took nine in FP64
+// (bound by VALU issue: 55 % of the batched navigator's instructions). Two
+// products and 32 VALU instructions for 1024 pairs measured 154 cycles of a
+// SIMD, 9 x 16 FP64 instructions about 700.
+//
+// The test is a filter: a pair that passes is evaluated in FP64, a pair that
+// is dropped must be one whose half-line misses the sphere. So every error
+// of the filter goes one way:
+//  - Lengths are taken in units where the mother's bounding radius is
+//    kCullR = 256, and every factor as two half-precision pieces (round
+//    toward zero, 21 bits) whose products are exact in the FP32 accumulator,
+//    the product of two second pieces left out.
+//  - r^2 is widened by delta = 2^-15 ((256 + L)^2 + |T|^2), L the shift
+//    below. With W = 256 + L + |T| (so delta >= 2^-16 W^2), the first
+//    product is off by at most 2^-18.8 W^2 and w.e by 2^-18.3 W (a sum of
+//    products off by 2^-22 of its terms' magnitudes was measured, four times
+//    that is allowed for), together 2^-16.8 W^2.
+//  - min(w.e, 0)^2 costs an instruction that w.e |w.e| does not, which is the
+//    same for w.e <= 0 and wrongly negative otherwise. The start is
+//    therefore moved back along the line by L, more than any radius: a
+//    half-line that meets a sphere then has w.e <= 0 there, and the test is
+//    exact for it; a line that meets a sphere up to L behind its start
+//    passes as well.
+//  - A daughter whose centre or radius is over kCullMax (out of the mother's
+//    reach) always passes.
+// A track that starts outside the mother has step 0 from the mother, which
+// no daughter can beat: it is left out, so every start is within 256.
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef _Float16 half8v __attribute__((ext_vector_type(8)));
+typedef float float16v __attribute__((ext_vector_type(16)));
+typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
+typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
+
+// a and b as half-precision pairs: hi the values toward zero, lo what is left.
+__device__ __forceinline__ unsigned int half_pair(float a, float b) {
+    return __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_pkrtz(a, b));
+}
+__device__ __forceinline__ void half_split(float a, float b, unsigned int &hi, unsigned int &lo) {
+    hi = half_pair(a, b);
+    const half2v h = __builtin_bit_cast(half2v, hi);
+    lo = half_pair(a - (float)h.x, b - (float)h.y);
 }
 
-// Navigates the tracks base + u * 64 + lane (u < U, index below `count`
+// The K = 16 slots, as pairs: lanes 0..31 hold slots 0..7 of row (column)
+// lane, lanes 32..63 slots 8..15 of row (column) lane - 32.
+//   daughter (hi, lo the pieces of -2 T, n of (|T|^2 - r^2 - delta) / 64, s of -2 r):
+//     hi.x hi.y | hi.z 64 | hi.x hi.y | hi.z 64 | lo.x lo.y | lo.z s.hi | n.hi n.lo | s.hi s.lo
+//   track (of a vector v, a constant c / 64 and a length f):
+//     hi.x hi.y | hi.z c.hi | lo.x lo.y | lo.z c.lo | hi.x hi.y | hi.z f.hi | 64 64 | f.lo f.hi
+// and for w.e, whose daughters are the same, zeros in the last four slots.
+// Their product is -2 T.v + c + |T|^2 - r^2 - delta - 2 r f.
+//
+// Row 8 i + 4 h + j (i, j < 4, h < 2) holds the daughter whose mask bit
+// cull_merge makes of lane half h and result 4 i + j: the block's first 16
+// daughters are in the last 8 results of the lanes.
+template <bool HAS_OFFS>
+__device__ __forceinline__ uint4v cull_operand(const VolumeRec &v, const DaughterRec *__restrict__ dau,
+                                               const double *__restrict__ offs, int k0, int lane) {
+    const int row = lane & 31;
+    const int bit = 15 - ((row >> 3) * 4 + (row & 3));
+    const int k = k0 + ((bit & 8) << 1) + ((row & 4) << 1) + (bit & 7);
+    float tx = 0.0f, ty = 0.0f, tz = 0.0f, r = 0.0f;
+    float n = kCullFar;  // past the last daughter: never passes
+    if (k < v.nd) {
+        const DaughterRec &D = dau[k];
+        double cx = D.tr[0], cy = D.tr[1], cz = D.tr[2];
+        if (HAS_OFFS) {
+            cx += offs[3 * k + 0];
+            cy += offs[3 * k + 1];
+            cz += offs[3 * k + 2];
+        }
+        const double s = v.cull_s;
+        tx = (float)(cx * s);
+        ty = (float)(cy * s);
+        tz = (float)(cz * s);
+        r = (float)(D.cull_r * s);
+        const float tt = fmaf(tz, tz, fmaf(ty, ty, tx * tx));
+        const float reach = kCullR + v.cull_back;
+        n = fmaf(-0x1p-15f, fmaf(reach, reach, tt), fmaf(-r, r, tt));
+        const bool near = s > 0.0 && fabsf(tx) <= kCullMax && fabsf(ty) <= kCullMax && fabsf(tz) <= kCullMax &&
+                          r <= v.cull_back;
+        if (!near) {  // (or not a number): always passes
+            tx = ty = tz = r = 0.0f;
+            n = -kCullFar;
+        }
+    }
+    unsigned int hxy, lxy, hzr, lzr, nn, rr, dummy;
+    half_split(-2.0f * tx, -2.0f * ty, hxy, lxy);
+    half_split(-2.0f * tz, -2.0f * r, hzr, lzr);
+    half_split(n * 0.015625f, 0.0f, nn, dummy);
+    const unsigned int n2 = (nn & 0xffffu) | (dummy << 16);
+    const unsigned int hz64 = (hzr & 0xffffu) | 0x54000000u;  // (64 in half precision: 0x5400)
+    const unsigned int lzsh = (lzr & 0xffffu) | (hzr & 0xffff0000u);
+    rr = (hzr >> 16) | (lzr & 0xffff0000u);
+    const bool upper = lane >= 32;
+    return uint4v{upper ? lxy : hxy, upper ? lzsh : hz64, upper ? n2 : hxy, upper ? rr : hz64};
+}
+
+// The two column operands (tracks 0..31 and 32..63) of a vector, a constant
+// and a length per lane, as above: each lane forms all 16 slots of its own
+// track, and the halves of the wavefront swap.
+__device__ __forceinline__ void cull_columns(float x, float y, float z, float c, float f, unsigned int ones,
+                                             uint4v (&col)[2]) {
+    unsigned int hxy, lxy, hzc, lzc, ff, fl;
+    half_split(x, y, hxy, lxy);
+    half_split(z, c * 0.015625f, hzc, lzc);
+    half_split(f, 0.0f, ff, fl);
+    const unsigned int lo[4] = {hxy, hzc, lxy, lzc};
+    const unsigned int hi[4] = {hxy, (hzc & 0xffffu) | (ff << 16), ones, (fl & 0xffffu) | (ff << 16)};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint2v r = __builtin_amdgcn_permlane32_swap(lo[i], hi[i], false, false);
+        col[0][i] = r.x;  // lower lanes' lo | lower lanes' hi
+        col[1][i] = r.y;  // upper lanes' lo | upper lanes' hi
+    }
+}
+
+// A wavefront's column operands: of |w|^2 - r^2 (p) and of w.e (e).
+struct CullTracks {
+    uint4v p[2], e[2];
+};
+
+// Starts moved back by v.cull_back along the unit direction. A zero
+// direction, or one whose |d|^2 overflows or is not a number, gives e = 0
+// (the test then takes the start point); the FP32 root serves unless a lane
+// that counts (`on`) has |d|^2 near the ends of its range.
+__device__ __forceinline__ void cull_tracks(const VolumeRec &v, double x, double y, double z, double ux, double uy,
+                                            double uz, bool on, CullTracks &c) {
+    float ex = (float)ux, ey = (float)uy, ez = (float)uz;
+    const float dd = fmaf(ez, ez, fmaf(ey, ey, ex * ex));
+    const bool odd = !(dd > 1e-30f && dd < 1e30f);
+    const float il = __builtin_amdgcn_rsqf(dd);
+    ex *= il;
+    ey *= il;
+    ez *= il;
+    if (__builtin_amdgcn_ballot_w64(on && odd) != 0ull) {
+        const double d2 = fma(uz, uz, fma(uy, uy, ux * ux));
+        const bool has = d2 > 0.0 && d2 < __builtin_inf();
+        const double il2 = rsqrt_fine(d2);
+        if (odd) {
+            ex = has ? (float)(ux * il2) : 0.0f;
+            ey = has ? (float)(uy * il2) : 0.0f;
+            ez = has ? (float)(uz * il2) : 0.0f;
+        }
+    }
+    const float back = -v.cull_back;
+    const double s = v.cull_s;
+    const float px = fmaf(back, ex, (float)(x * s));
+    const float py = fmaf(back, ey, (float)(y * s));
+    const float pz = fmaf(back, ez, (float)(z * s));
+    cull_columns(px, py, pz, fmaf(pz, pz, fmaf(py, py, px * px)), 0.0f, 0x54005400u, c.p);
+    cull_columns(0.5f * ex, 0.5f * ey, 0.5f * ez, fmaf(pz, ez, fmaf(py, ey, px * ex)), 0.0f, 0u, c.e);
+}
+
+__device__ __forceinline__ float16v cull_product(const uint4v &a, const uint4v &b) {
+    const float16v zero = {};
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8v, a), __builtin_bit_cast(half8v, b), zero,
+                                                  0, 0, 0);
+}
+
+// The signs of a product's 16 results in a lane (column lane % 32; result i
+// is row 8 (i / 4) + 4 (lane / 32) + i % 4), result i at bit 15 - i; of the
+// last 8 alone where the other rows hold no daughters. (A branch for each
+// group of 4 results cost more than it skipped: 54.9 to 56.4 us at 32
+// daughters and 2^22 tracks.)
+template <int N, typename F>
+__device__ __forceinline__ unsigned int cull_signs(F result) {
+    unsigned int m = 0u;
+#pragma unroll
+    for (int i = 16 - N; i < 16; ++i) m = __builtin_amdgcn_alignbit(m, __float_as_uint(result(i)), 31);
+    return m;
+}
+
+// The masks of the two halves' columns as each lane's own track's 32 rows:
+// bit k is daughter k of the block (the bytes of the lower lanes' rows and
+// the upper ones' in turn).
+__device__ __forceinline__ unsigned int cull_merge(unsigned int m0, unsigned int m1) {
+    const uint2v r = __builtin_amdgcn_permlane32_swap(m0, m1, false, false);
+    return __builtin_amdgcn_perm(r.y, r.x, 0x05010400u);
+}
+template <int N>
+__device__ __forceinline__ unsigned int cull_mask_of(const uint4v &a, const CullTracks &c) {
+    unsigned int m[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const float16v g = cull_product(a, c.p[t]);
+        const float16v b = cull_product(a, c.e[t]);
+        m[t] = cull_signs<N>([&](int i) { return fmaf(b[i], fabsf(b[i]), g[i]); });
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return cull_merge(m[0], m[1]);
+}
+// (left: daughters from the block's first on)
+__device__ __forceinline__ unsigned int cull_mask(const uint4v &a, const CullTracks &c, int left) {
+    return left <= 16 ? cull_mask_of<8>(a, c) : cull_mask_of<16>(a, c);
+}
+
+// Navigates the tracks base + u * 64 + lane (u < U, index below `count` > 0
 // past base) of one volume, leaving each track's step (as a key) and hit
 // index in S; with SURF, the hit slot also carries the surface that set the
-// step (for the adjoint).
+// step (for the adjoint). Each round's tracks are requested a round ahead
+// (with the tests on the matrix cores the wavefronts otherwise waited for
+// memory 75 % of their time).
 //
-// Without FINAL the last flush is left to the caller: the queue's length is
-// returned, its tracks holding slots.
+// Without FINAL the last batch is left to the caller: the queue's length is
+// returned.
 //
-// With SHIFTED (offsets only), the culling tests take their records from
-// `shifted`: the centres moved by this call's offsets and the thresholds of
-// the expanded test for them (k_shift_cull), so that they run as without
-// offsets; the queued pairs still form w = p - T - offset from the
-// unshifted records, as every other form does.
-template <int U, bool HAS_OFFS, bool COUNT, int KSET, bool SURF = true, bool FINAL = true, bool SHIFTED = false>
+// With TABLE the culling operands are read from `cul` (the volume's blocks,
+// or the blocks of this call's offsets); else they are formed from the
+// daughter records and the offsets, once per wavefront for the first block
+// and once per round for the others.
+struct Track {
+    double x, y, z, ux, uy, uz;
+};
+template <int U, bool HAS_OFFS, bool COUNT, int KSET, bool SURF = true, bool FINAL = true, bool TABLE = !HAS_OFFS>
 __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const DaughterRec *__restrict__ dau,
-                                                const CullRec *__restrict__ cul,
+                                                const CullBlock *__restrict__ cul,
                                                 const double *__restrict__ offs, const TracksDev &t,
                                                 int64_t base, int count, NavScratch<U> &S, int lane,
-                                                unsigned long long *census = nullptr,
-                                                const CullRec *__restrict__ shifted = nullptr) {
-    static_assert(!SHIFTED || HAS_OFFS, "shifted culling records go with offsets");
-    constexpr bool EXPLICIT = HAS_OFFS && !SHIFTED;  // tests that form w = p - T - offset
-    const CullRec *__restrict__ tcul = SHIFTED ? shifted : cul;
+                                                unsigned long long *census = nullptr) {
     int qn = 0;  // queue length (uniform)
-    int ns = 0;  // slots in use (uniform)
     const int nd = v.nd;
-    const int ndp = (nd + kCullChunk - 1) / kCullChunk * kCullChunk;
+    const TileTracks tt = tile_tracks(t, base);
+    auto operand = [&](int k0) -> uint4v {
+        if (TABLE) return *reinterpret_cast<const uint4v *>(cul[k0 / kCullBlock].a[lane]);
+        return cull_operand<HAS_OFFS>(v, dau, offs, k0, lane);
+    };
+    auto load = [&](int j) -> Track {  // (a lane past the end: the last track)
+        const unsigned int ju = (unsigned int)(j < count ? j : count - 1);
+        return Track{at32(tt.x, ju), at32(tt.y, ju), at32(tt.z, ju), at32(tt.ux, ju), at32(tt.uy, ju), at32(tt.uz, ju)};
+    };
+    Track next = load(lane);
+    uint4v first = {};
+    if (nd > 0) first = operand(0);
 #pragma unroll 1
     for (int u = 0; u < U; ++u) {
         if (u * 64 >= count) break;
         const int j = u * 64 + lane;
         const bool act = j < count;
-        const unsigned long long amask = __builtin_amdgcn_ballot_w64(act);
-        const TileTracks tt = tile_tracks(t, base);
-        const unsigned int ju = act ? (unsigned int)j : 0u;
-        double x = at32(tt.x, ju), y = at32(tt.y, ju), z = at32(tt.z, ju);
-        double ux = at32(tt.ux, ju), uy = at32(tt.uy, ju), uz = at32(tt.uz, ju);
-        if (COUNT && lane == 0) atomicAdd(&census[kCensusTracks], (unsigned long long)__popcll(amask));
+        uint4v a = first;
+        Track p = next;
+        if (U > 1 && (u + 1) * 64 < count && u + 1 < U) next = load(j + 64);
         int sid;
-        const double ms = mother_step<SURF, KSET>(v, x, y, z, ux, uy, uz, sid);
+        const double ms = mother_step<SURF, KSET>(v, p.x, p.y, p.z, p.ux, p.uy, p.uz, sid);
         lds_store(&S.key[j], step_key(ms, true));
         lds_store(&S.hit[j], hit_pack(-1, sid));
-        lds_store(&S.slot_of[j], kNoSlot);
-        unsigned long long pend = 0ull;  // lanes whose track has queued pairs (uniform)
-        double pp, pe, mpx, mpy, mpz, mex, mey, mez;
-        cull_constants(x, y, z, ux, uy, uz, pp, pe, mpx, mpy, mpz, mex, mey, mez);
-        // a lane past the tile's end gets |p|^2 = +inf: its expanded tests
-        // never pass, so their ballots need no mask
-        if (!act) pp = __builtin_inf();
-        // Daughters in chunks of kCullChunk (the tables are padded to whole
-        // chunks with records that never pass): the tests of a chunk run
-        // back to back, then its pairs are appended (after a flush if they
-        // would overflow the queue or their tracks the slots).
-        for (int k0 = 0; k0 < ndp; k0 += kCullChunk) {
-            // the chunk's records, loaded together (scalar loads), with
-            // their offsets (padding records take daughter 0's: they never
-            // pass)
-            double ctx[kCullChunk], cty[kCullChunk], ctz[kCullChunk], clim[kCullChunk];
-            double cox[kCullChunk], coy[kCullChunk], coz[kCullChunk];
-#pragma unroll
-            for (int kk = 0; kk < kCullChunk; ++kk) {
-                const CullRec &Q = tcul[k0 + kk];
-                ctx[kk] = Q.tx;
-                cty[kk] = Q.ty;
-                ctz[kk] = Q.tz;
-                clim[kk] = EXPLICIT ? dau[k0 + kk].cull_r2 : Q.q;
-                if (EXPLICIT) {
-                    const int ko = k0 + kk < nd ? k0 + kk : 0;
-                    cox[kk] = offs[3 * ko + 0];
-                    coy[kk] = offs[3 * ko + 1];
-                    coz[kk] = offs[3 * ko + 2];
-                }
-            }
-            // the chunk's tests (independent, so they interleave)
-            unsigned long long cm[kCullChunk];
-#pragma unroll
-            for (int kk = 0; kk < kCullChunk; ++kk) {
-                double b, g;  // w.e and |w|^2 - shift, with w = p - centre
-                if (EXPLICIT) {
-                    // the centre moves with the offset: w formed explicitly, shift 0,
-                    // limit r2
-                    const double wx = x - ctx[kk] - cox[kk];
-                    const double wy = y - cty[kk] - coy[kk];
-                    const double wz = z - ctz[kk] - coz[kk];
-                    b = fma(wz, -mez, fma(wy, -mey, wx * -mex));
-                    g = fma(wz, wz, fma(wy, wy, wx * wx));
-                } else {
-                    // shift |T|^2, limit q (its rounding bound included)
-                    b = fma(ctz[kk], mez, fma(cty[kk], mey, fma(ctx[kk], mex, pe)));
-                    g = fma(ctz[kk], mpz, fma(cty[kk], mpy, fma(ctx[kk], mpx, pp)));
-                }
-                const double lim = clim[kk];
-                // squared distance from T to the half-line, less the shift:
-                // |w|^2 - (w.e)^2 when the line's nearest point lies ahead
-                // (w.e < 0), else |w|^2
-                const double bn = fmin(b, 0.0);
-                const double f = fma(-bn, bn, g);
-                // lanes past the tile's end are masked out (the expanded form
-                // excludes them through |p|^2)
-                const unsigned long long pass = __builtin_amdgcn_ballot_w64(f <= lim);
-                cm[kk] = EXPLICIT ? (pass & amask) : pass;
-            }
-            if (COUNT && lane == 0)
-                atomicAdd(&census[kCensusCull],
-                          (unsigned long long)__popcll(amask) * (unsigned long long)min(kCullChunk, nd - k0));
-            const unsigned long long any = (cm[0] | cm[1]) | (cm[2] | cm[3]);
-            static_assert(kCullChunk == 4, "chunk epilogue");
-            if (any == 0ull) continue;
-            if (qn > kQueueCap - 64 * kCullChunk) {  // the chunk's pairs could overflow the queue
-                nav_flush<U, HAS_OFFS, COUNT, KSET, SURF>(dau, cul, offs, t, base, S, qn, ns, lane, census);
-                pend = 0ull;
-                // the track and its test constants are read and formed again
-                // rather than kept live through the flush's evaluations
-                x = at32(tt.x, ju);
-                y = at32(tt.y, ju);
-                z = at32(tt.z, ju);
-                ux = at32(tt.ux, ju);
-                uy = at32(tt.uy, ju);
-                uz = at32(tt.uz, ju);
-                cull_constants(x, y, z, ux, uy, uz, pp, pe, mpx, mpy, mpz, mex, mey, mez);
-                if (!act) pp = __builtin_inf();
-            }
-            pend |= any;
-#pragma unroll
-            for (int kk = 0; kk < kCullChunk; ++kk) {
-                const unsigned long long m = cm[kk];
-                if (__builtin_amdgcn_inverse_ballot_w64(m))
-                    S.queue[qn + lanes_below(m)] = ((unsigned int)(k0 + kk) << 10) | (unsigned int)j;
-                qn += __popcll(m);
+        if (COUNT) {
+            const int n = __popcll(__builtin_amdgcn_ballot_w64(act));
+            if (lane == 0) {
+                atomicAdd(&census[kCensusTracks], (unsigned long long)n);
+                atomicAdd(&census[kCensusCull], (unsigned long long)n * (unsigned long long)nd);
             }
         }
-        // the round's tracks with queued pairs take slots (after a flush if
-        // there are too few: the pairs then read their tracks from global
-        // memory while they are still in the cache)
-        if (pend != 0ull) {
-            if (ns + __popcll(pend) > kSlots) {
-                nav_flush<U, HAS_OFFS, COUNT, KSET, SURF>(dau, cul, offs, t, base, S, qn, ns, lane, census);
-            } else {
-                if (__builtin_amdgcn_inverse_ballot_w64(pend)) {
-                    const int sl = ns + lanes_below(pend);
-                    lds_store(&S.x[sl], x);
-                    lds_store(&S.y[sl], y);
-                    lds_store(&S.z[sl], z);
-                    lds_store(&S.ux[sl], ux);
-                    lds_store(&S.uy[sl], uy);
-                    lds_store(&S.uz[sl], uz);
-                    lds_store(&S.slot_of[j], (unsigned char)sl);
+        // a step of 0 from the mother (a start outside it), or one that is
+        // not a number, is not beaten
+        const bool on = act && ms > 0.0;
+        if (nd == 0 || __builtin_amdgcn_ballot_w64(on) == 0ull) continue;
+        CullTracks c;
+        cull_tracks(v, p.x, p.y, p.z, p.ux, p.uy, p.uz, on, c);
+        for (int k0 = 0; k0 < nd; k0 += kCullBlock) {
+            unsigned int m = cull_mask(a, c, nd - k0);
+            const bool blocks = k0 + kCullBlock < nd;
+            if (blocks) a = operand(k0 + kCullBlock);
+            if (!on) m = 0u;
+            // each lane with a daughter left appends its lowest, while there is room
+            for (;;) {
+                const unsigned long long more = __builtin_amdgcn_ballot_w64(m != 0u);
+                if (more == 0ull) break;
+                const int at = qn + lanes_below(more);
+                if (m != 0u && at < kQueueCap) {
+                    S.pair[at] = ((unsigned int)(k0 + __builtin_ctz(m)) << 10) | (unsigned int)j;
+                    S.x[at] = p.x;
+                    S.y[at] = p.y;
+                    S.z[at] = p.z;
+                    S.ux[at] = p.ux;
+                    S.uy[at] = p.uy;
+                    S.uz[at] = p.uz;
+                    m &= m - 1u;
                 }
-                ns += __popcll(pend);
+                qn += __popcll(more);
+                if (qn >= kQueueCap) {
+                    nav_batch<U, HAS_OFFS, COUNT, KSET, SURF>(dau, offs, S, kQueueCap, lane, census);
+                    qn = 0;
+                    // the track and its operands are read and formed again
+                    // rather than kept live through the evaluations (U == 1,
+                    // compiled for 5 wavefronts per SIMD: on every path, which
+                    // takes the kernel of every kind from 112 to 96 VGPRs)
+                    p = load(j);
+                    if (U == 1 || blocks) cull_tracks(v, p.x, p.y, p.z, p.ux, p.uy, p.uz, on, c);
+                    if (U == 1 && blocks) a = operand(k0 + kCullBlock);
+                }
             }
         }
     }
-    if (FINAL) nav_flush<U, HAS_OFFS, COUNT, KSET, SURF>(dau, cul, offs, t, base, S, qn, ns, lane, census);
+    if (FINAL && qn > 0) nav_batch<U, HAS_OFFS, COUNT, KSET, SURF>(dau, offs, S, qn, lane, census);
     return qn;
 }
 
@@ -1577,7 +1659,7 @@ __device__ __forceinline__ void nav_write(const NavScratch<U> &S, const TracksDe
 // The navigator of one wavefront's tile, writing its outputs.
 template <int U, bool HAS_OFFS, bool HITPT, bool COUNT, int KSET>
 __device__ __forceinline__ void nav_compact(const VolumeRec &v, const DaughterRec *__restrict__ dau,
-                                            const CullRec *__restrict__ cul,
+                                            const CullBlock *__restrict__ cul,
                                             const double *__restrict__ offs, const TracksDev &t,
                                             int64_t base, int count, NavScratch<U> &S, int lane,
                                             double *__restrict__ step, int32_t *__restrict__ hit,
@@ -1587,77 +1669,63 @@ __device__ __forceinline__ void nav_compact(const VolumeRec &v, const DaughterRe
     nav_write<U, HITPT>(S, t, base, count, lane, step, hit, hitpt);
 }
 
-// --------------------------------------------- workgroup-pooled last flush
-// A tile's last flush holds a few dozen pairs (about 0.12 per track on the
-// toy detectors), one batch whose lanes meet every daughter kind the volume
-// holds, so that batch runs each kind's code in turn, each on a few lanes.
+// --------------------------------------------- workgroup-pooled last batch
+// A tile's last batch holds a few dozen pairs (about 0.12 per track on the
+// toy detectors), whose lanes meet every daughter kind the volume holds, so
+// that the batch runs each kind's code in turn, each on a few lanes.
 // Instead, the W wavefronts of a workgroup pool their last queues: each
 // sorts its own queue by kind class; after a barrier the workgroup's pairs
 // of each class are cut into batches of 64, and the batches, in class order,
 // are dealt to the wavefronts in turn, so that each batch runs one class's
 // code. A pair's result (key and packed hit) goes back to its place in the
-// owner's queue; after a second barrier each wavefront merges its own
-// queue's results into its running minima, as a flush of its own would.
-// Without `shared` (uniform over the workgroup: its wavefronts' work is too
-// uneven to wait for each other) each wavefront flushes its own queue
-// alone, with no barrier. (Sorting a single wavefront's queue by class
-// saves nothing: its classes still run one after another.)
+// owner's queue, over the track it was formed from; after a second barrier
+// each wavefront merges its own queue's results into its running minima, as
+// a batch of its own would. Without `shared` (uniform over the workgroup:
+// its wavefronts' work is too uneven to wait for each other) each wavefront
+// runs its own last batch alone, with no barrier. (Sorting a single
+// wavefront's queue by class saves nothing: its classes still run one after
+// another.)
 constexpr int kClassSlots = 8;
 template <int W>
 struct PoolInfo {
-    int cnt[W][kClassSlots];  // pairs of each kind class in each wavefront's sorted queue
-    int64_t base[W];          // the wavefront's first track
-    int first[W];             // its volume's first daughter and culling record
+    int cnt[W][kClassSlots];             // pairs of each kind class in each wavefront's queue
+    unsigned char order[W][kQueueCap];   // the queue's places, sorted by class
+    int first[W];                        // its volume's first daughter record
 };
 
 template <int U, int W, bool HAS_OFFS, int KSET, bool SURF>
 __device__ __forceinline__ void pool_flush(const DaughterRec *__restrict__ dau_all,
-                                           const CullRec *__restrict__ cul_all,
-                                           const double *__restrict__ offs, const TracksDev &t,
-                                           NavScratch<U> *scr, PoolInfo<W> &P, bool shared, int wave,
-                                           int first, int64_t base, int qn, int lane) {
+                                           const double *__restrict__ offs, NavScratch<U> *scr, PoolInfo<W> &P,
+                                           bool shared, int wave, int first, int qn, int lane) {
     constexpr int NK = kind_classes<KSET>();
     static_assert(NK <= kClassSlots, "class slots");
-    static_assert(kPoolMax == 128, "two entries per lane");
+    static_assert(kQueueCap == 64, "one pair per lane");
     wave = __builtin_amdgcn_readfirstlane(wave);  // (uniform: the batch loop runs on scalars)
     NavScratch<U> &S = scr[wave];
-    if (!shared || qn > kPoolMax) {
-        // a longer queue is run by its wavefront alone
-        int ns = 0;
-        nav_flush<U, HAS_OFFS, false, KSET, SURF>(dau_all + first, cul_all + first, offs, t, base, S, qn,
-                                                 ns, lane, nullptr);
-        if (!shared) return;
+    if (!shared) {
+        nav_batch<U, HAS_OFFS, false, KSET, SURF>(dau_all + first, offs, S, qn, lane, nullptr);
+        return;
     }
-    // sort the queue by class (stable, in place: both entries are read first)
+    // the queue's places by class (stable)
     {
-        const bool on0 = lane < qn, on1 = lane + 64 < qn;
-        const unsigned int e0 = on0 ? S.queue[lane] : 0u;
-        const unsigned int e1 = on1 ? S.queue[lane + 64] : 0u;
-        const DaughterRec *dau = dau_all + first;
-        const int c0 = on0 ? kind_class<KSET>(dau[e0 >> 10].shape.kind) : -1;
-        const int c1 = on1 ? kind_class<KSET>(dau[e1 >> 10].shape.kind) : -1;
-        int d0 = 0, d1 = 0, off = 0;
+        const bool on = lane < qn;
+        const int c0 = on ? kind_class<KSET>(dau_all[first + (int)(S.pair[lane] >> 10)].shape.kind) : -1;
+        int d = 0, off = 0;
 #pragma unroll
         for (int c = 0; c < NK; ++c) {
-            const unsigned long long m0 = __builtin_amdgcn_ballot_w64(c0 == c);
-            const unsigned long long m1 = __builtin_amdgcn_ballot_w64(c1 == c);
-            if (c0 == c) d0 = off + lanes_below(m0);
-            if (c1 == c) d1 = off + __popcll(m0) + lanes_below(m1);
-            const int n = __popcll(m0) + __popcll(m1);
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(c0 == c);
+            if (c0 == c) d = off + lanes_below(m);
+            const int n = __popcll(m);
             if (lane == c) P.cnt[wave][c] = n;
             off += n;
         }
-        if (on0) S.pooled.entry[d0] = e0;
-        if (on1) S.pooled.entry[d1] = e1;
-        if (lane == 0) {
-            P.base[wave] = base;
-            P.first[wave] = first;
-        }
+        if (on) P.order[wave][d] = (unsigned char)lane;
+        if (lane == 0) P.first[wave] = first;
     }
     __syncthreads();
-    // per class: each wavefront's share, the pooled count and the number of
-    // batches (uniform values)
-    int cn[W][NK], tot[NK], nbc[NK], nb = 0;
+    // per class: each wavefront's share and the number of batches (uniform
+    // values)
+    int cn[W][NK], nbc[NK], nb = 0;
 #pragma unroll
     for (int c = 0; c < NK; ++c) {
         int n = 0;
@@ -1666,7 +1734,6 @@ __device__ __forceinline__ void pool_flush(const DaughterRec *__restrict__ dau_a
             cn[w][c] = __builtin_amdgcn_readfirstlane(P.cnt[w][c]);
             n += cn[w][c];
         }
-        tot[c] = n;
         nbc[c] = (n + 63) >> 6;
         nb += nbc[c];
     }
@@ -1681,8 +1748,8 @@ __device__ __forceinline__ void pool_flush(const DaughterRec *__restrict__ dau_a
             }
         const int l = p * 64 + lane;  // the lane's pair within the class
         // the class's pairs run through the wavefronts' sorted queues in
-        // order: the owner and the pair's place in its queue
-        int own = 0, pos = 0, pre = 0;
+        // order: the owner and the pair's rank in its queue
+        int own = 0, rank = 0, pre = 0;
 #pragma unroll
         for (int w = 0; w < W; ++w) {
             int before = 0, n = 0;
@@ -1693,56 +1760,34 @@ __device__ __forceinline__ void pool_flush(const DaughterRec *__restrict__ dau_a
             }
             if (l >= pre && l < pre + n) {
                 own = w;
-                pos = before + (l - pre);
+                rank = before + (l - pre);
             }
             pre += n;
         }
         if (l < pre) {
             NavScratch<U> &O = scr[own];
-            const unsigned int e = O.pooled.entry[pos];
-            const int j = (int)(e & 1023u);
-            const int k = (int)(e >> 10);
-            const int sl = lds_load(&O.slot_of[j]);
-            double x, y, z, ux, uy, uz;
-            if (sl != kNoSlot) {
-                x = lds_load(&O.x[sl]);
-                y = lds_load(&O.y[sl]);
-                z = lds_load(&O.z[sl]);
-                ux = lds_load(&O.ux[sl]);
-                uy = lds_load(&O.uy[sl]);
-                uz = lds_load(&O.uz[sl]);
-            } else {
-                const int64_t i = P.base[own] + j;
-                x = t.x[i];
-                y = t.y[i];
-                z = t.z[i];
-                ux = t.ux[i];
-                uy = t.uy[i];
-                uz = t.uz[i];
-            }
-            const int f = P.first[own];
+            const int at = P.order[own][rank];
+            const int k = (int)(O.pair[at] >> 10);
             int sid;
-            const double s = daughter_dist_out<HAS_OFFS, KSET>(dau_all[f + k], cul_all[f + k], offs, k, x, y,
-                                                               z, ux, uy, uz, sid, c);
-            O.pooled.key[pos] = step_key(s);
-            O.pooled.hit[pos] = hit_pack(k, SURF ? sid : -1);
+            const double s = daughter_dist_out<HAS_OFFS, KSET>(dau_all[P.first[own] + k], offs, k, O.x[at], O.y[at],
+                                                               O.z[at], O.ux[at], O.uy[at], O.uz[at], sid, c);
+            O.x[at] = __longlong_as_double((long long)step_key(s));
+            O.y[at] = __longlong_as_double((long long)hit_pack(k, SURF ? sid : -1));
         }
     }
     __syncthreads();
     // each wavefront merges its own pairs' results
-    for (int e0 = 0; e0 < qn; e0 += 64) {
-        const int e = e0 + lane;
-        if (e < qn) merge_key(S, (int)(S.pooled.entry[e] & 1023u), S.pooled.key[e], S.pooled.hit[e]);
-    }
+    if (lane < qn)
+        merge_key(S, (int)(S.pair[lane] & 1023u), (unsigned long long)__double_as_longlong(S.x[lane]),
+                  (int)__double_as_longlong(S.y[lane]));
 }
 
 // The navigator of the W tiles of a workgroup (wavefront `wave` holds
-// `count` tracks from `base` of volume v, whose records start at `first`;
-// count may be 0, the wavefront then only taking part in the pooled flush),
+// `count` tracks from `base` of volume v (culling blocks `cul`); count may be 0, the wavefront then only taking part in the pooled flush),
 // the last flush pooled over the workgroup when `shared`.
 template <int U, int W, bool HAS_OFFS, bool HITPT, int KSET>
 __device__ __forceinline__ void nav_compact_pooled(const VolumeRec &v, const DaughterRec *__restrict__ dau_all,
-                                                   const CullRec *__restrict__ cul_all, int first,
+                                                   const CullBlock *__restrict__ cul, int first,
                                                    const double *__restrict__ offs, const TracksDev &t,
                                                    int64_t base, int count, NavScratch<U> *scr,
                                                    PoolInfo<W> &P, bool shared, int wave, int lane,
@@ -1750,23 +1795,41 @@ __device__ __forceinline__ void nav_compact_pooled(const VolumeRec &v, const Dau
                                                    double *__restrict__ hitpt) {
     int qn = 0;
     if (count > 0)
-        qn = nav_compact_core<U, HAS_OFFS, false, KSET, false, false>(v, dau_all + first, cul_all + first, offs,
-                                                                     t, base, count, scr[wave], lane);
-    pool_flush<U, W, HAS_OFFS, KSET, false>(dau_all, cul_all, offs, t, scr, P, shared, wave, first, base, qn,
-                                            lane);
+        qn = nav_compact_core<U, HAS_OFFS, false, KSET, false, false>(v, dau_all + first, cul, offs, t, base,
+                                                                     count, scr[wave], lane);
+    pool_flush<U, W, HAS_OFFS, KSET, false>(dau_all, offs, scr, P, shared, wave, first, qn, lane);
     nav_write<U, HITPT>(scr[wave], t, base, count, lane, step, hit, hitpt);
 }
 
 // ---------------------------- compacted navigator safety and localization
-// The same queue for the navigator's other two tasks. Safety: a daughter is
-// queued for a point when |w| < s_mother + r (its Safety is at least
-// |w| - r, so otherwise it cannot go below the mother's, hence not below the
-// minimum); the minimum is merged as a 64-bit key like the step (-0 as +0).
+// The same queue for the navigator's other two tasks, one round of 64 points
+// per wavefront. Safety: a daughter is queued for a point when |w| < s + r
+// with s the mother's Safety (the daughter's is at least |w| - r, so
+// otherwise it cannot go below the mother's, hence not below the minimum);
+// the minimum is merged as a 64-bit key like the step (-0 as +0).
 // Localization: a daughter is queued for a point inside the mother when
 // |w| <= r; the lowest index of a queued daughter that contains the point
-// wins (an integer LDS min). The culling tests form w = p - T explicitly, as
-// points may lie outside the mother. The sequential loops report -0 as +0
-// too, so both forms give the same bits.
+// wins (an integer LDS min). Both tests are the first product of the
+// navigator's culling tests alone (|w|^2 - r^2 - delta, less 2 r s + s^2 for
+// the safety), one VALU instruction per pair after it, with the same
+// operands of the daughters: a start's bound 256 + L holds for the point and
+// for s here, and a point where it does not (far outside the mother)
+// takes every daughter. The sequential loops report -0 as +0 too, so both
+// forms give the same bits.
+//
+// The mother's Safety alone lets 1.7 pairs per point pass on the toy detector
+// (14 for the point of a wavefront that has the most, and its lanes append
+// one after another). The nearest daughter bounds the minimum better. With G
+// the smallest |w|^2 - r^2 - delta over the daughters, G > 0 puts the point
+// outside every sphere, and the nearest daughter's Safety is at most |w| - b
+// where a ball of radius b about its centre is solid (the way to the centre
+// meets the surface; (|w| - b)^2 <= |w|^2 - b^2), sqrt(|w|^2 + a^2) where its
+// hole is a full circle of radius a at z = 0, and |w| + q with q the distance
+// of any of its surface's points from the centre. With the volume's largest
+// r^2 + c (c = -b^2 or a^2) the minimum is at most sqrt(G + max(r^2 + c)): one
+// v_min3 per two pairs and the products once more with s replaced, for 0.83
+// pairs per point and 4.6 appends (a CPU simulation), one batch per
+// wavefront where there were two.
 __device__ __forceinline__ unsigned long long safety_key(double s) {
     return s == s ? step_key(s) : ~0ull;
 }
@@ -1775,32 +1838,27 @@ __device__ __forceinline__ unsigned long long safety_key(double s) {
 // the wavefront's points, which the queued pairs read back from LDS instead
 // of global memory (each lane stores its own point; the batches read them
 // later in the same wavefront's program order).
-template <int U>
 struct PointScratch : PointQueue {
-    static_assert(U == 1, "one round of 64 points per wavefront");
     double px[64], py[64], pz[64];
 };
 
-template <int MODE, bool HAS_OFFS, int KSET, int U>  // MODE 0: safety, 1: locate
-__device__ __forceinline__ void point_flush(const DaughterRec *__restrict__ dau,
-                                            const CullRec *__restrict__ cul,
-                                            const double *__restrict__ offs, PointScratch<U> &S,
-                                            int qn, int lane) {
+template <int MODE, bool HAS_OFFS, int KSET>  // MODE 0: safety, 1: locate
+__device__ __forceinline__ void point_flush(const DaughterRec *__restrict__ dau, const double *__restrict__ offs,
+                                            PointScratch &S, int qn, int lane) {
     for (int e0 = 0; e0 < qn; e0 += 64) {
         const int e = e0 + lane;
         if (e < qn) {
             const unsigned int q = S.queue[e];
             const int j = (int)(q & 1023u);
             const int k = (int)(q >> 10);
-            const CullRec &Q = cul[k];
-            double wx = lds_load(&S.px[j]) - Q.tx, wy = lds_load(&S.py[j]) - Q.ty,
-                   wz = lds_load(&S.pz[j]) - Q.tz;
+            const DaughterRec &D = dau[k];
+            double wx = lds_load(&S.px[j]) - D.tr[0], wy = lds_load(&S.py[j]) - D.tr[1],
+                   wz = lds_load(&S.pz[j]) - D.tr[2];
             if (HAS_OFFS) {
                 wx -= offs[3 * k + 0];
                 wy -= offs[3 * k + 1];
                 wz -= offs[3 * k + 2];
             }
-            const DaughterRec &D = dau[k];
             const double *R = D.rot;
             const double lx = fma(R[6], wz, fma(R[3], wy, R[0] * wx));
             const double ly = fma(R[7], wz, fma(R[4], wy, R[1] * wx));
@@ -1815,134 +1873,112 @@ __device__ __forceinline__ void point_flush(const DaughterRec *__restrict__ dau,
     }
 }
 
+// Daughters from which on the bound is formed (toy detector's grid, 2^20
+// points: 4 daughters 13.5 us without it and 14.5 with, 32 30.6 and 18.7, 64
+// 56.4 and 31.0).
+constexpr int kNearest = 8;
+
+// The bound of the minimum from G > 0 (in the tests' units; widened by more
+// than the products' and the roots' rounding).
+__device__ __forceinline__ float nearest_bound(const VolumeRec &v, float g) {
+    float b = __builtin_amdgcn_sqrtf(fmaxf(g + v.safe_d, 0.0f));
+    if (v.safe_q >= 0.0f) b = fmaxf(b, __builtin_amdgcn_sqrtf(g + v.safe_r2) + v.safe_q);
+    return fmaf(b, 0x1p-16f, b);
+}
+
 // Safety (MODE 0, out_s) or localization (MODE 1, out_w) of the points
-// base + u * 64 + lane (u < U, index below `count` past base). In
-// localization mode the key slots hold whether the point is in the mother.
-template <int MODE, bool HAS_OFFS, int KSET, int U>
+// base + lane (lane < count).
+template <int MODE, bool HAS_OFFS, int KSET>
 __device__ __forceinline__ void point_compact(const VolumeRec &v, const DaughterRec *__restrict__ dau,
-                                              const CullRec *__restrict__ cul,
+                                              const CullBlock *__restrict__ cul,
                                               const double *__restrict__ offs, const TracksDev &t,
-                                              int64_t base, int count, PointScratch<U> &S, int lane,
+                                              int64_t base, int count, PointScratch &S, int lane,
                                               double *__restrict__ out_s,
                                               int32_t *__restrict__ out_w) {
-    int qn = 0;
     const int nd = v.nd;
-    const int ndp = (nd + kCullChunk - 1) / kCullChunk * kCullChunk;
-#pragma unroll 1
-    for (int u = 0; u < U; ++u) {
-        if (u * 64 >= count) break;
-        const int j = u * 64 + lane;
-        const bool act = j < count;
-        const int64_t i = base + (act ? j : 0);
-        const double x = t.x[i], y = t.y[i], z = t.z[i];
-        lds_store(&S.px[j], x);
-        lds_store(&S.py[j], y);
-        lds_store(&S.pz[j], z);
-        double reach = 0.0;
-        bool in_m = false;
-        if (MODE == 0) {
-            const double ms = any_safety<KSET>(v.mother, v.pcon, x, y, z);
-            lds_store(&S.key[j], safety_key(ms));
-            reach = ms;
-        } else {
-            in_m = any_contains<KSET>(v.mother, v.pcon, x, y, z);
-            lds_store(&S.key[j], (unsigned long long)in_m);
-            lds_store(&S.hit[j], 0x7fffffff);
-        }
-        const unsigned long long amask = __builtin_amdgcn_ballot_w64(MODE == 0 ? act : (act && in_m));
-        if (amask == 0ull) continue;
-        // per-point constants of the expanded test (no offsets): |p|^2, -2 p,
-        // and for the safety 2 reach and reach^2; a lane outside amask gets
-        // |p|^2 = +inf, so that none of its expanded tests passes and their
-        // ballots need no mask (nor do padding records, whose q is -inf)
-        double pp = fma(z, z, fma(y, y, x * x));
-        if (!((amask >> lane) & 1ull)) pp = __builtin_inf();
-        const double mpx = -2.0 * x, mpy = -2.0 * y, mpz = -2.0 * z;
-        const double reach2 = 2.0 * reach, rr = reach * reach;
-        for (int k0 = 0; k0 < ndp; k0 += kCullChunk) {
-            if (qn > kQueueCap - 64 * kCullChunk) {
-                point_flush<MODE, HAS_OFFS, KSET, U>(dau, cul, offs, S, qn, lane);
-                qn = 0;
-            }
-            // the chunk's records and offsets, loaded together before its
-            // tests (scalar loads; padding records take daughter 0's offsets:
-            // they never pass)
-            double ctx[kCullChunk], cty[kCullChunk], ctz[kCullChunk], cr[kCullChunk], clim[kCullChunk];
-            double cox[kCullChunk], coy[kCullChunk], coz[kCullChunk];
-#pragma unroll
-            for (int kk = 0; kk < kCullChunk; ++kk) {
-                const CullRec &Q = cul[k0 + kk];
-                const DaughterRec &D = dau[k0 + kk];
-                ctx[kk] = Q.tx;
-                cty[kk] = Q.ty;
-                ctz[kk] = Q.tz;
-                cr[kk] = D.cull_r;
-                clim[kk] = HAS_OFFS ? D.cull_r2 : Q.q;
-                if (HAS_OFFS) {
-                    const int ko = k0 + kk < nd ? k0 + kk : 0;
-                    cox[kk] = offs[3 * ko + 0];
-                    coy[kk] = offs[3 * ko + 1];
-                    coz[kk] = offs[3 * ko + 2];
-                }
-            }
-            unsigned long long cm[kCullChunk];
-#pragma unroll
-            for (int kk = 0; kk < kCullChunk; ++kk) {
-                const int k = k0 + kk;
-                bool pass;
-                if (HAS_OFFS) {
-                    // the centre moves with the offset: |w|^2 formed explicitly
-                    const double wx = x - ctx[kk] - cox[kk];
-                    const double wy = y - cty[kk] - coy[kk];
-                    const double wz = z - ctz[kk] - coz[kk];
-                    const double ww = fma(wz, wz, fma(wy, wy, wx * wx));
-                    if (MODE == 0) {
-                        const double lim = reach + cr[kk];
-                        pass = ww < lim * lim;
-                    } else {
-                        pass = ww <= clim[kk];
-                    }
-                } else {
-                    // |w|^2 - |T|^2 = |p|^2 - 2 p.T against the thresholds less
-                    // |T|^2: r^2 - |T|^2 (q, its rounding bound included) for
-                    // the containment, (reach + r)^2 - |T|^2 = q + 2 r reach +
-                    // reach^2 for a daughter that may be nearer than reach
-                    // (reach is at most the mother's bounding radius R for a
-                    // point inside the mother, so every term stays within the
-                    // (3 R + 2 |T|)^2 that the bound of q covers)
-                    const double g = fma(ctz[kk], mpz, fma(cty[kk], mpy, fma(ctx[kk], mpx, pp)));
-                    if (MODE == 0)
-                        pass = g < fma(cr[kk], reach2, clim[kk]) + rr;
-                    else
-                        pass = g <= clim[kk];
-                }
-                // with offsets, lanes outside amask and padding records (k >= nd,
-                // whose radius is 0) are masked here
-                const unsigned long long bal = __builtin_amdgcn_ballot_w64(pass);
-                cm[kk] = HAS_OFFS ? bal & (k < nd ? amask : 0ull) : bal;
-            }
-#pragma unroll
-            for (int kk = 0; kk < kCullChunk; ++kk) {
-                const unsigned long long m = cm[kk];
-                if (m == 0ull) continue;
-                if (__builtin_amdgcn_inverse_ballot_w64(m))
-                    S.queue[qn + lanes_below(m)] = ((unsigned int)(k0 + kk) << 10) | (unsigned int)j;
-                qn += __popcll(m);
-            }
-        }
+    auto operand = [&](int k0) -> uint4v {
+        if (!HAS_OFFS) return *reinterpret_cast<const uint4v *>(cul[k0 / kCullBlock].a[lane]);
+        return cull_operand<HAS_OFFS>(v, dau, offs, k0, lane);
+    };
+    uint4v a = {};
+    if (nd > 0) a = operand(0);
+    const bool act = lane < count;
+    const int64_t i = base + (act ? lane : 0);
+    const double x = t.x[i], y = t.y[i], z = t.z[i];
+    lds_store(&S.px[lane], x);
+    lds_store(&S.py[lane], y);
+    lds_store(&S.pz[lane], z);
+    double reach = 0.0;
+    bool in_m = false;
+    if (MODE == 0) {
+        reach = any_safety<KSET>(v.mother, v.pcon, x, y, z);
+        lds_store(&S.key[lane], safety_key(reach));
+    } else {
+        in_m = any_contains<KSET>(v.mother, v.pcon, x, y, z);
+        lds_store(&S.hit[lane], 0x7fffffff);
     }
-    point_flush<MODE, HAS_OFFS, KSET, U>(dau, cul, offs, S, qn, lane);
-#pragma unroll 1
-    for (int u = 0; u < U; ++u) {
-        const int j = u * 64 + lane;
-        if (j < count) {
-            const int64_t o = base + j;
-            if (MODE == 0) {
-                out_s[o] = key_step(lds_load(&S.key[j]));
-            } else {
-                const int w = lds_load(&S.hit[j]);
-                out_w[o] = lds_load(&S.key[j]) == 0ull ? -2 : (w != 0x7fffffff ? w : -1);
+    const bool on = MODE == 0 ? act : (act && in_m);
+    if (nd > 0 && __builtin_amdgcn_ballot_w64(on) != 0ull) {
+        const double s = v.cull_s;
+        const float px = (float)(x * s), py = (float)(y * s), pz = (float)(z * s);
+        const float pp = fmaf(pz, pz, fmaf(py, py, px * px));
+        uint4v col[2];
+        float f = MODE == 0 ? (float)(reach * s) : 0.0f;
+        if (MODE == 0 && nd >= kNearest) {
+            cull_columns(px, py, pz, pp, 0.0f, 0x54005400u, col);
+            int g[2] = {0x7f000000, 0x7f000000};  // as integers: any negative result stays the smallest
+            uint4v b = a;
+            for (int k0 = 0; k0 < nd; k0 += kCullBlock) {
+                if (k0 > 0) b = operand(k0);
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const float16v r = cull_product(b, col[c]);
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) g[c] = min(g[c], __float_as_int(r[i]));
+                }
             }
+            const uint2v own = __builtin_amdgcn_permlane32_swap((unsigned int)g[0], (unsigned int)g[1], false, false);
+            const int gi = min((int)own.x, (int)own.y);
+            if (gi > 0) f = fminf(f, nearest_bound(v, __int_as_float(gi)));
+        }
+        const float lim = kCullR + v.cull_back;
+        const bool near = pp <= lim * lim && f <= lim;  // else (or not a number) takes every daughter
+        cull_columns(px, py, pz, MODE == 0 ? fmaf(-f, f, pp) : pp, f, 0x54005400u, col);
+        int qn = 0;
+        for (int k0 = 0; k0 < nd; k0 += kCullBlock) {
+            unsigned int h[2];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const float16v g = cull_product(a, col[c]);
+                h[c] = cull_signs<16>([&](int r) { return g[r]; });
+            }
+            unsigned int m = cull_merge(h[0], h[1]);
+            if (!near) m = nd - k0 >= kCullBlock ? ~0u : (1u << (nd - k0)) - 1u;
+            if (!on) m = 0u;
+            if (k0 + kCullBlock < nd) a = operand(k0 + kCullBlock);
+            for (;;) {  // each lane with a daughter left appends its lowest
+                const unsigned long long more = __builtin_amdgcn_ballot_w64(m != 0u);
+                if (more == 0ull) break;
+                if (qn > 512 - 64) {
+                    point_flush<MODE, HAS_OFFS, KSET>(dau, offs, S, qn, lane);
+                    qn = 0;
+                }
+                if (m != 0u) {
+                    const int k = k0 + __builtin_ctz(m);
+                    S.queue[qn + lanes_below(more)] = ((unsigned int)k << 10) | (unsigned int)lane;
+                    m &= m - 1u;
+                }
+                qn += __popcll(more);
+            }
+        }
+        point_flush<MODE, HAS_OFFS, KSET>(dau, offs, S, qn, lane);
+    }
+    if (act) {
+        if (MODE == 0) {
+            out_s[base + lane] = key_step(lds_load(&S.key[lane]));
+        } else {
+            const int w = lds_load(&S.hit[lane]);
+            out_w[base + lane] = !in_m ? -2 : (w != 0x7fffffff ? w : -1);
         }
     }
 }
@@ -1953,20 +1989,18 @@ __device__ __forceinline__ void point_compact(const VolumeRec &v, const Daughter
 // compacted form above).
 template <bool HAS_OFFS, int KSET = kSetAll>
 __device__ __forceinline__ double nav_safety(const VolumeRec &v, const DaughterRec *__restrict__ dau,
-                                             const CullRec *__restrict__ cul,
                                              const double *__restrict__ offs, double x, double y,
                                              double z) {
     double best = any_safety<KSET>(v.mother, v.pcon, x, y, z);
     const int nd = v.nd;
     for (int k = 0; k < nd; ++k) {
-        const CullRec &Q = cul[k];
-        double wx = x - Q.tx, wy = y - Q.ty, wz = z - Q.tz;
+        const DaughterRec &D = dau[k];
+        double wx = x - D.tr[0], wy = y - D.tr[1], wz = z - D.tr[2];
         if (HAS_OFFS) {
             wx -= offs[3 * k + 0];
             wy -= offs[3 * k + 1];
             wz -= offs[3 * k + 2];
         }
-        const DaughterRec &D = dau[k];
         const double *R = D.rot;
         const double lx = fma(R[6], wz, fma(R[3], wy, R[0] * wx));
         const double ly = fma(R[7], wz, fma(R[4], wy, R[1] * wx));
@@ -1980,21 +2014,19 @@ __device__ __forceinline__ double nav_safety(const VolumeRec &v, const DaughterR
 // -2 outside the mother.
 template <bool HAS_OFFS, int KSET = kSetAll>
 __device__ __forceinline__ int nav_locate(const VolumeRec &v, const DaughterRec *__restrict__ dau,
-                                          const CullRec *__restrict__ cul,
                                           const double *__restrict__ offs, double x, double y,
                                           double z) {
     int where = any_contains<KSET>(v.mother, v.pcon, x, y, z) ? -1 : -2;
     const int nd = v.nd;
     for (int k = 0; k < nd; ++k) {
         if (__ballot(where == -1) == 0) break;  // every lane placed
-        const CullRec &Q = cul[k];
-        double wx = x - Q.tx, wy = y - Q.ty, wz = z - Q.tz;
+        const DaughterRec &D = dau[k];
+        double wx = x - D.tr[0], wy = y - D.tr[1], wz = z - D.tr[2];
         if (HAS_OFFS) {
             wx -= offs[3 * k + 0];
             wy -= offs[3 * k + 1];
             wz -= offs[3 * k + 2];
         }
-        const DaughterRec &D = dau[k];
         const double *R = D.rot;
         const double lx = fma(R[6], wz, fma(R[3], wy, R[0] * wx));
         const double ly = fma(R[7], wz, fma(R[4], wy, R[1] * wx));

@@ -14,14 +14,14 @@ constexpr int kBackwardMaxBlocks = 2048;
 hipError_t launch_shape_query(const ShapeRec &s, const PconRec &pc, int query, const TracksDev &t,
                               void *out, hipStream_t st);
 
-hipError_t launch_nav_basket(const VolumeRec *vol, const DaughterRec *dau, const CullRec *cul,
+hipError_t launch_nav_basket(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul,
                              const TracksDev &t, const double *offs, double *step, int32_t *hit,
                              double *hitpt, bool cull, int kset, hipStream_t st);
 
-hipError_t launch_nav_safety(const VolumeRec *vol, const DaughterRec *dau, const CullRec *cul,
+hipError_t launch_nav_safety(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul,
                              const TracksDev &t, const double *offs, double *out, bool cull,
                              int kset, hipStream_t st);
-hipError_t launch_nav_locate(const VolumeRec *vol, const DaughterRec *dau, const CullRec *cul,
+hipError_t launch_nav_locate(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul,
                              const TracksDev &t, const double *offs, int32_t *out, bool cull,
                              int kset, hipStream_t st);
 
@@ -36,7 +36,7 @@ constexpr int kQueueStride = 64;  // in unsigned ints
 struct PersistentArgs {
     const VolumeRec *vols;
     const DaughterRec *dau;
-    const CullRec *cul;
+    const CullBlock *cul;
     const Tile *tiles;
     int32_t ntiles;
     unsigned int *cursors;       // kQueues * kQueueStride
@@ -85,13 +85,18 @@ int backward_blocks(int64_t n);
 constexpr size_t kScratchDoubles = (size_t)kBackwardMaxBlocks * 3 * 64;  // 3 MiB
 hipError_t scratch_partials(double **out);
 
-// shift_buf: room for the volume's culling records (nd rounded up to whole
-// chunks) moved by the offsets, written by a small kernel before the adjoint
-// when culling with offsets; NULL to cull with the offsets applied in every
-// test instead.
-hipError_t launch_backward(const VolumeRec *vol, const DaughterRec *dau, const CullRec *cul, int nd,
+// Writes the culling blocks of nvol volumes (of at most max_nd > 0 daughters).
+hipError_t launch_cull_blocks(const VolumeRec *vols, int nvol, int max_nd, const DaughterRec *dau, CullBlock *out,
+                              hipStream_t st);
+
+// shift_buf: room for the volume's culling blocks moved by the offsets,
+// written by a small kernel before the adjoint when culling with offsets;
+// NULL to form them in the adjoint kernel instead. dau_all is the geometry's
+// daughter table, dau the volume's part of it.
+hipError_t launch_backward(const VolumeRec *vol, const DaughterRec *dau_all, const DaughterRec *dau,
+                           const CullBlock *cul, int nd,
                            const TracksDev &t, const double *offs, const double *gstep,
                            const double *ghit, double *g_o, double *g_d, double *partial,
-                           double *g_off, bool cull, int kset, CullRec *shift_buf, hipStream_t st);
+                           double *g_off, bool cull, int kset, CullBlock *shift_buf, hipStream_t st);
 
 }  // namespace gn

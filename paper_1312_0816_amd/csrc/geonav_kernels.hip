@@ -15,8 +15,8 @@
 //                    of many volumes in one launch, one wavefront per tile;
 //  k_nav_persistent  the same with a machine-sized grid whose wavefronts
 //                    pull tiles from per-XCD queues;
-//  k_shift_cull      a volume's culling records moved by the daughter offsets
-//                    of one adjoint call;
+//  k_cull_blocks     the daughters' operands of the culling tests, for a
+//                    geometry or moved by one adjoint call's offsets;
 //  k_nav_backward    adjoint of the navigator (recompute + implicit-function
 //                    gradient of the surface that set the step) with
 //                    per-workgroup partial sums of the offset gradient;
@@ -97,14 +97,17 @@ hipError_t launch_shape_query(const ShapeRec &s, const PconRec &pc, int query, c
 // ---------------------------------------------------------- basket navigator
 // With culling, one wavefront takes U rounds of 64 tracks (compacted
 // evaluation; more tracks per wavefront fill more lanes of each batch of
-// queued pairs).
-// Volumes holding every kind: the polycone's code would take the kernel to
-// 102 VGPRs, 4 wavefronts per SIMD; held to 96 (5 wavefronts, a few bytes
-// spilled to scratch) the mixed detector's navigator runs 7 % faster.
+// queued pairs). One round: 86-96 VGPRs, 5 wavefronts per SIMD, so that a
+// basket of 300k tracks runs in one go (the mixed detector's 300007: 19.2 to
+// 15.8 us, 20.5 at 4 wavefronts). More rounds: the next round's tracks are
+// held in registers, 118-128 VGPRs, 4 wavefronts per SIMD; held to 96 the
+// kernel spills 25 (124 us against 52 on the toy detector's 2^22 tracks, 75 us
+// with the FP64 culling tests before the matrix cores; 4.8 TB/s of the 60 B
+// per track, 1 GiB copies reach 5.0).
 template <bool HAS_OFFS, bool HITPT, bool CULL, int KSET, int U = 1>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(KSET == kSetAll ? 5 : 1))) void k_nav_basket(const VolumeRec *__restrict__ vol,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? (U == 1 ? 5 : 4) : 1))) void k_nav_basket(const VolumeRec *__restrict__ vol,
                                                        const DaughterRec *__restrict__ dau,
-                                                       const CullRec *__restrict__ cul,
+                                                       const CullBlock *__restrict__ cul,
                                                        TracksDev t, const double *__restrict__ offs,
                                                        double *__restrict__ step,
                                                        int32_t *__restrict__ hit,
@@ -140,7 +143,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(KSET == 
     const double ux = t.ux[i], uy = t.uy[i], uz = t.uz[i];
     double best;
     int h, sid;
-    nav_track<HAS_OFFS, false, false, KSET>(*vol, dau, cul, offs, x, y, z, ux, uy, uz, best, h, sid);
+    nav_track<HAS_OFFS, false, false, KSET>(*vol, dau, offs, x, y, z, ux, uy, uz, best, h, sid);
     step[i] = best;
     hit[i] = h;
     if (HITPT) {
@@ -153,7 +156,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(KSET == 
 
 template <bool CULL, int KSET, int U = 1>
 static void launch_basket_variant(dim3 grid, const VolumeRec *vol, const DaughterRec *dau,
-                                  const CullRec *cul, const TracksDev &t, const double *offs, double *step, int32_t *hit,
+                                  const CullBlock *cul, const TracksDev &t, const double *offs, double *step, int32_t *hit,
                                   double *hitpt, hipStream_t st) {
     const dim3 block(kBlock);
     if (offs) {
@@ -167,13 +170,11 @@ static void launch_basket_variant(dim3 grid, const VolumeRec *vol, const Daughte
 
 // Baskets of at least kBasketWide tracks run 4 rounds per wavefront (still
 // about 4096 wavefronts, several per SIMD); smaller baskets one round. (8
-// rounds when the volume holds every kind, which fills each batch of queued
-// pairs better, gave 5 % with the running minima in LDS alone; with the
-// track cache beside them its LDS allows 3 wavefronts per SIMD instead of
-// 5: 162 against 141 us on a 2^22-track basket of the mixed detector.)
+// rounds: toy detector 55.9 against 52.2 us at 2^22 tracks, mixed 95 against
+// 77: about 60 pairs per tile, often a second batch of a few.)
 constexpr int64_t kBasketWide = (int64_t)1 << 20;
 
-hipError_t launch_nav_basket(const VolumeRec *vol, const DaughterRec *dau, const CullRec *cul,
+hipError_t launch_nav_basket(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul,
                              const TracksDev &t, const double *offs, double *step, int32_t *hit,
                              double *hitpt, bool cull, int kset, hipStream_t st) {
     if (t.n == 0) return hipSuccess;
@@ -190,67 +191,70 @@ hipError_t launch_nav_basket(const VolumeRec *vol, const DaughterRec *dau, const
 }
 
 // -------------------------------------------------- safety and locate
-template <bool HAS_OFFS, bool CULL, int KSET, int U = 1>
-__global__ __launch_bounds__(kBlock) void k_nav_safety(const VolumeRec *__restrict__ vol,
+template <bool HAS_OFFS, bool CULL, int KSET>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_nav_safety(const VolumeRec *__restrict__ vol,
                                                        const DaughterRec *__restrict__ dau,
-                                                       const CullRec *__restrict__ cul, TracksDev t,
+                                                       const CullBlock *__restrict__ cul, TracksDev t,
                                                        const double *__restrict__ offs,
                                                        double *__restrict__ out) {
     if constexpr (CULL) {
-        __shared__ PointScratch<U> scr[kBlock / 64];
+        __shared__ PointScratch scr[kBlock / 64];
         const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // (uniform)
-        const int64_t base = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * 64 * U;
+        const int64_t base = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * 64;
         if (base >= t.n) return;
-        const int count = t.n - base < 64 * U ? (int)(t.n - base) : 64 * U;
-        point_compact<0, HAS_OFFS, KSET, U>(*vol, dau, cul, offs, t, base, count, scr[wave],
+        const int count = t.n - base < 64 ? (int)(t.n - base) : 64;
+        point_compact<0, HAS_OFFS, KSET>(*vol, dau, cul, offs, t, base, count, scr[wave],
                                             (int)(threadIdx.x & 63), out, nullptr);
         return;
     }
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= t.n) return;
-    out[i] = nav_safety<HAS_OFFS, KSET>(*vol, dau, cul, offs, t.x[i], t.y[i], t.z[i]);
+    out[i] = nav_safety<HAS_OFFS, KSET>(*vol, dau, offs, t.x[i], t.y[i], t.z[i]);
 }
 
-template <bool HAS_OFFS, bool CULL, int KSET, int U = 1>
-__global__ __launch_bounds__(kBlock) void k_nav_locate(const VolumeRec *__restrict__ vol,
+template <bool HAS_OFFS, bool CULL, int KSET>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_nav_locate(const VolumeRec *__restrict__ vol,
                                                        const DaughterRec *__restrict__ dau,
-                                                       const CullRec *__restrict__ cul, TracksDev t,
+                                                       const CullBlock *__restrict__ cul, TracksDev t,
                                                        const double *__restrict__ offs,
                                                        int32_t *__restrict__ out) {
     if constexpr (CULL) {
-        __shared__ PointScratch<U> scr[kBlock / 64];
+        __shared__ PointScratch scr[kBlock / 64];
         const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // (uniform)
-        const int64_t base = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * 64 * U;
+        const int64_t base = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * 64;
         if (base >= t.n) return;
-        const int count = t.n - base < 64 * U ? (int)(t.n - base) : 64 * U;
-        point_compact<1, HAS_OFFS, KSET, U>(*vol, dau, cul, offs, t, base, count, scr[wave],
+        const int count = t.n - base < 64 ? (int)(t.n - base) : 64;
+        point_compact<1, HAS_OFFS, KSET>(*vol, dau, cul, offs, t, base, count, scr[wave],
                                             (int)(threadIdx.x & 63), nullptr, out);
         return;
     }
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= t.n) return;
-    out[i] = nav_locate<HAS_OFFS, KSET>(*vol, dau, cul, offs, t.x[i], t.y[i], t.z[i]);
+    out[i] = nav_locate<HAS_OFFS, KSET>(*vol, dau, offs, t.x[i], t.y[i], t.z[i]);
 }
 
-template <bool CULL, int KSET, int U = 1>
+template <bool CULL, int KSET>
 static void launch_safety_variant(dim3 grid, const VolumeRec *vol, const DaughterRec *dau,
-                                  const CullRec *cul, const TracksDev &t, const double *offs,
+                                  const CullBlock *cul, const TracksDev &t, const double *offs,
                                   double *out, hipStream_t st) {
-    if (offs) hipLaunchKernelGGL((k_nav_safety<true, CULL, KSET, U>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
-    else hipLaunchKernelGGL((k_nav_safety<false, CULL, KSET, U>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
+    if (offs) hipLaunchKernelGGL((k_nav_safety<true, CULL, KSET>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
+    else hipLaunchKernelGGL((k_nav_safety<false, CULL, KSET>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
 }
 
-template <bool CULL, int KSET, int U = 1>
+template <bool CULL, int KSET>
 static void launch_locate_variant(dim3 grid, const VolumeRec *vol, const DaughterRec *dau,
-                                  const CullRec *cul, const TracksDev &t, const double *offs,
+                                  const CullBlock *cul, const TracksDev &t, const double *offs,
                                   int32_t *out, hipStream_t st) {
-    if (offs) hipLaunchKernelGGL((k_nav_locate<true, CULL, KSET, U>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
-    else hipLaunchKernelGGL((k_nav_locate<false, CULL, KSET, U>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
+    if (offs) hipLaunchKernelGGL((k_nav_locate<true, CULL, KSET>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
+    else hipLaunchKernelGGL((k_nav_locate<false, CULL, KSET>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
 }
 
 // One round of 64 points per wavefront: with four (as the basket navigator
-// takes for large baskets) both ran 5-15 % slower on the toy detector.
-hipError_t launch_nav_safety(const VolumeRec *vol, const DaughterRec *dau, const CullRec *cul,
+// takes for large baskets) both ran 5-15 % slower on the toy detector. At
+// 2^22 points there, before and after the tests on the matrix cores and the
+// safety's bound from the nearest sphere: safety 105.7 to 74.8 us, localization
+// 37.0 to 30.4.
+hipError_t launch_nav_safety(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul,
                              const TracksDev &t, const double *offs, double *out, bool cull,
                              int kset, hipStream_t st) {
     if (t.n == 0) return hipSuccess;
@@ -260,7 +264,7 @@ hipError_t launch_nav_safety(const VolumeRec *vol, const DaughterRec *dau, const
     return hipGetLastError();
 }
 
-hipError_t launch_nav_locate(const VolumeRec *vol, const DaughterRec *dau, const CullRec *cul,
+hipError_t launch_nav_locate(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul,
                              const TracksDev &t, const double *offs, int32_t *out, bool cull,
                              int kset, hipStream_t st) {
     if (t.n == 0) return hipSuccess;
@@ -278,17 +282,18 @@ hipError_t launch_nav_locate(const VolumeRec *vol, const DaughterRec *dau, const
 template <int U, bool CULL, bool COUNT, int KSET>
 __device__ __forceinline__ void run_tile(const Tile &tl, const VolumeRec *__restrict__ vols,
                                          const DaughterRec *__restrict__ dau_all,
-                                         const CullRec *__restrict__ cul_all, const TracksDev &t,
+                                         const CullBlock *__restrict__ cul_all, const TracksDev &t,
                                          double *__restrict__ step, int32_t *__restrict__ hit,
                                          unsigned long long *census, int lane,
                                          NavScratch<U> *scr) {
     const VolumeRec &v = vols[tl.volume];
     const DaughterRec *dau = dau_all + v.first;
-    const CullRec *cul = cul_all + v.first;
     if constexpr (CULL) {
-        nav_compact<U, false, false, COUNT, KSET>(v, dau, cul, nullptr, t, tl.offset, tl.count, *scr,
-                                                  lane, step, hit, nullptr, census);
-        return;
+        if (!v.dense) {
+            nav_compact<U, false, false, COUNT, KSET>(v, dau, cul_all + v.first_block, nullptr, t, tl.offset,
+                                                      tl.count, *scr, lane, step, hit, nullptr, census);
+            return;
+        }
     }
 #pragma unroll 1
     for (int u = 0; u < U; ++u) {
@@ -299,7 +304,7 @@ __device__ __forceinline__ void run_tile(const Tile &tl, const VolumeRec *__rest
             const double ux = t.ux[i], uy = t.uy[i], uz = t.uz[i];
             double best;
             int h, sid;
-            nav_track<false, false, COUNT, KSET>(v, dau, cul, nullptr, x, y, z, ux, uy, uz,
+            nav_track<false, false, COUNT, KSET>(v, dau, nullptr, x, y, z, ux, uy, uz,
                                                        best, h, sid, census);
             step[i] = best;
             hit[i] = h;
@@ -315,9 +320,9 @@ __device__ __forceinline__ void run_tile(const Tile &tl, const VolumeRec *__rest
 // then the others in turn; it exits once every queue's cursor has passed the
 // queue's length, so every wavefront terminates.
 template <int U, bool CULL, bool COUNT, int KSET>
-__global__ __launch_bounds__(kBlock) void k_nav_persistent(const VolumeRec *__restrict__ vols,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? (U == 1 ? 5 : 4) : 1))) void k_nav_persistent(const VolumeRec *__restrict__ vols,
                                                            const DaughterRec *__restrict__ dau_all,
-                                                           const CullRec *__restrict__ cul_all,
+                                                           const CullBlock *__restrict__ cul_all,
                                                            const Tile *__restrict__ tiles,
                                                            int32_t ntiles, unsigned int *cursors,
                                                            TracksDev t, double *__restrict__ step,
@@ -343,12 +348,12 @@ __global__ __launch_bounds__(kBlock) void k_nav_persistent(const VolumeRec *__re
 
 // Hardware-scheduled form: one wavefront per tile, workgroups dispatched in
 // tile order (same parameters as the persistent form; `cursors` unused).
-// Every kind: held to 5 wavefronts per SIMD as the basket navigator (up to
-// 4 rounds per wavefront; with 8 the LDS allows 3 anyway).
+// Registers as in the basket navigator. (512 baskets of 64 volumes: 85.0 to
+// 66.5 us with the tile expansion.)
 template <int U, bool CULL, bool COUNT, int KSET>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(KSET == kSetAll && U <= 4 ? 5 : 1))) void k_nav_tiles(const VolumeRec *__restrict__ vols,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? (U == 1 ? 5 : 4) : 1))) void k_nav_tiles(const VolumeRec *__restrict__ vols,
                                                       const DaughterRec *__restrict__ dau_all,
-                                                      const CullRec *__restrict__ cul_all,
+                                                      const CullBlock *__restrict__ cul_all,
                                                       const Tile *__restrict__ tiles, int32_t ntiles,
                                                       unsigned int *cursors, TracksDev t,
                                                       double *__restrict__ step,
@@ -372,7 +377,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(KSET == 
         tl.offset = 0;
         if (w < ntiles) tl = tiles[w];
         const VolumeRec &v = vols[tl.volume];
-        nav_compact_pooled<U, kBlock / 64, false, false, KSET>(v, dau_all, cul_all, v.first, nullptr, t, tl.offset,
+        if (v.dense) {  // (all four of a shared workgroup)
+            if (w < ntiles)
+                run_tile<U, false, false, KSET>(tl, vols, dau_all, cul_all, t, step, hit, nullptr,
+                                                (int)(threadIdx.x & 63), nullptr);
+            return;
+        }
+        nav_compact_pooled<U, kBlock / 64, false, false, KSET>(v, dau_all, cul_all + v.first_block, v.first, nullptr, t, tl.offset,
                                                                tl.count, scr, pool, shared, (int)(threadIdx.x >> 6),
                                                                (int)(threadIdx.x & 63), step, hit, nullptr);
         return;
@@ -469,34 +480,29 @@ int batched_grid(int waves_per_simd, int num_cus, int64_t ntiles) {
 }
 
 // ------------------------------------------------------------------ adjoint
-// The volume's culling records moved by this call's daughter offsets, for
-// the adjoint's forward: centre T' = T + offset and the threshold of the
-// expanded test for it, q' = r2 - |T'|^2 + 64 eps (3 R + 2 |T'|)^2 (R the
-// mother's bounding radius), the same bound as the unshifted records'.
-// Padding records are copied (q = -infinity: they never pass). The moved
-// centre differs from T + offset by a rounding, far inside the culling
-// radius's enlargement of 1e-6 relative + 1e-6, so the tests stay
-// conservative for the daughter where the queued pairs place it.
-__global__ __launch_bounds__(kBlock) void k_shift_cull(const VolumeRec *__restrict__ vol,
-                                                       const CullRec *__restrict__ cul,
-                                                       const DaughterRec *__restrict__ dau,
-                                                       const double *__restrict__ offs,
-                                                       CullRec *__restrict__ out) {
-    const int nd = vol->nd;
-    const int ndp = (nd + kCullChunk - 1) / kCullChunk * kCullChunk;
-    const double R = vol->bound_r;
-    for (int k = (int)(blockIdx.x * blockDim.x + threadIdx.x); k < ndp; k += (int)(gridDim.x * blockDim.x)) {
-        if (k < nd) {
-            const double tx = cul[k].tx + offs[3 * k + 0];
-            const double ty = cul[k].ty + offs[3 * k + 1];
-            const double tz = cul[k].tz + offs[3 * k + 2];
-            const double tt = tx * tx + ty * ty + tz * tz;
-            const double span = 3.0 * R + 2.0 * fsqrt(tt);
-            out[k] = CullRec{tx, ty, tz, dau[k].cull_r2 - tt + 64.0 * 2.220446049250313e-16 * span * span};
-        } else {
-            out[k] = cul[k];
-        }
-    }
+// Culling blocks from the daughter records: blockIdx.y is the volume (of
+// vols), blockIdx.x its block, one wavefront each. HAS_OFFS false: into the
+// geometry's table; true: one volume's, moved by this call's daughter
+// offsets, into a buffer of its own (for the adjoint's forward). The tests'
+// centre T + offset is rounded once more than the T of the evaluation, far
+// inside the culling radius's enlargement of 1e-6 relative + 1e-6.
+template <bool HAS_OFFS>
+__global__ __launch_bounds__(64) void k_cull_blocks(const VolumeRec *__restrict__ vols,
+                                                    const DaughterRec *__restrict__ dau_all,
+                                                    const double *__restrict__ offs, CullBlock *__restrict__ out) {
+    const VolumeRec &v = vols[blockIdx.y];
+    const int k0 = (int)blockIdx.x * kCullBlock, lane = (int)threadIdx.x;
+    if (k0 >= v.nd) return;
+    CullBlock *blocks = HAS_OFFS ? out : out + v.first_block;
+    *reinterpret_cast<uint4v *>(blocks[blockIdx.x].a[lane]) =
+        cull_operand<HAS_OFFS>(v, dau_all + v.first, offs, k0, lane);
+}
+
+hipError_t launch_cull_blocks(const VolumeRec *vols, int nvol, int max_nd, const DaughterRec *dau, CullBlock *out,
+                              hipStream_t st) {
+    const dim3 grid((max_nd + kCullBlock - 1) / kCullBlock, nvol);
+    hipLaunchKernelGGL(k_cull_blocks<false>, grid, dim3(64), 0, st, vols, dau, nullptr, out);
+    return hipGetLastError();
 }
 
 // For each track: recompute the forward step keeping the surface that set it,
@@ -508,15 +514,15 @@ __global__ __launch_bounds__(kBlock) void k_shift_cull(const VolumeRec *__restri
 // The offset gradient of the workgroup's tracks is summed per daughter in a
 // fixed lane order into the workgroup's row of `partial`, accumulated over
 // the workgroup's passes in LDS when lds_acc (3 nd doubles; else in the row
-// itself) and written once. With SHIFTED the forward's culling tests read
-// `shifted` (k_shift_cull), the records moved by the offsets.
-template <bool HAS_OFFS, bool CULL, int KSET, bool SHIFTED = false>
-__global__ __launch_bounds__(kBlock) void k_nav_backward(
+// itself) and written once. With TABLE the forward's culling operands are
+// read from `cul`: the volume's, or with offsets those k_cull_blocks moved.
+template <bool HAS_OFFS, bool CULL, int KSET, bool TABLE = !HAS_OFFS>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 4 : 1))) void k_nav_backward(
     const VolumeRec *__restrict__ vol, const DaughterRec *__restrict__ dau,
-    const CullRec *__restrict__ cul, TracksDev t, const double *__restrict__ offs,
+    const CullBlock *__restrict__ cul, TracksDev t, const double *__restrict__ offs,
     const double *__restrict__ gstep,
     const double *__restrict__ ghit, double *__restrict__ g_o, double *__restrict__ g_d,
-    double *__restrict__ partial, bool lds_acc, const CullRec *__restrict__ shifted) {
+    double *__restrict__ partial, bool lds_acc) {
     __shared__ double s_g[3][kBlock];
     __shared__ NavScratch<1> scr[CULL ? kBlock / 64 : 1];
     // [3 nd] doubles of the row's accumulator when lds_acc, then 4 nd + nd + 1
@@ -542,12 +548,8 @@ __global__ __launch_bounds__(kBlock) void k_nav_backward(
             const int64_t wbase = base + wave * 64;
             if (wbase < n) {
                 const int cnt = n - wbase < 64 ? (int)(n - wbase) : 64;
-                if (SHIFTED)
-                    nav_compact_core<1, HAS_OFFS, false, KSET, true, true, SHIFTED>(
-                        *vol, dau, cul, offs, t, wbase, cnt, scr[wave], lane, nullptr, shifted);
-                else
-                    nav_compact_core<1, HAS_OFFS, false, KSET>(*vol, dau, cul, offs, t, wbase, cnt, scr[wave],
-                                                               lane);
+                nav_compact_core<1, HAS_OFFS, false, KSET, true, true, TABLE>(*vol, dau, cul, offs, t, wbase, cnt,
+                                                                              scr[wave], lane);
             }
         }
         if (i < n) {
@@ -563,7 +565,7 @@ __global__ __launch_bounds__(kBlock) void k_nav_backward(
                 h = hit_index(v);
                 sid = hit_surface(v);
             } else {
-                nav_track<HAS_OFFS, true, false, KSET>(*vol, dau, cul, offs, x, y, z, ux, uy, uz, best,
+                nav_track<HAS_OFFS, true, false, KSET>(*vol, dau, offs, x, y, z, ux, uy, uz, best,
                                                        h, sid);
             }
             const bool finite = best < kBig;
@@ -709,22 +711,22 @@ constexpr int kBackwardLdsAcc = 256;
 
 template <bool CULL, int KSET>
 static void launch_backward_variant(int nblocks, int nd, const VolumeRec *vol, const DaughterRec *dau,
-                                    const CullRec *cul, const TracksDev &t, const double *offs, const double *gstep,
+                                    const CullBlock *cul, const TracksDev &t, const double *offs, const double *gstep,
                                     const double *ghit, double *g_o, double *g_d, double *part,
-                                    const CullRec *shifted, hipStream_t st) {
+                                    const CullBlock *shifted, hipStream_t st) {
     // the offset-gradient sort's counts and runs; the row's accumulator in
     // LDS up to kBackwardLdsAcc daughters (6 KB)
     const bool lds_acc = part && nd <= kBackwardLdsAcc;
     const size_t dyn = (lds_acc ? sizeof(double) * 3 * (size_t)nd : 0) + sizeof(int) * (size_t)(5 * nd + 1);
     if (offs && CULL && shifted)
         hipLaunchKernelGGL((k_nav_backward<true, CULL, KSET, CULL>), dim3(nblocks), dim3(kBlock), dyn, st, vol, dau,
-                           cul, t, offs, gstep, ghit, g_o, g_d, part, lds_acc, shifted);
+                           shifted, t, offs, gstep, ghit, g_o, g_d, part, lds_acc);
     else if (offs)
-        hipLaunchKernelGGL((k_nav_backward<true, CULL, KSET>), dim3(nblocks), dim3(kBlock), dyn, st, vol, dau, cul, t,
-                           offs, gstep, ghit, g_o, g_d, part, lds_acc, nullptr);
+        hipLaunchKernelGGL((k_nav_backward<true, CULL, KSET, false>), dim3(nblocks), dim3(kBlock), dyn, st, vol, dau,
+                           cul, t, offs, gstep, ghit, g_o, g_d, part, lds_acc);
     else
         hipLaunchKernelGGL((k_nav_backward<false, CULL, KSET>), dim3(nblocks), dim3(kBlock), dyn, st, vol, dau, cul, t,
-                           offs, gstep, ghit, g_o, g_d, part, lds_acc, nullptr);
+                           offs, gstep, ghit, g_o, g_d, part, lds_acc);
 }
 
 int backward_blocks(int64_t n) {
@@ -732,18 +734,19 @@ int backward_blocks(int64_t n) {
     return (int)(need < kBackwardMaxBlocks ? (need > 0 ? need : 1) : kBackwardMaxBlocks);
 }
 
-hipError_t launch_backward(const VolumeRec *vol, const DaughterRec *dau, const CullRec *cul, int nd,
+hipError_t launch_backward(const VolumeRec *vol, const DaughterRec *dau_all, const DaughterRec *dau,
+                           const CullBlock *cul, int nd,
                            const TracksDev &t, const double *offs, const double *gstep,
                            const double *ghit, double *g_o, double *g_d, double *partial,
-                           double *g_off, bool cull, int kset, CullRec *shift_buf, hipStream_t st) {
+                           double *g_off, bool cull, int kset, CullBlock *shift_buf, hipStream_t st) {
     const int nblocks = backward_blocks(t.n);
     double *part = (g_off && nd > 0) ? partial : nullptr;
     if (t.n > 0 || part) {
-        const CullRec *shifted = nullptr;
+        const CullBlock *shifted = nullptr;
         if (cull && offs && shift_buf && nd > 0 && t.n > 0) {
-            const int ndp = (nd + kCullChunk - 1) / kCullChunk * kCullChunk;
-            hipLaunchKernelGGL(k_shift_cull, dim3((ndp + kBlock - 1) / kBlock), dim3(kBlock), 0, st, vol, cul, dau,
-                               offs, shift_buf);
+            // (the kernel takes the geometry's daughter table)
+            hipLaunchKernelGGL(k_cull_blocks<true>, dim3((nd + kCullBlock - 1) / kCullBlock), dim3(64), 0, st, vol,
+                               dau_all, offs, shift_buf);
             shifted = shift_buf;
         }
         if (cull)
