@@ -111,7 +111,9 @@ int make_pcon(const double *p, PconRec &pc, double *bound_r, const char *what) {
     pc.rout2_0 = hi2(pc.rout[0]);
     pc.rin2_l = lo2(pc.rin[nz - 1]);
     pc.rout2_l = hi2(pc.rout[nz - 1]);
-    if (bound_r) *bound_r = std::sqrt(rm * rm + zm * zm);
+    const double br = std::sqrt(rm * rm + zm * zm);
+    pc.far2 = br * (1.0 + 1e-6) * (br * (1.0 + 1e-6));
+    if (bound_r) *bound_r = br;
     return GEO_OK;
 }
 

@@ -68,7 +68,7 @@ struct alignas(16) PconRec {
     double ao[kPconMax - 1], bo[kPconMax - 1], ai[kPconMax - 1], bi[kPconMax - 1];
     double inv_eo[kPconMax - 1], inv_ei[kPconMax - 1];   // 1 / |profile edge|^2, outer and inner
     double eps;  // slack of the range tests at hit points: 1e-12 x (max |z| + max rmax)
-    double pad2;
+    double far2; // square of a radius about the origin that holds the polycone, 1e-6 enlarged
 };
 static_assert(sizeof(PconRec) == 592, "PconRec layout");
 
@@ -698,11 +698,12 @@ __device__ __forceinline__ bool pcon_in_profile(const PconRec &P, double u, doub
     return in;
 }
 
-template <bool SEG>
+// (SIDE: the point is known to be outside, or inside)
+template <bool SEG, bool SIDE = false>
 __device__ __forceinline__ double pcon_dist_out(const ShapeRec &S, const PconRec &P, double x,
                                                 double y, double z, double ux, double uy,
                                                 double uz, int &sid) {
-    const bool inside = pcon_contains(P, x, y, z) && (!SEG || wedge_in(S, x, y));
+    const bool inside = !SIDE && pcon_contains(P, x, y, z) && (!SEG || wedge_in(S, x, y));
     const int ns = P.nz - 1;
     double best = kBig;
     sid = -1;
@@ -756,11 +757,11 @@ __device__ __forceinline__ double pcon_dist_out(const ShapeRec &S, const PconRec
     return inside ? 0.0 : best;
 }
 
-template <bool SEG>
+template <bool SEG, bool SIDE = false>
 __device__ __forceinline__ double pcon_dist_in(const ShapeRec &S, const PconRec &P, double x,
                                                double y, double z, double ux, double uy, double uz,
                                                int &sid) {
-    const bool inside = pcon_contains(P, x, y, z) && (!SEG || wedge_in(S, x, y));
+    const bool inside = SIDE || (pcon_contains(P, x, y, z) && (!SEG || wedge_in(S, x, y)));
     const int ns = P.nz - 1;
     double best = kBig;
     sid = -1;
