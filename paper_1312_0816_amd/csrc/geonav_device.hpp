@@ -1594,9 +1594,13 @@ __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const Daught
         CullTracks c;
         cull_tracks(v, p.x, p.y, p.z, p.ux, p.uy, p.uz, on, c);
         for (int k0 = 0; k0 < nd; k0 += kCullBlock) {
+            if (k0 > 0) {
+                // waited for here: a wait where the paths join would be for
+                // the next round's tracks as well, in the first block too
+                a = operand(k0);
+                asm volatile("" : "+v"(a));
+            }
             unsigned int m = cull_mask(a, c, nd - k0);
-            const bool blocks = k0 + kCullBlock < nd;
-            if (blocks) a = operand(k0 + kCullBlock);
             if (!on) m = 0u;
             // each lane with a daughter left appends its lowest, while there is room
             for (;;) {
@@ -1617,13 +1621,17 @@ __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const Daught
                 if (qn >= kQueueCap) {
                     nav_batch<U, HAS_OFFS, COUNT, KSET, SURF>(dau, offs, S, kQueueCap, lane, census);
                     qn = 0;
-                    // the track and its operands are read and formed again
-                    // rather than kept live through the evaluations (U == 1,
-                    // compiled for 5 wavefronts per SIMD: on every path, which
-                    // takes the kernel of every kind from 112 to 96 VGPRs)
-                    p = load(j);
-                    if (U == 1 || blocks) cull_tracks(v, p.x, p.y, p.z, p.ux, p.uy, p.uz, on, c);
-                    if (U == 1 && blocks) a = operand(k0 + kCullBlock);
+                    // the tracks and the operands are read and formed again
+                    // rather than kept live through the evaluations (from an
+                    // address that is not formed ahead of them either): 104
+                    // to 91 VGPRs
+                    int again = j;
+                    asm volatile("" : "+v"(again));
+                    p = load(again);
+                    if (U > 1) next = load(again + 64);
+                    if (TABLE) first = operand(0);
+                    if (U == 1 || k0 + kCullBlock < nd)
+                        cull_tracks(v, p.x, p.y, p.z, p.ux, p.uy, p.uz, on, c);
                 }
             }
         }

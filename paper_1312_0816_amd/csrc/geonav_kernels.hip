@@ -216,15 +216,17 @@ hipError_t launch_shape_query(const ShapeRec &s, const PconRec &pc, int query, c
 // ---------------------------------------------------------- basket navigator
 // With culling, one wavefront takes U rounds of 64 tracks (compacted
 // evaluation; more tracks per wavefront fill more lanes of each batch of
-// queued pairs). One round: 86-96 VGPRs, 5 wavefronts per SIMD, so that a
-// basket of 300k tracks runs in one go (the mixed detector's 300007: 19.2 to
-// 15.8 us, 20.5 at 4 wavefronts). More rounds: the next round's tracks are
-// held in registers, 118-128 VGPRs, 4 wavefronts per SIMD; held to 96 the
-// kernel spills 25 (124 us against 52 on the toy detector's 2^22 tracks, 75 us
-// with the FP64 culling tests before the matrix cores; 4.8 TB/s of the 60 B
-// per track, 1 GiB copies reach 5.0).
+// queued pairs). What bounds it is the memory's latency as much as VALU issue
+// (0.85 of the lanes' time; 4.8 TB/s of the 60 B per track on the toy
+// detector, 1 GiB copies reach 5.0), so wavefronts in flight count: all are
+// compiled for 5 per SIMD (75-96 VGPRs), which takes that nothing is kept
+// live through a full queue's batch, nor an address formed ahead of it (118
+// VGPRs, 4 per SIMD, before). 2^22 tracks, three sets of buffers in turn (us),
+// FP64 culling tests / these tests at 4 / at 5: toy detector 84.6 / 62 / 59.4,
+// every kind 112 / 87 / 83, 8 daughters 60.3 / 58.8 / 56.4, 64 131 / 89 / 85;
+// 300007 tracks of every kind, one round, 19.5 / 20.5 / 15.8.
 template <bool HAS_OFFS, bool HITPT, bool CULL, int KSET, int U = 1>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? (U == 1 ? 5 : 4) : 1))) void k_nav_basket(const VolumeRec *__restrict__ vol,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 5 : 1))) void k_nav_basket(const VolumeRec *__restrict__ vol,
                                                        const DaughterRec *__restrict__ dau,
                                                        const CullBlock *__restrict__ cul,
                                                        TracksDev t, const double *__restrict__ offs,
@@ -439,7 +441,7 @@ __device__ __forceinline__ void run_tile(const Tile &tl, const VolumeRec *__rest
 // then the others in turn; it exits once every queue's cursor has passed the
 // queue's length, so every wavefront terminates.
 template <int U, bool CULL, bool COUNT, int KSET>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? (U == 1 ? 5 : 4) : 1))) void k_nav_persistent(const VolumeRec *__restrict__ vols,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 5 : 1))) void k_nav_persistent(const VolumeRec *__restrict__ vols,
                                                            const DaughterRec *__restrict__ dau_all,
                                                            const CullBlock *__restrict__ cul_all,
                                                            const Tile *__restrict__ tiles,
@@ -467,10 +469,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? (
 
 // Hardware-scheduled form: one wavefront per tile, workgroups dispatched in
 // tile order (same parameters as the persistent form; `cursors` unused).
-// Registers as in the basket navigator. (512 baskets of 64 volumes: 85.0 to
-// 66.5 us with the tile expansion.)
+// Registers as in the basket navigator. (512 baskets of 64 volumes, three
+// pools in turn, with the tile expansion: 96 us with FP64 culling tests, 79.8
+// at 4 wavefronts per SIMD, 76.9 at 5.)
 template <int U, bool CULL, bool COUNT, int KSET>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? (U == 1 ? 5 : 4) : 1))) void k_nav_tiles(const VolumeRec *__restrict__ vols,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 5 : 1))) void k_nav_tiles(const VolumeRec *__restrict__ vols,
                                                       const DaughterRec *__restrict__ dau_all,
                                                       const CullBlock *__restrict__ cul_all,
                                                       const Tile *__restrict__ tiles, int32_t ntiles,
