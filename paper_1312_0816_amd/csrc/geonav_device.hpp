@@ -1185,6 +1185,12 @@ struct NavScratch {
     // the queued pairs: (daughter << 10) | round * 64 + lane, and the track
     unsigned int pair[kQueueCap];
     double x[kQueueCap], y[kQueueCap], z[kQueueCap], ux[kQueueCap], uy[kQueueCap], uz[kQueueCap];
+    // the volume's second culling block (tiles of a few rounds; volumes of
+    // box, tube and cone, whose kernels have the registers): read from global
+    // memory in every round, it would be waited for behind the next round's
+    // tracks (512 baskets of 64 volumes 76.7 to 75.0 us)
+    static constexpr bool kSecond = U == 2 || U == 4;
+    unsigned int second[kSecond ? 64 : 1][4];
     static_assert(U * 64 <= 1024, "track index within the tile: 10 bits");
 };
 
@@ -1568,6 +1574,8 @@ __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const Daught
     Track next = load(lane);
     uint4v first = {};
     if (nd > 0) first = operand(0);
+    constexpr bool SECOND = NavScratch<U>::kSecond && KSET == kSetBasic;
+    if (SECOND && nd > kCullBlock) *reinterpret_cast<uint4v *>(S.second[lane]) = operand(kCullBlock);
 #pragma unroll 1
     for (int u = 0; u < U; ++u) {
         if (u * 64 >= count) break;
@@ -1594,7 +1602,9 @@ __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const Daught
         CullTracks c;
         cull_tracks(v, p.x, p.y, p.z, p.ux, p.uy, p.uz, on, c);
         for (int k0 = 0; k0 < nd; k0 += kCullBlock) {
-            if (k0 > 0) {
+            if (SECOND && k0 == kCullBlock) {
+                a = *reinterpret_cast<const uint4v *>(S.second[lane]);
+            } else if (k0 > 0) {
                 // waited for here: a wait where the paths join would be for
                 // the next round's tracks as well, in the first block too
                 a = operand(k0);
