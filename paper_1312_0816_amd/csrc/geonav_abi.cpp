@@ -740,7 +740,7 @@ int geo_navigate_backward_noalloc(const geo_geometry *g, int32_t volume, geo_tra
     if ((rc = check_device(g))) return rc;
     double *part = nullptr;
     if (g_off && nd > 0) {
-        const size_t need = (size_t)backward_blocks(t.n) * 3 * (size_t)nd;
+        const size_t need = (size_t)backward_rows(t.n) * 3 * (size_t)nd;
         if (need > kScratchDoubles)
             return fail(GEO_ERR_INVALID_ARG,
                         "geo_navigate_backward_noalloc: %d daughters over %lld tracks need %zu partial sums, "

@@ -1537,7 +1537,7 @@ __device__ __forceinline__ unsigned int cull_mask(const uint4v &a, const CullTra
     return left <= 16 ? cull_mask_of<8>(a, c) : cull_mask_of<16>(a, c);
 }
 
-// Navigates the tracks base + u * 64 + lane (u < U, index below `count` > 0
+// Navigates the tracks base + u * STRIDE + lane (u < U, index below `count` > 0
 // past base) of one volume, leaving each track's step (as a key) and hit
 // index in S; with SURF, the hit slot also carries the surface that set the
 // step (for the adjoint). Each round's tracks are requested a round ahead
@@ -1554,7 +1554,12 @@ __device__ __forceinline__ unsigned int cull_mask(const uint4v &a, const CullTra
 struct Track {
     double x, y, z, ux, uy, uz;
 };
-template <int U, bool HAS_OFFS, bool COUNT, int KSET, bool SURF = true, bool FINAL = true, bool TABLE = !HAS_OFFS>
+//
+// STRIDE is the distance of the rounds' first tracks (64: a tile of
+// consecutive tracks); `count` then counts the tracks from base to the end
+// of the last round.
+template <int U, bool HAS_OFFS, bool COUNT, int KSET, bool SURF = true, bool FINAL = true, bool TABLE = !HAS_OFFS,
+          int STRIDE = 64>
 __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const DaughterRec *__restrict__ dau,
                                                 const CullBlock *__restrict__ cul,
                                                 const double *__restrict__ offs, const TracksDev &t,
@@ -1567,8 +1572,10 @@ __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const Daught
         if (TABLE) return *reinterpret_cast<const uint4v *>(cul[k0 / kCullBlock].a[lane]);
         return cull_operand<HAS_OFFS>(v, dau, offs, k0, lane);
     };
+    auto place = [](int j) { return STRIDE == 64 ? j : (j >> 6) * STRIDE + (j & 63); };
     auto load = [&](int j) -> Track {  // (a lane past the end: the last track)
-        const unsigned int ju = (unsigned int)(j < count ? j : count - 1);
+        const int at = place(j);
+        const unsigned int ju = (unsigned int)(at < count ? at : count - 1);
         return Track{at32(tt.x, ju), at32(tt.y, ju), at32(tt.z, ju), at32(tt.ux, ju), at32(tt.uy, ju), at32(tt.uz, ju)};
     };
     Track next = load(lane);
@@ -1578,12 +1585,12 @@ __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const Daught
     if (SECOND && nd > kCullBlock) *reinterpret_cast<uint4v *>(S.second[lane]) = operand(kCullBlock);
 #pragma unroll 1
     for (int u = 0; u < U; ++u) {
-        if (u * 64 >= count) break;
+        if (u * STRIDE >= count) break;
         const int j = u * 64 + lane;
-        const bool act = j < count;
+        const bool act = place(j) < count;
         uint4v a = first;
         Track p = next;
-        if (U > 1 && (u + 1) * 64 < count && u + 1 < U) next = load(j + 64);
+        if (U > 1 && (u + 1) * STRIDE < count && u + 1 < U) next = load(j + 64);
         int sid;
         const double ms = mother_step<SURF, KSET>(v, p.x, p.y, p.z, p.ux, p.uy, p.uz, sid);
         lds_store(&S.key[j], step_key(ms, true));

@@ -75,9 +75,13 @@ const void *build_tiles_kernel();
 // one wavefront per tile (waves_per_simd == 0).
 int batched_grid(int waves_per_simd, int num_cus, int64_t ntiles);
 
-// Workgroups of an adjoint launch over n tracks (each writes one row of
-// 3 * nd partial sums of the offset gradient).
-int backward_blocks(int64_t n);
+// Rows of 3 * nd partial sums of the offset gradient that the limit of the
+// allocation-free adjoint counts, one per 256 tracks (a launch over n tracks
+// writes that many or fewer).
+inline int backward_rows(int64_t n) {
+    const int64_t need = (n + kBlock - 1) / kBlock;
+    return (int)(need < kBackwardMaxBlocks ? (need > 0 ? need : 1) : kBackwardMaxBlocks);
+}
 
 // The static partial-sum buffer of the allocation-free adjoint: doubles it
 // holds, and its device address on the current device (looked up once per

@@ -638,7 +638,11 @@ hipError_t launch_cull_blocks(const VolumeRec *vols, int nvol, int max_nd, const
 // the workgroup's passes in LDS when lds_acc (3 nd doubles; else in the row
 // itself) and written once. With TABLE the forward's culling operands are
 // read from `cul`: the volume's, or with offsets those k_cull_blocks moved.
-template <bool HAS_OFFS, bool CULL, int KSET, bool TABLE = !HAS_OFFS>
+//
+// A workgroup takes U passes of 256 tracks at a time: each wavefront navigates
+// its 64 tracks of all of them in one go, so that a batch of queued pairs
+// holds U times as many, then the passes are differentiated one by one.
+template <bool HAS_OFFS, bool CULL, int KSET, bool TABLE, int U>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 4 : 1))) void k_nav_backward(
     const VolumeRec *__restrict__ vol, const DaughterRec *__restrict__ dau,
     const CullBlock *__restrict__ cul, TracksDev t, const double *__restrict__ offs,
@@ -646,7 +650,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 4
     const double *__restrict__ ghit, double *__restrict__ g_o, double *__restrict__ g_d,
     double *__restrict__ partial, bool lds_acc) {
     __shared__ double s_g[3][kBlock];
-    __shared__ NavScratch<1> scr[CULL ? kBlock / 64 : 1];
+    __shared__ NavScratch<U> scr[CULL ? kBlock / 64 : 1];
     // [3 nd] doubles of the row's accumulator when lds_acc, then 4 nd + nd + 1
     // ints (see below)
     extern __shared__ double s_dyn[];
@@ -660,18 +664,22 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 4
     if (prow)
         for (int j = tid; j < nj; j += kBlock) acc_row[j] = 0.0;
     const int64_t n = t.n;
-    for (int64_t base = (int64_t)blockIdx.x * kBlock; base < n; base += (int64_t)gridDim.x * kBlock) {
+    for (int64_t pass = (int64_t)blockIdx.x * U; pass * kBlock < n;
+         pass += pass % U + 1 < U ? 1 : ((int64_t)gridDim.x - 1) * U + 1) {
+        const int u = (int)(pass % U);
+        const int64_t base = pass * kBlock;
         const int64_t i = base + tid;
         int h = -2;
         double gdx = 0.0, gdy = 0.0, gdz = 0.0;
         if constexpr (CULL) {
-            // the forward step and hit by the compacted navigator (per
-            // wavefront of 64 tracks)
+            // the forward steps and hits of the next U passes by the
+            // compacted navigator
             const int64_t wbase = base + wave * 64;
-            if (wbase < n) {
-                const int cnt = n - wbase < 64 ? (int)(n - wbase) : 64;
-                nav_compact_core<1, HAS_OFFS, false, KSET, true, true, TABLE>(*vol, dau, cul, offs, t, wbase, cnt,
-                                                                              scr[wave], lane);
+            if (u == 0 && wbase < n) {
+                constexpr int most = (U - 1) * kBlock + 64;
+                const int cnt = n - wbase < most ? (int)(n - wbase) : most;
+                nav_compact_core<U, HAS_OFFS, false, KSET, true, true, TABLE, kBlock>(*vol, dau, cul, offs, t, wbase,
+                                                                                      cnt, scr[wave], lane);
             }
         }
         if (i < n) {
@@ -682,8 +690,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 4
             if constexpr (CULL) {
                 // the step, the winner and the surface that set its step, as
                 // the compacted navigator left them
-                best = key_step(lds_load(&scr[wave].key[lane]));
-                const int v = lds_load(&scr[wave].hit[lane]);
+                best = key_step(lds_load(&scr[wave].key[u * 64 + lane]));
+                const int v = lds_load(&scr[wave].hit[u * 64 + lane]);
                 h = hit_index(v);
                 sid = hit_surface(v);
             } else {
@@ -831,7 +839,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_partials(const double *__rest
 
 constexpr int kBackwardLdsAcc = 256;
 
-template <bool CULL, int KSET>
+template <bool CULL, int KSET, int U>
 static void launch_backward_variant(int nblocks, int nd, const VolumeRec *vol, const DaughterRec *dau,
                                     const CullBlock *cul, const TracksDev &t, const double *offs, const double *gstep,
                                     const double *ghit, double *g_o, double *g_d, double *part,
@@ -841,18 +849,30 @@ static void launch_backward_variant(int nblocks, int nd, const VolumeRec *vol, c
     const bool lds_acc = part && nd <= kBackwardLdsAcc;
     const size_t dyn = (lds_acc ? sizeof(double) * 3 * (size_t)nd : 0) + sizeof(int) * (size_t)(5 * nd + 1);
     if (offs && CULL && shifted)
-        hipLaunchKernelGGL((k_nav_backward<true, CULL, KSET, CULL>), dim3(nblocks), dim3(kBlock), dyn, st, vol, dau,
-                           shifted, t, offs, gstep, ghit, g_o, g_d, part, lds_acc);
+        hipLaunchKernelGGL((k_nav_backward<true, CULL, KSET, CULL, U>), dim3(nblocks), dim3(kBlock), dyn, st, vol,
+                           dau, shifted, t, offs, gstep, ghit, g_o, g_d, part, lds_acc);
     else if (offs)
-        hipLaunchKernelGGL((k_nav_backward<true, CULL, KSET, false>), dim3(nblocks), dim3(kBlock), dyn, st, vol, dau,
-                           cul, t, offs, gstep, ghit, g_o, g_d, part, lds_acc);
+        hipLaunchKernelGGL((k_nav_backward<true, CULL, KSET, false, U>), dim3(nblocks), dim3(kBlock), dyn, st, vol,
+                           dau, cul, t, offs, gstep, ghit, g_o, g_d, part, lds_acc);
     else
-        hipLaunchKernelGGL((k_nav_backward<false, CULL, KSET>), dim3(nblocks), dim3(kBlock), dyn, st, vol, dau, cul, t,
-                           offs, gstep, ghit, g_o, g_d, part, lds_acc);
+        hipLaunchKernelGGL((k_nav_backward<false, CULL, KSET, true, U>), dim3(nblocks), dim3(kBlock), dyn, st, vol,
+                           dau, cul, t, offs, gstep, ghit, g_o, g_d, part, lds_acc);
 }
 
-int backward_blocks(int64_t n) {
-    const int64_t need = (n + kBlock - 1) / kBlock;
+// Passes that a workgroup takes at a time: kBackwardRounds from the sizes on
+// at which the fuller batches gain more than the fewer workgroups lose, for
+// volumes of box, tube and cone, and sooner where a batch runs more kinds'
+// code. (us, one pass / four: toy detector 2^20 tracks 66.2 / 53.1, 800k 44.3 /
+// 45.2, 450k 32 / 34; every kind 2^20 118.8 / 72.4, 450k 58 / 48.5, 300k 47.8 /
+// 48.)
+constexpr int kBackwardRounds = 4;
+static bool backward_wide(int64_t n, int kset) {
+    return n >= (kset == kSetBasic ? (int64_t)1 << 20 : (int64_t)7 << 16);
+}
+
+static int backward_blocks(int64_t n, int kset) {
+    const int64_t per = backward_wide(n, kset) ? (int64_t)kBlock * kBackwardRounds : kBlock;
+    const int64_t need = (n + per - 1) / per;
     return (int)(need < kBackwardMaxBlocks ? (need > 0 ? need : 1) : kBackwardMaxBlocks);
 }
 
@@ -861,7 +881,7 @@ hipError_t launch_backward(const VolumeRec *vol, const DaughterRec *dau_all, con
                            const TracksDev &t, const double *offs, const double *gstep,
                            const double *ghit, double *g_o, double *g_d, double *partial,
                            double *g_off, bool cull, int kset, CullBlock *shift_buf, hipStream_t st) {
-    const int nblocks = backward_blocks(t.n);
+    const int nblocks = backward_blocks(t.n, kset);
     double *part = (g_off && nd > 0) ? partial : nullptr;
     if (t.n > 0 || part) {
         const CullBlock *shifted = nullptr;
@@ -871,12 +891,15 @@ hipError_t launch_backward(const VolumeRec *vol, const DaughterRec *dau_all, con
                                dau_all, offs, shift_buf);
             shifted = shift_buf;
         }
-        if (cull)
-            GN_KSET(kset, (launch_backward_variant<true, KS>(nblocks, nd, vol, dau, cul, t, offs, gstep, ghit,
-                                                             g_o, g_d, part, shifted, st)));
-        else
-            GN_KSET(kset, (launch_backward_variant<false, KS>(nblocks, nd, vol, dau, cul, t, offs, gstep, ghit,
-                                                              g_o, g_d, part, nullptr, st)));
+        const bool wide = backward_wide(t.n, kset);
+#define GN_BACKWARD(CULL, U) \
+    GN_KSET(kset, (launch_backward_variant<CULL, KS, U>(nblocks, nd, vol, dau, cul, t, offs, gstep, ghit, g_o, g_d, \
+                                                        part, CULL ? shifted : nullptr, st)))
+        if (cull && wide) GN_BACKWARD(true, kBackwardRounds);
+        else if (cull) GN_BACKWARD(true, 1);
+        else if (wide) GN_BACKWARD(false, kBackwardRounds);
+        else GN_BACKWARD(false, 1);
+#undef GN_BACKWARD
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

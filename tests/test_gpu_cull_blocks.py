@@ -312,3 +312,46 @@ def test_safety_near_daughters(gv, kinds, nd):
     g.close()
     for a, b in zip(out[True], out[False]):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kinds", [(W.BOX, W.TUBE, W.CONE), (W.BOX, W.TUBE, W.CONE, W.TUBS, W.CONS, W.PCON)])
+@pytest.mark.parametrize("n", [(7 << 16) - 1, 7 << 16, (1 << 20) - 1, 1 << 20, (1 << 20) + 1, (1 << 20) + 255,
+                               (1 << 20) + 1025, (1 << 21) + (1 << 20) + 300])
+def test_adjoint_passes(gv, kinds, n):
+    """The adjoint around the sizes from which a workgroup takes four passes
+    at a time (and over its largest grid), against the same tracks in smaller
+    baskets: tracks' gradients bit for bit, the offsets' to the rounding of
+    differently grouped sums; culling on and off the same bits."""
+    import torch
+    rng = np.random.default_rng(n)
+    vol = _boxes(rng, 33, kinds=kinds)
+    m = 200003
+    tr = torch.from_numpy(W.tracks_uniform_in_mother(rng, vol, m)).cuda().repeat(1, -(-n // m))[:, :n]
+    o, d = tr[:3].contiguous(), tr[3:].contiguous()
+    gs = torch.rand(n, dtype=o.dtype, device="cuda") - 0.5
+    gh = torch.rand((3, n), dtype=o.dtype, device="cuda") - 0.5
+    offs = torch.from_numpy(rng.uniform(-0.5, 0.5, (33, 3))).cuda()
+    g = gv.Geometry([vol])
+    out = {}
+    for cull in (True, False):
+        g.culling = cull
+        out[cull] = [_bits(x) for x in gv.geo_navigate_backward(g, 0, o, d, offs, gs, gh)]
+    for a, b in zip(out[True], out[False]):
+        assert np.array_equal(a, b)
+    g.culling = True
+    parts = []
+    for i in range(0, n, m):
+        c = slice(i, min(i + m, n))
+        parts.append(gv.geo_navigate_backward(g, 0, o[:, c].contiguous(), d[:, c].contiguous(), offs,
+                                              gs[c].contiguous(), gh[:, c].contiguous()))
+    for k in (0, 1):
+        assert np.array_equal(out[True][k], _bits(torch.cat([p[k] for p in parts], dim=1)))
+    off = sum(p[2] for p in parts).cpu().numpy()
+    got = out[True][2].view(np.float64)
+    # each entry is a sum of at most n terms: n eps of the terms' magnitudes
+    # bounds the difference of two groupings; the terms are -c ds/dp, the
+    # difference of g_o and ghit
+    terms = (out[True][0].view(np.float64) - gh.cpu().numpy())
+    assert np.abs(got - off).max() <= n * 2.3e-16 * np.abs(terms).sum(1).max()
+    g.close()
