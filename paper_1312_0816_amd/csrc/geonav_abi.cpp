@@ -558,6 +558,8 @@ int geo_geometry_create(const geo_volume_desc *v, int32_t nvol, geo_geometry **o
         r.safe_d = (float)(safe_d + wide);
         r.safe_r2 = (float)(safe_r2 + wide);
         r.safe_q = (float)(safe_q < 0 ? -1.0 : safe_q * (1 + 1e-6) + 1e-6);
+        r.near_r = (float)(back * (1 + 1e-6) + 1e-6);
+        r.near_r2 = (float)(back * back + wide);
         // A line through a convex mother meets a sphere inside it with the
         // ratio of their surfaces as probability. Where that is a third of
         // the daughters or more, walking all of them in lockstep costs less

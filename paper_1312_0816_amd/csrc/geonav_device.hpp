@@ -115,7 +115,9 @@ struct alignas(16) VolumeRec {
     // |w| > r is at most sqrt(|w|^2 + c), the largest r^2 + c; of the others,
     // at most |w| + q, the largest r^2 and q (q < 0: none)
     float safe_d, safe_r2, safe_q;
-    int32_t pad[2];
+    // the largest radius of both, and its square (inside a sphere: the Safety
+    // of its daughter is at most |w| + r)
+    float near_r, near_r2;
 };
 static_assert(sizeof(VolumeRec) == 304, "VolumeRec layout");
 
@@ -277,9 +279,10 @@ __device__ __forceinline__ double box_dist_out(const double *c, double x, double
 // outside).
 __device__ __forceinline__ double box_exit(const double *c, double x, double y, double z, double ux,
                                            double uy, double uz) {
-    const double tx = fdiv(c[0] - (ux > 0.0 ? x : -x), fabs(ux));
-    const double ty = fdiv(c[1] - (uy > 0.0 ? y : -y), fabs(uy));
-    const double tz = fdiv(c[2] - (uz > 0.0 ? z : -z), fabs(uz));
+    // (numerator and denominator with the direction's sign: the same quotient)
+    const double tx = fdiv(copysign(c[0], ux) - x, ux);
+    const double ty = fdiv(copysign(c[1], uy) - y, uy);
+    const double tz = fdiv(copysign(c[2], uz) - z, uz);
     const double best = fmin(kBig, fmin(tx, fmin(ty, tz)));
     return box_contains(c, x, y, z) ? best : 0.0;
 }
@@ -1203,15 +1206,17 @@ struct PointQueue {
     unsigned int queue[512];
 };
 
-// A NaN daughter step never wins and a NaN mother step is never beaten, as
-// in the sequential loop.
-__device__ __forceinline__ unsigned long long step_key(double s, bool mother = false) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(s == 0.0 ? 0.0 : s);
-    const unsigned long long k = (b >> 63) ? ~b : (b | 0x8000000000000000ull);
-    return s == s ? k : (mother ? 0ull : ~0ull);
+// The key of a step: steps are >= 0 (or -0, taken as +0), so their bits less
+// the sign order them; one more, so that 0 is left for a mother step that is
+// not a number, which is never beaten. A daughter's, larger than every
+// number's, never wins. (As in the sequential loop. 6 VALU instructions for
+// the mother's and 3 for a daughter's, 16 and 13 for a map of all doubles.)
+__device__ __forceinline__ unsigned long long step_key(double s) {
+    return ((unsigned long long)__double_as_longlong(s) & 0x7fffffffffffffffull) + 1ull;
 }
+__device__ __forceinline__ unsigned long long mother_key(double s) { return s == s ? step_key(s) : 0ull; }
 __device__ __forceinline__ double key_step(unsigned long long k) {
-    return __longlong_as_double((long long)((k >> 63) ? (k & 0x7fffffffffffffffull) : ~k));
+    return __longlong_as_double((long long)(k - 1ull));
 }
 
 // Accesses to the running minima, which other lanes of the wavefront update
@@ -1367,7 +1372,6 @@ __device__ __forceinline__ void nav_batch(const DaughterRec *__restrict__ dau,
 //    reach) always passes.
 // A track that starts outside the mother has step 0 from the mother, which
 // no daughter can beat: it is left out, so every start is within 256.
-typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef _Float16 half8v __attribute__((ext_vector_type(8)));
 typedef float float16v __attribute__((ext_vector_type(16)));
 typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
@@ -1379,8 +1383,10 @@ __device__ __forceinline__ unsigned int half_pair(float a, float b) {
 }
 __device__ __forceinline__ void half_split(float a, float b, unsigned int &hi, unsigned int &lo) {
     hi = half_pair(a, b);
-    const half2v h = __builtin_bit_cast(half2v, hi);
-    lo = half_pair(a - (float)h.x, b - (float)h.y);
+    float ra, rb;  // a and b less their halves of hi, one mixed fma each
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(ra) : "v"(hi), "v"(a));
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(rb) : "v"(hi), "v"(b));
+    lo = half_pair(ra, rb);
 }
 
 // The K = 16 slots, as pairs: lanes 0..31 hold slots 0..7 of row (column)
@@ -1438,23 +1444,38 @@ __device__ __forceinline__ uint4v cull_operand(const VolumeRec &v, const Daughte
     return uint4v{upper ? lxy : hxy, upper ? lzsh : hz64, upper ? n2 : hxy, upper ? rr : hz64};
 }
 
-// The two column operands (tracks 0..31 and 32..63) of a vector, a constant
-// and a length per lane, as above: each lane forms all 16 slots of its own
-// track, and the halves of the wavefront swap.
-__device__ __forceinline__ void cull_columns(float x, float y, float z, float c, float f, unsigned int ones,
-                                             uint4v (&col)[2]) {
-    unsigned int hxy, lxy, hzc, lzc, ff, fl;
-    half_split(x, y, hxy, lxy);
-    half_split(z, c * 0.015625f, hzc, lzc);
-    half_split(f, 0.0f, ff, fl);
-    const unsigned int lo[4] = {hxy, hzc, lxy, lzc};
-    const unsigned int hi[4] = {hxy, (hzc & 0xffffu) | (ff << 16), ones, (fl & 0xffffu) | (ff << 16)};
+// The two column operands (tracks 0..31 and 32..63) from the 16 slots that
+// each lane forms of its own track: the halves of the wavefront swap.
+__device__ __forceinline__ void cull_swap(const unsigned int (&lo)[4], const unsigned int (&hi)[4], uint4v (&col)[2]) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const uint2v r = __builtin_amdgcn_permlane32_swap(lo[i], hi[i], false, false);
         col[0][i] = r.x;  // lower lanes' lo | lower lanes' hi
         col[1][i] = r.y;  // upper lanes' lo | upper lanes' hi
     }
+}
+
+// Columns of a vector and a constant (the length 0); `ones` is the pair that
+// meets n, (64, 64) or zeros. The split vector stays in v (z in the low
+// halves of its second pairs).
+struct CullVector {
+    unsigned int xy_hi, xy_lo, z_hi, z_lo;
+};
+__device__ __forceinline__ void cull_columns(float x, float y, float z, float c, unsigned int ones, CullVector &v,
+                                             uint4v (&col)[2]) {
+    half_split(x, y, v.xy_hi, v.xy_lo);
+    half_split(z, c * 0.015625f, v.z_hi, v.z_lo);
+    cull_swap({v.xy_hi, v.z_hi, v.xy_lo, v.z_lo}, {v.xy_hi, v.z_hi & 0xffffu, ones, 0u}, col);
+}
+// The same vector's columns with another constant, and a length.
+__device__ __forceinline__ void cull_columns(const CullVector &v, float c, float f, uint4v (&col)[2]) {
+    unsigned int h, l;
+    half_split(c * 0.015625f, f, h, l);
+    cull_swap({v.xy_hi, __builtin_amdgcn_perm(h, v.z_hi, 0x05040100u), v.xy_lo,
+               __builtin_amdgcn_perm(l, v.z_lo, 0x05040100u)},
+              {v.xy_hi, __builtin_amdgcn_perm(h, v.z_hi, 0x07060100u), 0x54005400u,
+               __builtin_amdgcn_perm(h, l, 0x07060302u)},
+              col);
 }
 
 // A wavefront's column operands: of |w|^2 - r^2 (p) and of w.e (e).
@@ -1490,8 +1511,9 @@ __device__ __forceinline__ void cull_tracks(const VolumeRec &v, double x, double
     const float px = fmaf(back, ex, (float)(x * s));
     const float py = fmaf(back, ey, (float)(y * s));
     const float pz = fmaf(back, ez, (float)(z * s));
-    cull_columns(px, py, pz, fmaf(pz, pz, fmaf(py, py, px * px)), 0.0f, 0x54005400u, c.p);
-    cull_columns(0.5f * ex, 0.5f * ey, 0.5f * ez, fmaf(pz, ez, fmaf(py, ey, px * ex)), 0.0f, 0u, c.e);
+    CullVector split;
+    cull_columns(px, py, pz, fmaf(pz, pz, fmaf(py, py, px * px)), 0x54005400u, split, c.p);
+    cull_columns(0.5f * ex, 0.5f * ey, 0.5f * ez, fmaf(pz, ez, fmaf(py, ey, px * ex)), 0u, split, c.e);
 }
 
 __device__ __forceinline__ float16v cull_product(const uint4v &a, const uint4v &b) {
@@ -1593,7 +1615,7 @@ __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const Daught
         if (U > 1 && (u + 1) * STRIDE < count && u + 1 < U) next = load(j + 64);
         int sid;
         const double ms = mother_step<SURF, KSET>(v, p.x, p.y, p.z, p.ux, p.uy, p.uz, sid);
-        lds_store(&S.key[j], step_key(ms, true));
+        lds_store(&S.key[j], mother_key(ms));
         lds_store(&S.hit[j], hit_pack(-1, sid));
         if (COUNT) {
             const int n = __popcll(__builtin_amdgcn_ballot_w64(act));
@@ -1856,10 +1878,6 @@ __device__ __forceinline__ void nav_compact_pooled(const VolumeRec &v, const Dau
 // v_min3 per two pairs and the products once more with s replaced, for 0.83
 // pairs per point and 4.6 appends (a CPU simulation), one batch per
 // wavefront where there were two.
-__device__ __forceinline__ unsigned long long safety_key(double s) {
-    return s == s ? step_key(s) : ~0ull;
-}
-
 // Scratch of the compacted safety and localization: the navigator's, plus
 // the wavefront's points, which the queued pairs read back from LDS instead
 // of global memory (each lane stores its own point; the batches read them
@@ -1890,7 +1908,7 @@ __device__ __forceinline__ void point_flush(const DaughterRec *__restrict__ dau,
             const double ly = fma(R[7], wz, fma(R[4], wy, R[1] * wx));
             const double lz = fma(R[8], wz, fma(R[5], wy, R[2] * wx));
             if (MODE == 0) {
-                const unsigned long long key = safety_key(any_safety<KSET>(D.shape, D.pcon, lx, ly, lz));
+                const unsigned long long key = step_key(any_safety<KSET>(D.shape, D.pcon, lx, ly, lz));
                 __hip_atomic_fetch_min(&S.key[j], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
             } else if (any_contains<KSET>(D.shape, D.pcon, lx, ly, lz)) {
                 __hip_atomic_fetch_min(&S.hit[j], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
@@ -1904,12 +1922,17 @@ __device__ __forceinline__ void point_flush(const DaughterRec *__restrict__ dau,
 // 56.4 and 31.0).
 constexpr int kNearest = 8;
 
-// The bound of the minimum from G > 0 (in the tests' units; widened by more
-// than the products' and the roots' rounding).
+// The bound of the minimum from g, the |w|^2 - r^2 - delta of a daughter (in
+// the tests' units; widened by more than the products' and the roots'
+// rounding): from the smallest, positive ones, as above; a point inside some
+// sphere (any negative one) takes |w| + r. A daughter that always passes, far
+// below -r^2, bounds nothing.
 __device__ __forceinline__ float nearest_bound(const VolumeRec &v, float g) {
-    float b = __builtin_amdgcn_sqrtf(fmaxf(g + v.safe_d, 0.0f));
-    if (v.safe_q >= 0.0f) b = fmaxf(b, __builtin_amdgcn_sqrtf(g + v.safe_r2) + v.safe_q);
-    return fmaf(b, 0x1p-16f, b);
+    const bool outside = g > 0.0f;
+    float b = __builtin_amdgcn_sqrtf(fmaxf(g + (outside ? v.safe_d : v.near_r2), 0.0f));
+    if (!outside) b += v.near_r;
+    if (v.safe_q >= 0.0f) b = fmaxf(b, __builtin_amdgcn_sqrtf(fmaxf(g + v.safe_r2, 0.0f)) + v.safe_q);
+    return g >= -v.near_r2 ? fmaf(b, 0x1p-16f, b) : __builtin_inff();
 }
 
 // Safety (MODE 0, out_s) or localization (MODE 1, out_w) of the points
@@ -1938,7 +1961,7 @@ __device__ __forceinline__ void point_compact(const VolumeRec &v, const Daughter
     bool in_m = false;
     if (MODE == 0) {
         reach = any_safety<KSET>(v.mother, v.pcon, x, y, z);
-        lds_store(&S.key[lane], safety_key(reach));
+        lds_store(&S.key[lane], step_key(reach));
     } else {
         in_m = any_contains<KSET>(v.mother, v.pcon, x, y, z);
         lds_store(&S.hit[lane], 0x7fffffff);
@@ -1948,10 +1971,11 @@ __device__ __forceinline__ void point_compact(const VolumeRec &v, const Daughter
         const double s = v.cull_s;
         const float px = (float)(x * s), py = (float)(y * s), pz = (float)(z * s);
         const float pp = fmaf(pz, pz, fmaf(py, py, px * px));
+        CullVector split;
         uint4v col[2];
+        cull_columns(px, py, pz, pp, 0x54005400u, split, col);
         float f = MODE == 0 ? (float)(reach * s) : 0.0f;
         if (MODE == 0 && nd >= kNearest) {
-            cull_columns(px, py, pz, pp, 0.0f, 0x54005400u, col);
             int g[2] = {0x7f000000, 0x7f000000};  // as integers: any negative result stays the smallest
             uint4v b = a;
             for (int k0 = 0; k0 < nd; k0 += kCullBlock) {
@@ -1965,11 +1989,11 @@ __device__ __forceinline__ void point_compact(const VolumeRec &v, const Daughter
             }
             const uint2v own = __builtin_amdgcn_permlane32_swap((unsigned int)g[0], (unsigned int)g[1], false, false);
             const int gi = min((int)own.x, (int)own.y);
-            if (gi > 0) f = fminf(f, nearest_bound(v, __int_as_float(gi)));
+            f = fminf(f, nearest_bound(v, __int_as_float(gi)));
         }
         const float lim = kCullR + v.cull_back;
         const bool near = pp <= lim * lim && f <= lim;  // else (or not a number) takes every daughter
-        cull_columns(px, py, pz, MODE == 0 ? fmaf(-f, f, pp) : pp, f, 0x54005400u, col);
+        if (MODE == 0) cull_columns(split, fmaf(-f, f, pp), f, col);
         int qn = 0;
         for (int k0 = 0; k0 < nd; k0 += kCullBlock) {
             unsigned int h[2];
