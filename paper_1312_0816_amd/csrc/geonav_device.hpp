@@ -1031,6 +1031,13 @@ __device__ __forceinline__ double class_dist_out(int cls, const ShapeRec &s, con
     GN_KIND_SWITCH_ON(cls, GN_CALL)
 #undef GN_CALL
 }
+template <int KSET>
+__device__ __forceinline__ double class_safety(int cls, const ShapeRec &s, const PconRec *pc, double x, double y,
+                                               double z) {
+#define GN_CALL(K) shape_safety<K>(s, pc, x, y, z)
+    GN_KIND_SWITCH_ON(cls, GN_CALL)
+#undef GN_CALL
+}
 #undef GN_KIND_SWITCH
 #undef GN_KIND_SWITCH_ON
 
@@ -1935,15 +1942,118 @@ __device__ __forceinline__ float nearest_bound(const VolumeRec &v, float g) {
     return g >= -v.near_r2 ? fmaf(b, 0x1p-16f, b) : __builtin_inff();
 }
 
+// The safety's last queues pooled over the workgroup's W wavefronts, for
+// volumes of more kinds than box, tube and cone, whose Safety takes 200 to 700
+// VALU instructions for a cut solid: a batch of one wavefront's queue runs
+// the code of every kind it holds in turn. As in the navigators' pooled batch,
+// the workgroup's pairs are cut into batches of one kind class, dealt to the
+// wavefronts; a result goes into its owner's minimum at once (an LDS minimum
+// of the key, whatever the order). Queues of more than kPointPool pairs are
+// run by their own wavefront. Every wavefront of the workgroup takes part.
+constexpr int kPointPool = 128;
+template <int W>
+struct PointPool {
+    int cnt[W][kClassSlots];
+    unsigned char order[W][kPointPool];  // the queue's places, sorted by class
+};
+template <int W, bool HAS_OFFS, int KSET>
+__device__ __forceinline__ void point_pool(const DaughterRec *__restrict__ dau, const double *__restrict__ offs,
+                                           PointScratch *scr, PointPool<W> &P, int wave, int qn, int lane) {
+    constexpr int NK = kind_classes<KSET>();
+    PointScratch &S = scr[wave];
+    if (qn > kPointPool) {
+        point_flush<0, HAS_OFFS, KSET>(dau, offs, S, qn, lane);
+        qn = 0;
+    }
+    {
+        const bool on0 = lane < qn, on1 = lane + 64 < qn;
+        const int c0 = on0 ? kind_class<KSET>(dau[(int)(S.queue[lane] >> 10)].shape.kind) : -1;
+        const int c1 = on1 ? kind_class<KSET>(dau[(int)(S.queue[lane + 64] >> 10)].shape.kind) : -1;
+        int off = 0;
+#pragma unroll
+        for (int c = 0; c < NK; ++c) {
+            const unsigned long long m0 = __builtin_amdgcn_ballot_w64(c0 == c);
+            const unsigned long long m1 = __builtin_amdgcn_ballot_w64(c1 == c);
+            const int n0 = __popcll(m0), n = n0 + __popcll(m1);
+            if (c0 == c) P.order[wave][off + lanes_below(m0)] = (unsigned char)lane;
+            if (c1 == c) P.order[wave][off + n0 + lanes_below(m1)] = (unsigned char)(lane + 64);
+            if (lane == c) P.cnt[wave][c] = n;
+            off += n;
+        }
+    }
+    __syncthreads();
+    int cn[W][NK], nbc[NK], nb = 0;  // (uniform values)
+#pragma unroll
+    for (int c = 0; c < NK; ++c) {
+        int n = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            cn[w][c] = __builtin_amdgcn_readfirstlane(P.cnt[w][c]);
+            n += cn[w][c];
+        }
+        nbc[c] = (n + 63) >> 6;
+        nb += nbc[c];
+    }
+    for (int b = wave; b < nb; b += W) {
+        // from the last class (the costliest code) down
+        int c = NK - 1, p = b;
+#pragma unroll
+        for (int cc = NK - 1; cc > 0; --cc)
+            if (c == cc && p >= nbc[cc]) {
+                p -= nbc[cc];
+                c = cc - 1;
+            }
+        const int l = p * 64 + lane;  // the lane's pair within the class
+        int own = 0, rank = 0, pre = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            int before = 0, n = 0;
+#pragma unroll
+            for (int cc = 0; cc < NK; ++cc) {
+                if (cc < c) before += cn[w][cc];
+                if (cc == c) n = cn[w][cc];
+            }
+            if (l >= pre && l < pre + n) {
+                own = w;
+                rank = before + (l - pre);
+            }
+            pre += n;
+        }
+        if (l < pre) {
+            PointScratch &O = scr[own];
+            const unsigned int q = O.queue[P.order[own][rank]];
+            const int j = (int)(q & 1023u);
+            const int k = (int)(q >> 10);
+            const DaughterRec &D = dau[k];
+            double wx = lds_load(&O.px[j]) - D.tr[0], wy = lds_load(&O.py[j]) - D.tr[1],
+                   wz = lds_load(&O.pz[j]) - D.tr[2];
+            if (HAS_OFFS) {
+                wx -= offs[3 * k + 0];
+                wy -= offs[3 * k + 1];
+                wz -= offs[3 * k + 2];
+            }
+            const double *R = D.rot;
+            const double lx = fma(R[6], wz, fma(R[3], wy, R[0] * wx));
+            const double ly = fma(R[7], wz, fma(R[4], wy, R[1] * wx));
+            const double lz = fma(R[8], wz, fma(R[5], wy, R[2] * wx));
+            const unsigned long long key = step_key(class_safety<KSET>(c, D.shape, D.pcon, lx, ly, lz));
+            __hip_atomic_fetch_min(&O.key[j], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    }
+    __syncthreads();
+}
+
 // Safety (MODE 0, out_s) or localization (MODE 1, out_w) of the points
-// base + lane (lane < count).
-template <int MODE, bool HAS_OFFS, int KSET>
+// base + lane (lane < count), in S = scr[wave]. With POOL every wavefront of
+// the workgroup calls it, one past the last point with count 0.
+template <int MODE, bool HAS_OFFS, int KSET, bool POOL, int W>
 __device__ __forceinline__ void point_compact(const VolumeRec &v, const DaughterRec *__restrict__ dau,
                                               const CullBlock *__restrict__ cul,
                                               const double *__restrict__ offs, const TracksDev &t,
-                                              int64_t base, int count, PointScratch &S, int lane,
-                                              double *__restrict__ out_s,
+                                              int64_t base, int count, PointScratch *scr, PointPool<W> *pool,
+                                              int wave, int lane, double *__restrict__ out_s,
                                               int32_t *__restrict__ out_w) {
+    PointScratch &S = scr[wave];
     const int nd = v.nd;
     auto operand = [&](int k0) -> uint4v {
         if (!HAS_OFFS) return *reinterpret_cast<const uint4v *>(cul[k0 / kCullBlock].a[lane]);
@@ -1952,7 +2062,7 @@ __device__ __forceinline__ void point_compact(const VolumeRec &v, const Daughter
     uint4v a = {};
     if (nd > 0) a = operand(0);
     const bool act = lane < count;
-    const int64_t i = base + (act ? lane : 0);
+    const int64_t i = act ? base + lane : 0;
     const double x = t.x[i], y = t.y[i], z = t.z[i];
     lds_store(&S.px[lane], x);
     lds_store(&S.py[lane], y);
@@ -1967,6 +2077,7 @@ __device__ __forceinline__ void point_compact(const VolumeRec &v, const Daughter
         lds_store(&S.hit[lane], 0x7fffffff);
     }
     const bool on = MODE == 0 ? act : (act && in_m);
+    int qn = 0;
     if (nd > 0 && __builtin_amdgcn_ballot_w64(on) != 0ull) {
         const double s = v.cull_s;
         const float px = (float)(x * s), py = (float)(y * s), pz = (float)(z * s);
@@ -1994,7 +2105,6 @@ __device__ __forceinline__ void point_compact(const VolumeRec &v, const Daughter
         const float lim = kCullR + v.cull_back;
         const bool near = pp <= lim * lim && f <= lim;  // else (or not a number) takes every daughter
         if (MODE == 0) cull_columns(split, fmaf(-f, f, pp), f, col);
-        int qn = 0;
         for (int k0 = 0; k0 < nd; k0 += kCullBlock) {
             unsigned int h[2];
 #pragma unroll
@@ -2021,8 +2131,9 @@ __device__ __forceinline__ void point_compact(const VolumeRec &v, const Daughter
                 qn += __popcll(more);
             }
         }
-        point_flush<MODE, HAS_OFFS, KSET>(dau, offs, S, qn, lane);
+        if (!POOL) point_flush<MODE, HAS_OFFS, KSET>(dau, offs, S, qn, lane);
     }
+    if constexpr (POOL) point_pool<W, HAS_OFFS, KSET>(dau, offs, scr, *pool, wave, qn, lane);
     if (act) {
         if (MODE == 0) {
             out_s[base + lane] = key_step(lds_load(&S.key[lane]));

@@ -319,13 +319,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                                                        const double *__restrict__ offs,
                                                        double *__restrict__ out) {
     if constexpr (CULL) {
+        constexpr bool POOL = KSET != kSetBasic;
         __shared__ PointScratch scr[kBlock / 64];
+        __shared__ PointPool<kBlock / 64> pool;
         const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // (uniform)
         const int64_t base = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * 64;
-        if (base >= t.n) return;
-        const int count = t.n - base < 64 ? (int)(t.n - base) : 64;
-        point_compact<0, HAS_OFFS, KSET>(*vol, dau, cul, offs, t, base, count, scr[wave],
-                                            (int)(threadIdx.x & 63), out, nullptr);
+        if (!POOL && base >= t.n) return;
+        const int64_t left = t.n - base;
+        const int count = left <= 0 ? 0 : (left < 64 ? (int)left : 64);
+        point_compact<0, HAS_OFFS, KSET, POOL, kBlock / 64>(*vol, dau, cul, offs, t, base, count, scr, &pool, wave,
+                                                            (int)(threadIdx.x & 63), out, nullptr);
         return;
     }
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -345,8 +348,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         const int64_t base = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * 64;
         if (base >= t.n) return;
         const int count = t.n - base < 64 ? (int)(t.n - base) : 64;
-        point_compact<1, HAS_OFFS, KSET>(*vol, dau, cul, offs, t, base, count, scr[wave],
-                                            (int)(threadIdx.x & 63), nullptr, out);
+        point_compact<1, HAS_OFFS, KSET, false, kBlock / 64>(*vol, dau, cul, offs, t, base, count, scr, nullptr,
+                                                             wave, (int)(threadIdx.x & 63), nullptr, out);
         return;
     }
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
