@@ -1204,15 +1204,6 @@ struct NavScratch {
     static_assert(U * 64 <= 1024, "track index within the tile: 10 bits");
 };
 
-// Scratch of the compacted safety and localization (one round of 64 points
-// per wavefront): running minima per point and the queue of (point,
-// daughter) pairs, (daughter << 10) | point.
-struct PointQueue {
-    unsigned long long key[64];
-    int hit[64];
-    unsigned int queue[512];
-};
-
 // The key of a step: steps are >= 0 (or -0, taken as +0), so their bits less
 // the sign order them; one more, so that 0 is left for a mother step that is
 // not a number, which is never beaten. A daughter's, larger than every
@@ -1857,8 +1848,7 @@ __device__ __forceinline__ void nav_compact_pooled(const VolumeRec &v, const Dau
 }
 
 // ---------------------------- compacted navigator safety and localization
-// The same queue for the navigator's other two tasks, one round of 64 points
-// per wavefront. Safety: a daughter is queued for a point when |w| < s + r
+// The same for the navigator's other two tasks. Safety: a daughter is queued for a point when |w| < s + r
 // with s the mother's Safety (the daughter's is at least |w| - r, so
 // otherwise it cannot go below the mother's, hence not below the minimum);
 // the minimum is merged as a 64-bit key like the step (-0 as +0).
@@ -1885,15 +1875,16 @@ __device__ __forceinline__ void nav_compact_pooled(const VolumeRec &v, const Dau
 // v_min3 per two pairs and the products once more with s replaced, for 0.83
 // pairs per point and 4.6 appends (a CPU simulation), one batch per
 // wavefront where there were two.
-// Scratch of the compacted safety and localization: the navigator's, plus
-// the wavefront's points, which the queued pairs read back from LDS instead
-// of global memory (each lane stores its own point; the batches read them
-// later in the same wavefront's program order).
-struct PointScratch : PointQueue {
+// Scratch of the safety, per wavefront: running minima, the queue of
+// (daughter << 10) | point, and the points, which the queued pairs read back.
+constexpr int kPointQueue = 512;
+struct PointScratch {
+    unsigned long long key[64];
+    unsigned int queue[kPointQueue];
     double px[64], py[64], pz[64];
 };
 
-template <int MODE, bool HAS_OFFS, int KSET>  // MODE 0: safety, 1: locate
+template <bool HAS_OFFS, int KSET>
 __device__ __forceinline__ void point_flush(const DaughterRec *__restrict__ dau, const double *__restrict__ offs,
                                             PointScratch &S, int qn, int lane) {
     for (int e0 = 0; e0 < qn; e0 += 64) {
@@ -1914,12 +1905,8 @@ __device__ __forceinline__ void point_flush(const DaughterRec *__restrict__ dau,
             const double lx = fma(R[6], wz, fma(R[3], wy, R[0] * wx));
             const double ly = fma(R[7], wz, fma(R[4], wy, R[1] * wx));
             const double lz = fma(R[8], wz, fma(R[5], wy, R[2] * wx));
-            if (MODE == 0) {
-                const unsigned long long key = step_key(any_safety<KSET>(D.shape, D.pcon, lx, ly, lz));
-                __hip_atomic_fetch_min(&S.key[j], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-            } else if (any_contains<KSET>(D.shape, D.pcon, lx, ly, lz)) {
-                __hip_atomic_fetch_min(&S.hit[j], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-            }
+            const unsigned long long key = step_key(any_safety<KSET>(D.shape, D.pcon, lx, ly, lz));
+            __hip_atomic_fetch_min(&S.key[j], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
         }
     }
 }
@@ -1962,7 +1949,7 @@ __device__ __forceinline__ void point_pool(const DaughterRec *__restrict__ dau, 
     constexpr int NK = kind_classes<KSET>();
     PointScratch &S = scr[wave];
     if (qn > kPointPool) {
-        point_flush<0, HAS_OFFS, KSET>(dau, offs, S, qn, lane);
+        point_flush<HAS_OFFS, KSET>(dau, offs, S, qn, lane);
         qn = 0;
     }
     {
@@ -2043,16 +2030,68 @@ __device__ __forceinline__ void point_pool(const DaughterRec *__restrict__ dau, 
     __syncthreads();
 }
 
-// Safety (MODE 0, out_s) or localization (MODE 1, out_w) of the points
-// base + lane (lane < count), in S = scr[wave]. With POOL every wavefront of
-// the workgroup calls it, one past the last point with count 0.
-template <int MODE, bool HAS_OFFS, int KSET, bool POOL, int W>
-__device__ __forceinline__ void point_compact(const VolumeRec &v, const DaughterRec *__restrict__ dau,
+// The tests of a wavefront's 64 points: their columns, and whether a point is
+// within their range (else it takes every daughter).
+struct PointTests {
+    uint4v col[2];
+    bool near;
+};
+// MODE 0: with the mother's Safety `reach`, less the bound of the nearest
+// sphere; f receives the length tested with. `a` is the first block's operand,
+// operand(k0) the others'.
+template <int MODE, typename Operand>
+__device__ __forceinline__ void point_tests(const VolumeRec &v, double x, double y, double z, double reach,
+                                            const uint4v &a, Operand operand, float &f, PointTests &T) {
+    const int nd = v.nd;
+    const double s = v.cull_s;
+    const float px = (float)(x * s), py = (float)(y * s), pz = (float)(z * s);
+    const float pp = fmaf(pz, pz, fmaf(py, py, px * px));
+    CullVector split;
+    cull_columns(px, py, pz, pp, 0x54005400u, split, T.col);
+    f = MODE == 0 ? (float)(reach * s) : 0.0f;
+    if (MODE == 0 && nd >= kNearest) {
+        int g[2] = {0x7f000000, 0x7f000000};  // as integers: any negative result stays the smallest
+        uint4v b = a;
+        for (int k0 = 0; k0 < nd; k0 += kCullBlock) {
+            if (k0 > 0) {
+                b = operand(k0);
+                asm volatile("" : "+v"(b));  // (waited for here, see nav_compact_core)
+            }
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const float16v r = cull_product(b, T.col[c]);
+#pragma unroll
+                for (int i = 0; i < 16; ++i) g[c] = min(g[c], __float_as_int(r[i]));
+            }
+        }
+        const uint2v own = __builtin_amdgcn_permlane32_swap((unsigned int)g[0], (unsigned int)g[1], false, false);
+        f = fminf(f, nearest_bound(v, __int_as_float(min((int)own.x, (int)own.y))));
+    }
+    const float lim = kCullR + v.cull_back;
+    T.near = pp <= lim * lim && f <= lim;  // (false if not a number)
+    if (MODE == 0) cull_columns(split, fmaf(-f, f, pp), f, T.col);
+}
+// Mask of the block's daughters that pass (left: daughters from its first on).
+__device__ __forceinline__ unsigned int point_mask(const uint4v &a, const PointTests &T, int left) {
+    unsigned int h[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const float16v g = cull_product(a, T.col[c]);
+        h[c] = cull_signs<16>([&](int r) { return g[r]; });
+    }
+    const unsigned int m = cull_merge(h[0], h[1]);
+    return T.near ? m : (left >= kCullBlock ? ~0u : (1u << left) - 1u);
+}
+
+// Safety of the points base + lane (lane < count), in scr[wave]. With POOL
+// every wavefront of the workgroup calls it, one past the last point with
+// count 0.
+template <bool HAS_OFFS, int KSET, bool POOL, int W>
+__device__ __forceinline__ void safety_compact(const VolumeRec &v, const DaughterRec *__restrict__ dau,
                                               const CullBlock *__restrict__ cul,
                                               const double *__restrict__ offs, const TracksDev &t,
                                               int64_t base, int count, PointScratch *scr, PointPool<W> *pool,
-                                              int wave, int lane, double *__restrict__ out_s,
-                                              int32_t *__restrict__ out_w) {
+                                              int wave, int lane, double *__restrict__ out) {
     PointScratch &S = scr[wave];
     const int nd = v.nd;
     auto operand = [&](int k0) -> uint4v {
@@ -2067,60 +2106,22 @@ __device__ __forceinline__ void point_compact(const VolumeRec &v, const Daughter
     lds_store(&S.px[lane], x);
     lds_store(&S.py[lane], y);
     lds_store(&S.pz[lane], z);
-    double reach = 0.0;
-    bool in_m = false;
-    if (MODE == 0) {
-        reach = any_safety<KSET>(v.mother, v.pcon, x, y, z);
-        lds_store(&S.key[lane], step_key(reach));
-    } else {
-        in_m = any_contains<KSET>(v.mother, v.pcon, x, y, z);
-        lds_store(&S.hit[lane], 0x7fffffff);
-    }
-    const bool on = MODE == 0 ? act : (act && in_m);
+    const double reach = any_safety<KSET>(v.mother, v.pcon, x, y, z);
+    lds_store(&S.key[lane], step_key(reach));
     int qn = 0;
-    if (nd > 0 && __builtin_amdgcn_ballot_w64(on) != 0ull) {
-        const double s = v.cull_s;
-        const float px = (float)(x * s), py = (float)(y * s), pz = (float)(z * s);
-        const float pp = fmaf(pz, pz, fmaf(py, py, px * px));
-        CullVector split;
-        uint4v col[2];
-        cull_columns(px, py, pz, pp, 0x54005400u, split, col);
-        float f = MODE == 0 ? (float)(reach * s) : 0.0f;
-        if (MODE == 0 && nd >= kNearest) {
-            int g[2] = {0x7f000000, 0x7f000000};  // as integers: any negative result stays the smallest
-            uint4v b = a;
-            for (int k0 = 0; k0 < nd; k0 += kCullBlock) {
-                if (k0 > 0) b = operand(k0);
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const float16v r = cull_product(b, col[c]);
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) g[c] = min(g[c], __float_as_int(r[i]));
-                }
-            }
-            const uint2v own = __builtin_amdgcn_permlane32_swap((unsigned int)g[0], (unsigned int)g[1], false, false);
-            const int gi = min((int)own.x, (int)own.y);
-            f = fminf(f, nearest_bound(v, __int_as_float(gi)));
-        }
-        const float lim = kCullR + v.cull_back;
-        const bool near = pp <= lim * lim && f <= lim;  // else (or not a number) takes every daughter
-        if (MODE == 0) cull_columns(split, fmaf(-f, f, pp), f, col);
+    if (nd > 0 && count > 0) {
+        PointTests T;
+        float f;
+        point_tests<0>(v, x, y, z, reach, a, operand, f, T);
         for (int k0 = 0; k0 < nd; k0 += kCullBlock) {
-            unsigned int h[2];
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                const float16v g = cull_product(a, col[c]);
-                h[c] = cull_signs<16>([&](int r) { return g[r]; });
-            }
-            unsigned int m = cull_merge(h[0], h[1]);
-            if (!near) m = nd - k0 >= kCullBlock ? ~0u : (1u << (nd - k0)) - 1u;
-            if (!on) m = 0u;
+            unsigned int m = point_mask(a, T, nd - k0);
+            if (!act) m = 0u;
             if (k0 + kCullBlock < nd) a = operand(k0 + kCullBlock);
             for (;;) {  // each lane with a daughter left appends its lowest
                 const unsigned long long more = __builtin_amdgcn_ballot_w64(m != 0u);
                 if (more == 0ull) break;
-                if (qn > 512 - 64) {
-                    point_flush<MODE, HAS_OFFS, KSET>(dau, offs, S, qn, lane);
+                if (qn > kPointQueue - 64) {
+                    point_flush<HAS_OFFS, KSET>(dau, offs, S, qn, lane);
                     qn = 0;
                 }
                 if (m != 0u) {
@@ -2131,15 +2132,121 @@ __device__ __forceinline__ void point_compact(const VolumeRec &v, const Daughter
                 qn += __popcll(more);
             }
         }
-        if (!POOL) point_flush<MODE, HAS_OFFS, KSET>(dau, offs, S, qn, lane);
     }
     if constexpr (POOL) point_pool<W, HAS_OFFS, KSET>(dau, offs, scr, *pool, wave, qn, lane);
-    if (act) {
-        if (MODE == 0) {
-            out_s[base + lane] = key_step(lds_load(&S.key[lane]));
-        } else {
-            const int w = lds_load(&S.hit[lane]);
-            out_w[base + lane] = !in_m ? -2 : (w != 0x7fffffff ? w : -1);
+    else point_flush<HAS_OFFS, KSET>(dau, offs, S, qn, lane);
+    if (act) out[base + lane] = key_step(lds_load(&S.key[lane]));
+}
+
+// Localization of the points base + u * 64 + lane (u < U, index below `count`
+// > 0 past base), as the navigator takes its tracks: a queue of 64 pairs that
+// carry their points, run when it is full, each round's points requested a
+// round ahead (one round per wavefront waited for its points half its time,
+// and ran a batch for the one pair in 64 points that passes).
+template <int U>
+struct LocateScratch {
+    int hit[U * 64];  // lowest daughter; 0x7fffffff none, -2 outside the mother
+    unsigned int pair[kQueueCap];
+    double x[kQueueCap], y[kQueueCap], z[kQueueCap];
+};
+template <bool HAS_OFFS, int KSET, int U>
+__device__ __forceinline__ void locate_batch(const DaughterRec *__restrict__ dau, const double *__restrict__ offs,
+                                             LocateScratch<U> &S, int qn, int lane) {
+    if (lane < qn) {
+        const unsigned int q = S.pair[lane];
+        const int j = (int)(q & 1023u);
+        const int k = (int)(q >> 10);
+        const DaughterRec &D = dau[k];
+        double wx = S.x[lane] - D.tr[0], wy = S.y[lane] - D.tr[1], wz = S.z[lane] - D.tr[2];
+        if (HAS_OFFS) {
+            wx -= offs[3 * k + 0];
+            wy -= offs[3 * k + 1];
+            wz -= offs[3 * k + 2];
+        }
+        const double *R = D.rot;
+        const double lx = fma(R[6], wz, fma(R[3], wy, R[0] * wx));
+        const double ly = fma(R[7], wz, fma(R[4], wy, R[1] * wx));
+        const double lz = fma(R[8], wz, fma(R[5], wy, R[2] * wx));
+        if (any_contains<KSET>(D.shape, D.pcon, lx, ly, lz))
+            __hip_atomic_fetch_min(&S.hit[j], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    }
+}
+template <bool HAS_OFFS, int KSET, int U>
+__device__ __forceinline__ void locate_compact(const VolumeRec &v, const DaughterRec *__restrict__ dau,
+                                               const CullBlock *__restrict__ cul,
+                                               const double *__restrict__ offs, const TracksDev &t,
+                                               int64_t base, int count, LocateScratch<U> &S, int lane,
+                                               int32_t *__restrict__ out) {
+    struct Point {
+        double x, y, z;
+    };
+    const int nd = v.nd;
+    const double *tx = t.x + base, *ty = t.y + base, *tz = t.z + base;
+    auto operand = [&](int k0) -> uint4v {
+        if (!HAS_OFFS) return *reinterpret_cast<const uint4v *>(cul[k0 / kCullBlock].a[lane]);
+        return cull_operand<HAS_OFFS>(v, dau, offs, k0, lane);
+    };
+    auto load = [&](int j) -> Point {  // (a lane past the end: the last point)
+        const unsigned int ju = (unsigned int)(j < count ? j : count - 1);
+        return Point{at32(tx, ju), at32(ty, ju), at32(tz, ju)};
+    };
+    int qn = 0;  // queue length (uniform)
+    Point next = load(lane);
+    uint4v first = {};
+    if (nd > 0) first = operand(0);
+#pragma unroll 1
+    for (int u = 0; u < U; ++u) {
+        if (u * 64 >= count) break;
+        const int j = u * 64 + lane;
+        Point p = next;
+        if (U > 1 && (u + 1) * 64 < count && u + 1 < U) next = load(j + 64);
+        const bool in_m = any_contains<KSET>(v.mother, v.pcon, p.x, p.y, p.z);
+        lds_store(&S.hit[j], in_m ? 0x7fffffff : -2);
+        const bool on = j < count && in_m;
+        if (nd == 0 || __builtin_amdgcn_ballot_w64(on) == 0ull) continue;
+        PointTests T;
+        float f;
+        point_tests<1>(v, p.x, p.y, p.z, 0.0, first, operand, f, T);
+        uint4v a = first;
+        for (int k0 = 0; k0 < nd; k0 += kCullBlock) {
+            if (k0 > 0) {
+                a = operand(k0);
+                asm volatile("" : "+v"(a));  // (waited for here, see nav_compact_core)
+            }
+            unsigned int m = point_mask(a, T, nd - k0);
+            if (!on) m = 0u;
+            // each lane with a daughter left appends its lowest, while there is room
+            for (;;) {
+                const unsigned long long more = __builtin_amdgcn_ballot_w64(m != 0u);
+                if (more == 0ull) break;
+                const int at = qn + lanes_below(more);
+                if (m != 0u && at < kQueueCap) {
+                    S.pair[at] = ((unsigned int)(k0 + __builtin_ctz(m)) << 10) | (unsigned int)j;
+                    S.x[at] = p.x;
+                    S.y[at] = p.y;
+                    S.z[at] = p.z;
+                    m &= m - 1u;
+                }
+                qn += __popcll(more);
+                if (qn >= kQueueCap) {
+                    locate_batch<HAS_OFFS, KSET, U>(dau, offs, S, kQueueCap, lane);
+                    qn = 0;
+                    // the points are read again (from an address that is not
+                    // formed ahead of the batch)
+                    int again = j;
+                    asm volatile("" : "+v"(again));
+                    p = load(again);
+                }
+            }
+        }
+    }
+    if (qn > 0) locate_batch<HAS_OFFS, KSET, U>(dau, offs, S, qn, lane);
+#pragma unroll 1
+    for (int u = 0; u < U; ++u) {
+        const int j = u * 64 + lane;
+        if (j < count) {
+            const int w = lds_load(&S.hit[j]);
+            at32(out + base, (unsigned int)j) = w != 0x7fffffff ? w : -1;
         }
     }
 }

@@ -312,6 +312,11 @@ hipError_t launch_nav_basket(const VolumeRec *vol, const DaughterRec *dau, const
 }
 
 // -------------------------------------------------- safety and locate
+// The safety takes one round of 64 points per wavefront, VALU issue being what
+// bounds it (four rounds with a queue run when it is full: 76.1 against 75.6 us
+// at 2^22 points of the toy detector, 23.7 against 22.0 at 10^6); volumes with
+// segments or polycones pool their pairs over the workgroup. 2^22 points, three
+// sets in turn, with FP64 culling tests 110 us; of every kind 364, now 189.
 template <bool HAS_OFFS, bool CULL, int KSET>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_nav_safety(const VolumeRec *__restrict__ vol,
                                                        const DaughterRec *__restrict__ dau,
@@ -327,8 +332,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         if (!POOL && base >= t.n) return;
         const int64_t left = t.n - base;
         const int count = left <= 0 ? 0 : (left < 64 ? (int)left : 64);
-        point_compact<0, HAS_OFFS, KSET, POOL, kBlock / 64>(*vol, dau, cul, offs, t, base, count, scr, &pool, wave,
-                                                            (int)(threadIdx.x & 63), out, nullptr);
+        safety_compact<HAS_OFFS, KSET, POOL, kBlock / 64>(*vol, dau, cul, offs, t, base, count, scr, &pool, wave,
+                                                          (int)(threadIdx.x & 63), out);
         return;
     }
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -336,20 +341,20 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     out[i] = nav_safety<HAS_OFFS, KSET>(*vol, dau, offs, t.x[i], t.y[i], t.z[i]);
 }
 
-template <bool HAS_OFFS, bool CULL, int KSET>
+template <bool HAS_OFFS, bool CULL, int KSET, int U = 1>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_nav_locate(const VolumeRec *__restrict__ vol,
                                                        const DaughterRec *__restrict__ dau,
                                                        const CullBlock *__restrict__ cul, TracksDev t,
                                                        const double *__restrict__ offs,
                                                        int32_t *__restrict__ out) {
     if constexpr (CULL) {
-        __shared__ PointScratch scr[kBlock / 64];
+        __shared__ LocateScratch<U> scr[kBlock / 64];
         const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // (uniform)
-        const int64_t base = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * 64;
+        const int64_t base = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * (64 * U);
         if (base >= t.n) return;
-        const int count = t.n - base < 64 ? (int)(t.n - base) : 64;
-        point_compact<1, HAS_OFFS, KSET, false, kBlock / 64>(*vol, dau, cul, offs, t, base, count, scr, nullptr,
-                                                             wave, (int)(threadIdx.x & 63), nullptr, out);
+        const int count = t.n - base < 64 * U ? (int)(t.n - base) : 64 * U;
+        locate_compact<HAS_OFFS, KSET, U>(*vol, dau, cul, offs, t, base, count, scr[wave], (int)(threadIdx.x & 63),
+                                          out);
         return;
     }
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -365,19 +370,15 @@ static void launch_safety_variant(dim3 grid, const VolumeRec *vol, const Daughte
     else hipLaunchKernelGGL((k_nav_safety<false, CULL, KSET>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
 }
 
-template <bool CULL, int KSET>
-static void launch_locate_variant(dim3 grid, const VolumeRec *vol, const DaughterRec *dau,
+template <bool CULL, int KSET, int U = 1>
+static void launch_locate_variant(const VolumeRec *vol, const DaughterRec *dau,
                                   const CullBlock *cul, const TracksDev &t, const double *offs,
                                   int32_t *out, hipStream_t st) {
-    if (offs) hipLaunchKernelGGL((k_nav_locate<true, CULL, KSET>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
-    else hipLaunchKernelGGL((k_nav_locate<false, CULL, KSET>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
+    const dim3 grid((unsigned)((t.n + kBlock * U - 1) / (kBlock * U)));
+    if (offs) hipLaunchKernelGGL((k_nav_locate<true, CULL, KSET, U>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
+    else hipLaunchKernelGGL((k_nav_locate<false, CULL, KSET, U>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
 }
 
-// One round of 64 points per wavefront: with four (as the basket navigator
-// takes for large baskets) both ran 5-15 % slower on the toy detector. At
-// 2^22 points there, before and after the tests on the matrix cores and the
-// safety's bound from the nearest sphere: safety 105.7 to 74.8 us, localization
-// 37.0 to 30.4.
 hipError_t launch_nav_safety(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul,
                              const TracksDev &t, const double *offs, double *out, bool cull,
                              int kset, hipStream_t st) {
@@ -388,13 +389,22 @@ hipError_t launch_nav_safety(const VolumeRec *vol, const DaughterRec *dau, const
     return hipGetLastError();
 }
 
+// Localizations of at least kLocateWide points run kLocateRounds rounds of 64
+// per wavefront, still about 3000 wavefronts; smaller ones one round. (Toy
+// detector, three sets in turn, one round / four: 2^22 points 35.4 / 29.1 us,
+// 10^6 10.1 / 9.4; every kind 2^20 13.9 / 12.4. 37 us and 17.8 with FP64 culling
+// tests.)
+constexpr int64_t kLocateWide = (int64_t)3 << 18;
+constexpr int kLocateRounds = 4;
+
 hipError_t launch_nav_locate(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul,
                              const TracksDev &t, const double *offs, int32_t *out, bool cull,
                              int kset, hipStream_t st) {
     if (t.n == 0) return hipSuccess;
-    const dim3 grid((unsigned)((t.n + kBlock - 1) / kBlock));
-    if (cull) GN_KSET(kset, (launch_locate_variant<true, KS>(grid, vol, dau, cul, t, offs, out, st)));
-    else GN_KSET(kset, (launch_locate_variant<false, KS>(grid, vol, dau, cul, t, offs, out, st)));
+    if (cull && t.n >= kLocateWide)
+        GN_KSET(kset, (launch_locate_variant<true, KS, kLocateRounds>(vol, dau, cul, t, offs, out, st)));
+    else if (cull) GN_KSET(kset, (launch_locate_variant<true, KS>(vol, dau, cul, t, offs, out, st)));
+    else GN_KSET(kset, (launch_locate_variant<false, KS>(vol, dau, cul, t, offs, out, st)));
     return hipGetLastError();
 }
 

@@ -355,3 +355,34 @@ def test_adjoint_passes(gv, kinds, n):
     terms = (out[True][0].view(np.float64) - gh.cpu().numpy())
     assert np.abs(got - off).max() <= n * 2.3e-16 * np.abs(terms).sum(1).max()
     g.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kinds", [(W.BOX, W.TUBE, W.CONE), (W.BOX, W.TUBE, W.CONE, W.TUBS, W.CONS, W.PCON)])
+@pytest.mark.parametrize("n", [(3 << 18) - 1, 3 << 18, (3 << 18) + 1, (3 << 18) + 257, (1 << 20) + 63])
+def test_locate_rounds(gv, kinds, n):
+    """Localization around the size from which a wavefront takes four rounds,
+    points uniform in the mother and points crowded into the daughters (full
+    queues in the middle of a round): culling on and off, and in smaller
+    baskets, the same indices."""
+    import torch
+    rng = np.random.default_rng(n)
+    vol = _boxes(rng, 40, kinds=kinds)
+    m = 100003
+    p = W.tracks_uniform_in_mother(rng, vol, m)[:3]
+    k = rng.integers(0, vol.nd, m)
+    crowd = vol.trs[k].T + 0.7 * vol.bound_r[k] * rng.uniform(-1, 1, (3, m))
+    offs = torch.from_numpy(rng.uniform(-1, 1, (vol.nd, 3))).cuda()
+    g = gv.Geometry([vol])
+    for pts in (p, crowd, np.where(rng.uniform(size=m) < 0.5, p, 1.5 * crowd)):
+        t = torch.from_numpy(np.ascontiguousarray(pts)).cuda().repeat(1, -(-n // m))[:, :n].contiguous()
+        for f in (None, offs):
+            out = {}
+            for cull in (True, False):
+                g.culling = cull
+                out[cull] = gv.geo_locate(g, 0, t, f)
+            assert torch.equal(out[True], out[False])
+            g.culling = True
+            parts = [gv.geo_locate(g, 0, t[:, i:i + m].contiguous(), f) for i in range(0, n, m)]
+            assert torch.equal(out[True], torch.cat(parts))
+    g.close()
