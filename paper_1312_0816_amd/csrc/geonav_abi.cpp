@@ -781,7 +781,7 @@ int geo_navigate_safety(const geo_geometry *g, int32_t volume, geo_tracks t, con
     if (rc || t.n == 0) return rc;
     const int first = g->h_vols[volume].first;
     hipError_t e = launch_nav_safety(g->d_vols + volume, g->d_dau ? g->d_dau + first : nullptr,
-                                     volume_blocks(g, volume), to_dev(t),
+                                     volume_blocks(g, volume), g->h_vols[volume].nd, to_dev(t),
                                      g->h_vols[volume].nd > 0 ? offsets : nullptr, safety,
                                      culls(g, volume) && g->h_vols[volume].nd > kSafetyAll,
                                      g->vol_kset[volume], stream);

@@ -1877,16 +1877,61 @@ __device__ __forceinline__ void nav_compact_pooled(const VolumeRec &v, const Dau
 // wavefront where there were two.
 // Scratch of the safety, per wavefront: running minima, the queue of
 // (daughter << 10) | point, and the points, which the queued pairs read back.
-constexpr int kPointQueue = 512;
+constexpr int kPointQueue = 256;
 struct PointScratch {
     unsigned long long key[64];
     unsigned int queue[kPointQueue];
     double px[64], py[64], pz[64];
 };
 
-template <bool HAS_OFFS, int KSET>
-__device__ __forceinline__ void point_flush(const DaughterRec *__restrict__ dau, const double *__restrict__ offs,
-                                            PointScratch &S, int qn, int lane) {
+// Where the queued pairs read their daughter's record. From the geometry's
+// table, one pair per lane, a batch takes a dozen 16-byte loads of up to 64
+// cache lines each, and they were what bound the safety: 185,000 lookups of
+// the vector cache per CU in the 190,000 cycles of 2^22 points (toy detector),
+// 0.55 of the VALU's slots used. From a copy in the workgroup's LDS, in 16-byte
+// parts whose odd number per record spreads the records over the banks: 75.4
+// to 60.5 us (10^6 points 22.0 to 18.3; 64 daughters, 2^20, 30.8 to 26.8; 8,
+// 17.2 to 15.5; every kind 52.0 to 48.9). Boxes, tubes and cones need the front
+// 19 parts only (the Safety reads c[0] to c[16]): with a queue of 256 pairs
+// seven workgroups of 32 daughters fit a CU, as many as the registers allow.
+struct GlobalRecords {
+    const DaughterRec *__restrict__ dau;
+    static __device__ __forceinline__ void ready() {}
+    __device__ __forceinline__ const DaughterRec &operator[](int k) const { return dau[k]; }
+};
+template <int KSET>
+struct LdsRecords {  // (the front Q parts of each record)
+    static constexpr int Q = KSET == kSetBasic ? 19 : (int)sizeof(DaughterRec) / 16;
+    static_assert(Q % 2 == 1 && Q * 16 >= (int)(offsetof(DaughterRec, shape) + offsetof(ShapeRec, c[17])), "");
+    const uint4v *at;
+    static __device__ __forceinline__ void ready() { __syncthreads(); }
+    __device__ __forceinline__ const DaughterRec &operator[](int k) const {
+        return *reinterpret_cast<const DaughterRec *>(at + k * Q);
+    }
+};
+// Copies them, the workgroup's threads side by side, four loads at a time; read
+// after ready().
+template <int KSET>
+__device__ __forceinline__ void lds_records(const DaughterRec *__restrict__ dau, int nd, uint4v *to) {
+    constexpr int Q = LdsRecords<KSET>::Q, P = (int)sizeof(DaughterRec) / 16, N = 4;
+    const uint4v *from = reinterpret_cast<const uint4v *>(dau);
+    const int n = nd * Q, step = (int)blockDim.x;
+    for (int i0 = (int)threadIdx.x; i0 < n; i0 += N * step) {
+        uint4v r[N];
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+            const int i = i0 + c * step < n ? i0 + c * step : i0;
+            r[c] = from[i / Q * P + i % Q];
+        }
+#pragma unroll
+        for (int c = 0; c < N; ++c)
+            if (i0 + c * step < n) to[i0 + c * step] = r[c];
+    }
+}
+
+template <bool HAS_OFFS, int KSET, typename Records>
+__device__ __forceinline__ void point_flush(const Records &dau, const double *__restrict__ offs, PointScratch &S,
+                                            int qn, int lane) {
     for (int e0 = 0; e0 < qn; e0 += 64) {
         const int e = e0 + lane;
         if (e < qn) {
@@ -1943,9 +1988,8 @@ struct PointPool {
     int cnt[W][kClassSlots];
     unsigned char order[W][kPointPool];  // the queue's places, sorted by class
 };
-template <int W, bool HAS_OFFS, int KSET>
-__device__ __forceinline__ void point_pool(const DaughterRec *__restrict__ dau, const double *__restrict__ offs,
-                                           PointScratch *scr, PointPool<W> &P, int wave, int qn, int lane) {
+template <int W, bool HAS_OFFS, int KSET, typename Records>
+__device__ __forceinline__ void point_pool(const Records &dau, const double *__restrict__ offs, PointScratch *scr, PointPool<W> &P, int wave, int qn, int lane) {
     constexpr int NK = kind_classes<KSET>();
     PointScratch &S = scr[wave];
     if (qn > kPointPool) {
@@ -2086,8 +2130,9 @@ __device__ __forceinline__ unsigned int point_mask(const uint4v &a, const PointT
 // Safety of the points base + lane (lane < count), in scr[wave]. With POOL
 // every wavefront of the workgroup calls it, one past the last point with
 // count 0.
-template <bool HAS_OFFS, int KSET, bool POOL, int W>
+template <bool HAS_OFFS, int KSET, bool POOL, int W, typename Records>
 __device__ __forceinline__ void safety_compact(const VolumeRec &v, const DaughterRec *__restrict__ dau,
+                                              const Records &recs,
                                               const CullBlock *__restrict__ cul,
                                               const double *__restrict__ offs, const TracksDev &t,
                                               int64_t base, int count, PointScratch *scr, PointPool<W> *pool,
@@ -2109,6 +2154,7 @@ __device__ __forceinline__ void safety_compact(const VolumeRec &v, const Daughte
     const double reach = any_safety<KSET>(v.mother, v.pcon, x, y, z);
     lds_store(&S.key[lane], step_key(reach));
     int qn = 0;
+    Records::ready();
     if (nd > 0 && count > 0) {
         PointTests T;
         float f;
@@ -2121,7 +2167,7 @@ __device__ __forceinline__ void safety_compact(const VolumeRec &v, const Daughte
                 const unsigned long long more = __builtin_amdgcn_ballot_w64(m != 0u);
                 if (more == 0ull) break;
                 if (qn > kPointQueue - 64) {
-                    point_flush<HAS_OFFS, KSET>(dau, offs, S, qn, lane);
+                    point_flush<HAS_OFFS, KSET>(recs, offs, S, qn, lane);
                     qn = 0;
                 }
                 if (m != 0u) {
@@ -2133,8 +2179,8 @@ __device__ __forceinline__ void safety_compact(const VolumeRec &v, const Daughte
             }
         }
     }
-    if constexpr (POOL) point_pool<W, HAS_OFFS, KSET>(dau, offs, scr, *pool, wave, qn, lane);
-    else point_flush<HAS_OFFS, KSET>(dau, offs, S, qn, lane);
+    if constexpr (POOL) point_pool<W, HAS_OFFS, KSET>(recs, offs, scr, *pool, wave, qn, lane);
+    else point_flush<HAS_OFFS, KSET>(recs, offs, S, qn, lane);
     if (act) out[base + lane] = key_step(lds_load(&S.key[lane]));
 }
 

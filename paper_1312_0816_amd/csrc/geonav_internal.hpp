@@ -18,7 +18,7 @@ hipError_t launch_nav_basket(const VolumeRec *vol, const DaughterRec *dau, const
                              const TracksDev &t, const double *offs, double *step, int32_t *hit,
                              double *hitpt, bool cull, int kset, hipStream_t st);
 
-hipError_t launch_nav_safety(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul,
+hipError_t launch_nav_safety(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul, int nd,
                              const TracksDev &t, const double *offs, double *out, bool cull,
                              int kset, hipStream_t st);
 hipError_t launch_nav_locate(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul,

@@ -312,12 +312,14 @@ hipError_t launch_nav_basket(const VolumeRec *vol, const DaughterRec *dau, const
 }
 
 // -------------------------------------------------- safety and locate
-// The safety takes one round of 64 points per wavefront, VALU issue being what
-// bounds it (four rounds with a queue run when it is full: 76.1 against 75.6 us
-// at 2^22 points of the toy detector, 23.7 against 22.0 at 10^6); volumes with
-// segments or polycones pool their pairs over the workgroup. 2^22 points, three
-// sets in turn, with FP64 culling tests 110 us; of every kind 364, now 189.
-template <bool HAS_OFFS, bool CULL, int KSET>
+// The safety takes one round of 64 points per wavefront (four rounds with a
+// queue run when it is full: 76.1 against 75.6 us at 2^22 points of the toy
+// detector before the records were in LDS, 23.7 against 22.0 at 10^6); volumes
+// with segments or polycones pool their pairs over the workgroup. With TABLE
+// the workgroup copies the daughters' records into its LDS first. 2^22 points,
+// three sets in turn, with FP64 culling tests 110 us, now 60.5; of every kind
+// 364, now 181.
+template <bool HAS_OFFS, bool CULL, int KSET, bool TABLE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_nav_safety(const VolumeRec *__restrict__ vol,
                                                        const DaughterRec *__restrict__ dau,
                                                        const CullBlock *__restrict__ cul, TracksDev t,
@@ -329,11 +331,19 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         __shared__ PointPool<kBlock / 64> pool;
         const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // (uniform)
         const int64_t base = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * 64;
-        if (!POOL && base >= t.n) return;
+        if (!POOL && !TABLE && base >= t.n) return;
         const int64_t left = t.n - base;
         const int count = left <= 0 ? 0 : (left < 64 ? (int)left : 64);
-        safety_compact<HAS_OFFS, KSET, POOL, kBlock / 64>(*vol, dau, cul, offs, t, base, count, scr, &pool, wave,
-                                                          (int)(threadIdx.x & 63), out);
+        const int lane = (int)(threadIdx.x & 63);
+        if constexpr (TABLE) {
+            extern __shared__ uint4v recs[];
+            lds_records<KSET>(dau, vol->nd, recs);
+            safety_compact<HAS_OFFS, KSET, POOL, kBlock / 64>(*vol, dau, LdsRecords<KSET>{recs}, cul, offs, t, base,
+                                                              count, scr, &pool, wave, lane, out);
+        } else {
+            safety_compact<HAS_OFFS, KSET, POOL, kBlock / 64>(*vol, dau, GlobalRecords{dau}, cul, offs, t, base,
+                                                              count, scr, &pool, wave, lane, out);
+        }
         return;
     }
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -362,12 +372,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     out[i] = nav_locate<HAS_OFFS, KSET>(*vol, dau, offs, t.x[i], t.y[i], t.z[i]);
 }
 
-template <bool CULL, int KSET>
+template <bool CULL, int KSET, bool TABLE = false>
 static void launch_safety_variant(dim3 grid, const VolumeRec *vol, const DaughterRec *dau,
-                                  const CullBlock *cul, const TracksDev &t, const double *offs,
+                                  const CullBlock *cul, int nd, const TracksDev &t, const double *offs,
                                   double *out, hipStream_t st) {
-    if (offs) hipLaunchKernelGGL((k_nav_safety<true, CULL, KSET>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
-    else hipLaunchKernelGGL((k_nav_safety<false, CULL, KSET>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
+    const size_t lds = TABLE ? (size_t)nd * LdsRecords<KSET>::Q * 16 : 0;
+    if (offs)
+        hipLaunchKernelGGL((k_nav_safety<true, CULL, KSET, TABLE>), grid, dim3(kBlock), lds, st, vol, dau, cul, t, offs, out);
+    else
+        hipLaunchKernelGGL((k_nav_safety<false, CULL, KSET, TABLE>), grid, dim3(kBlock), lds, st, vol, dau, cul, t, offs, out);
 }
 
 template <bool CULL, int KSET, int U = 1>
@@ -379,13 +392,21 @@ static void launch_locate_variant(const VolumeRec *vol, const DaughterRec *dau,
     else hipLaunchKernelGGL((k_nav_locate<false, CULL, KSET, U>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
 }
 
-hipError_t launch_nav_safety(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul,
+// Volumes of up to kSafetyTable daughters (20 to 24 KB of records in LDS, four
+// workgroups on a CU) have them copied: faster at every count measured, 8 to
+// 64 (above, and at LdsRecords), and no slower at 10,000 points (7.6 us). Larger
+// volumes read the geometry's table.
+constexpr int kSafetyTable = 64;
+
+hipError_t launch_nav_safety(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul, int nd,
                              const TracksDev &t, const double *offs, double *out, bool cull,
                              int kset, hipStream_t st) {
     if (t.n == 0) return hipSuccess;
     const dim3 grid((unsigned)((t.n + kBlock - 1) / kBlock));
-    if (cull) GN_KSET(kset, (launch_safety_variant<true, KS>(grid, vol, dau, cul, t, offs, out, st)));
-    else GN_KSET(kset, (launch_safety_variant<false, KS>(grid, vol, dau, cul, t, offs, out, st)));
+    if (cull && nd <= kSafetyTable)
+        GN_KSET(kset, (launch_safety_variant<true, KS, true>(grid, vol, dau, cul, nd, t, offs, out, st)));
+    else if (cull) GN_KSET(kset, (launch_safety_variant<true, KS>(grid, vol, dau, cul, nd, t, offs, out, st)));
+    else GN_KSET(kset, (launch_safety_variant<false, KS>(grid, vol, dau, cul, nd, t, offs, out, st)));
     return hipGetLastError();
 }
 

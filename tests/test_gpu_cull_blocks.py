@@ -315,6 +315,30 @@ def test_safety_near_daughters(gv, kinds, nd):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("kinds", [(W.BOX, W.TUBE, W.CONE), (W.TUBE, W.CONS), (W.BOX, W.TUBE, W.CONE, W.TUBS, W.CONS, W.PCON)])
+@pytest.mark.parametrize("nd", [5, 13, 44, 53, 54, 63, 64, 65])
+def test_safety_records(gv, kinds, nd):
+    """The daughters' records copied by a workgroup, around the counts where
+    its copy takes one pass more and where it stops; workgroups and wavefronts
+    that are full, nearly empty and empty; the same bits as the sequential loop."""
+    import torch
+    rng = np.random.default_rng(nd)
+    vol = _boxes(rng, nd, kinds=kinds)
+    tr = torch.from_numpy(W.tracks_uniform_in_mother(rng, vol, 1100)).cuda()
+    offs = torch.from_numpy(rng.uniform(-2, 2, (nd, 3))).cuda()
+    g = gv.Geometry([vol])
+    for n in (1, 63, 64, 65, 192, 256, 257, 1100):
+        p = tr[:3, :n].contiguous()
+        out = {}
+        for cull in (True, False):
+            g.culling = cull
+            out[cull] = [_bits(gv.geo_navigate_safety(g, 0, p, f)) for f in (None, offs)]
+        for a, b in zip(out[True], out[False]):
+            assert np.array_equal(a, b)
+    g.close()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("kinds", [(W.BOX, W.TUBE, W.CONE), (W.BOX, W.TUBE, W.CONE, W.TUBS, W.CONS, W.PCON)])
 @pytest.mark.parametrize("n", [(7 << 16) - 1, 7 << 16, (1 << 20) - 1, 1 << 20, (1 << 20) + 1, (1 << 20) + 255,
                                (1 << 20) + 1025, (1 << 21) + (1 << 20) + 300])
