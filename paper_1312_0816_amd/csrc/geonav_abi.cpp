@@ -431,8 +431,10 @@ void destroy_graph(geo_geometry *g) {
 // culled 13.5).
 constexpr int kBasketAll = 1, kSafetyAll = 4;
 
-// Whether a call on one volume culls.
-bool culls(const geo_geometry *g, int volume) { return g->cull && !g->h_vols[volume].dense; }
+// Whether a call on n tracks of one volume culls.
+bool culls(const geo_geometry *g, int volume, int64_t n) {
+    return g->cull && (!g->h_vols[volume].dense || n <= kDenseFew);
+}
 
 const CullBlock *volume_blocks(const geo_geometry *g, int volume) {
     return g->d_cull ? g->d_cull + g->h_vols[volume].first_block : nullptr;
@@ -697,7 +699,7 @@ int geo_navigate_basket(const geo_geometry *g, int32_t volume, geo_tracks t, con
     hipError_t e = launch_nav_basket(g->d_vols + volume, g->d_dau ? g->d_dau + first : nullptr,
                                      volume_blocks(g, volume), to_dev(t),
                                      g->h_vols[volume].nd > 0 ? offsets : nullptr, step, hit, hitpt,
-                                     culls(g, volume) && g->h_vols[volume].nd > kBasketAll,
+                                     culls(g, volume, t.n) && g->h_vols[volume].nd > kBasketAll,
                                      g->vol_kset[volume], stream);
     if (e != hipSuccess) return hip_fail(e, "navigator launch");
     return GEO_OK;
@@ -721,7 +723,7 @@ int geo_navigate_backward(const geo_geometry *g, int32_t volume, geo_tracks t, c
     hipError_t e = launch_backward(g->d_vols + volume, g->d_dau, g->d_dau ? g->d_dau + first : nullptr,
                                    volume_blocks(g, volume), nd, to_dev(t),
                                    nd > 0 ? offsets : nullptr, gstep, ghit, g_o, g_d, g->d_partial,
-                                   nd > 0 ? g_off : nullptr, culls(g, volume), g->vol_kset[volume], g->d_shift, stream);
+                                   nd > 0 ? g_off : nullptr, culls(g, volume, t.n), g->vol_kset[volume], g->d_shift, stream);
     if (e != hipSuccess) return hip_fail(e, "adjoint launch");
     return GEO_OK;
 }
@@ -755,7 +757,7 @@ int geo_navigate_backward_noalloc(const geo_geometry *g, int32_t volume, geo_tra
     hipError_t e = launch_backward(g->d_vols + volume, g->d_dau, g->d_dau ? g->d_dau + first : nullptr,
                                    volume_blocks(g, volume), nd, to_dev(t),
                                    nd > 0 ? offsets : nullptr, gstep, ghit, g_o, g_d, part,
-                                   nd > 0 ? g_off : nullptr, culls(g, volume), g->vol_kset[volume], nullptr, stream);
+                                   nd > 0 ? g_off : nullptr, culls(g, volume, t.n), g->vol_kset[volume], nullptr, stream);
     if (e != hipSuccess) return hip_fail(e, "adjoint launch");
     return GEO_OK;
 }
@@ -783,7 +785,7 @@ int geo_navigate_safety(const geo_geometry *g, int32_t volume, geo_tracks t, con
     hipError_t e = launch_nav_safety(g->d_vols + volume, g->d_dau ? g->d_dau + first : nullptr,
                                      volume_blocks(g, volume), g->h_vols[volume].nd, to_dev(t),
                                      g->h_vols[volume].nd > 0 ? offsets : nullptr, safety,
-                                     culls(g, volume) && g->h_vols[volume].nd > kSafetyAll,
+                                     culls(g, volume, t.n) && g->h_vols[volume].nd > kSafetyAll,
                                      g->vol_kset[volume], stream);
     if (e != hipSuccess) return hip_fail(e, "safety launch");
     return GEO_OK;
@@ -796,7 +798,7 @@ int geo_locate(const geo_geometry *g, int32_t volume, geo_tracks t, const double
     const int first = g->h_vols[volume].first;
     hipError_t e = launch_nav_locate(g->d_vols + volume, g->d_dau ? g->d_dau + first : nullptr,
                                      volume_blocks(g, volume), to_dev(t),
-                                     g->h_vols[volume].nd > 0 ? offsets : nullptr, where, culls(g, volume),
+                                     g->h_vols[volume].nd > 0 ? offsets : nullptr, where, culls(g, volume, t.n),
                                      g->vol_kset[volume], stream);
     if (e != hipSuccess) return hip_fail(e, "locate launch");
     return GEO_OK;

@@ -84,6 +84,14 @@ struct alignas(16) DaughterRec {
 };
 static_assert(sizeof(DaughterRec) == 368, "DaughterRec layout");
 
+// Tracks up to which a dense volume (VolumeRec.dense) is culled all the same:
+// their pairs fill one or two batches, and each daughter walked in lockstep
+// would be a step of a serial chain for the few lanes. (The paper's toy
+// detector, 8 daughters, us per call of 8, 16, 24, 32, 64 tracks: navigator in
+// lockstep 7.2 7.3 7.3 7.3 7.1, culled 5.0 6.4 6.7 7.6 11.1; adjoint 8.7 and 6.4
+// 7.9 8.1 9.1 12.6; safety 5.4 and 4.2 4.6 4.6 5.2 6.8.)
+constexpr int kDenseFew = 24;
+
 // Culling block: the daughters' operand of the culling tests, which run on
 // the matrix cores (see "Culling" below), for up to kCullBlock daughters of a
 // volume: 8 half-precision entries of each wavefront lane, in the layout of
@@ -109,7 +117,7 @@ struct alignas(16) VolumeRec {
     double cull_s;
     float cull_back;
     int32_t first_block;  // index of the volume's first culling block
-    int32_t dense;        // most lines meet most culling spheres: not culled
+    int32_t dense;        // most lines meet most culling spheres: culled up to kDenseFew tracks only
     // the safety's bound from the nearest culling sphere (see the compacted
     // safety), in the tests' units: of the daughters whose Safety at distance
     // |w| > r is at most sqrt(|w|^2 + c), the largest r^2 + c; of the others,

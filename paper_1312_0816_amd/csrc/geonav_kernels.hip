@@ -444,7 +444,7 @@ __device__ __forceinline__ void run_tile(const Tile &tl, const VolumeRec *__rest
     const VolumeRec &v = vols[tl.volume];
     const DaughterRec *dau = dau_all + v.first;
     if constexpr (CULL) {
-        if (!v.dense) {
+        if (!v.dense || tl.count <= kDenseFew) {
             nav_compact<U, false, false, COUNT, KSET>(v, dau, cul_all + v.first_block, nullptr, t, tl.offset,
                                                       tl.count, *scr, lane, step, hit, nullptr, census);
             return;

@@ -290,6 +290,36 @@ def test_volumes_that_are_not_culled(gv, n):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("n", [1, 23, 24, 25, 64])
+def test_few_tracks_of_a_dense_volume(gv, n):
+    """Up to 24 tracks such a volume is culled: every task, and batched
+    baskets of both sides of the line, the same bits as the sequential loop."""
+    import torch
+    paper = W.paper_toy_detector()
+    tr = torch.from_numpy(np.ascontiguousarray(W.paper_toy_tracks(seed=n, n=40 * n))).cuda()
+    t = tr[:, :n].contiguous()
+    o, d = t[:3].contiguous(), t[3:].contiguous()
+    rng = np.random.default_rng(n)
+    gs, gh = (torch.from_numpy(rng.uniform(-1, 1, k)).cuda() for k in ((n,), (3, n)))
+    offs = torch.from_numpy(rng.uniform(-1, 1, (paper.nd, 3))).cuda()
+    g = gv.Geometry([paper])
+    perm = rng.permutation(40)
+    out = {}
+    for cull in (True, False):
+        g.culling = cull
+        res = []
+        for f in (None, offs):
+            res += [*gv.geo_navigate_basket(g, 0, o, d, f), gv.geo_navigate_safety(g, 0, t, f), gv.geo_locate(g, 0, t, f)]
+        res += gv.geo_navigate_backward(g, 0, o, d, offs, gs, gh)
+        res += gv.geo_navigate_batched(g, np.zeros(40, np.int32), perm * n, np.full(40, n), tr)
+        out[cull] = [_bits(x) for x in res if x is not None]
+    g.close()
+    assert len(out[True]) == len(out[False])
+    for a, b in zip(out[True], out[False]):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("kinds", [(W.BOX,), (W.TUBE, W.CONE), (W.BOX, W.TUBE, W.CONE, W.TUBS, W.CONS, W.PCON)])
 @pytest.mark.parametrize("nd", [7, 8, 32, 70])
 def test_safety_near_daughters(gv, kinds, nd):
