@@ -66,10 +66,9 @@ PROFILE = "k_nav_tiles_batched512.md"
 # launch does comes from the library's census (geo_navigate_batched_census):
 # lane-evaluations per daughter kind, culling tests and tracks.
 FLOPS_MOTHER_BOX = 6             # box DistFromInside: 3 x (sub, div)
-FLOPS_TRACK_CULL = 24            # once per track: |d|^2 (5), 1 / |d| (sqrt, div), |p|^2 (5),
-                                 # p.e with e = d / |d| (6), -2 p (3), -e (3)
-FLOPS_CULL_TEST = 14             # (p - T).e (3 fma), |p|^2 - 2 p.T (3 fma), the half-line's
-                                 # distance term (fma)
+FLOPS_TRACK_CULL = 3             # once per track: the start in the culling tests' units (the
+                                 # rest of its operands is formed in FP32)
+FLOPS_CULL_TEST = 0              # on the matrix cores, from half-precision operands
 FLOPS_ROTATION = 30              # R^T w and R^T d (2 x 3 x (mul + 2 fma))
 FLOPS_DIST_OUT = [               # census slot 2 * kind + hole
     21, 21,                      # box: 3 slab excesses + 3 faces x (div, mul, 2 fma)
