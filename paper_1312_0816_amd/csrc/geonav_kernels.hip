@@ -3,10 +3,13 @@
 //  k_shape_query     one query of one shape over a basket (section 3.1);
 //                    streaming, one lane per track, HBM-bound (the polycone
 //                    and the cone segment's Safety are ALU-bound).
+//  k_shape_dist      the same for the distances of large polycone baskets: the
+//                    tracks that need its sections evaluated are queued.
 //  k_nav_basket      the simple navigator (section 3, Fig. 1b) over one
-//                    basket: culling tests in lockstep queue (track, daughter)
-//                    pairs in LDS, evaluated one pair per lane; bound by VALU
-//                    issue (with culling off, every lane walks every daughter).
+//                    basket: culling tests on the matrix cores, the (track,
+//                    daughter) pairs that pass queued in LDS and evaluated one
+//                    per lane; near the copy rate over large baskets (with
+//                    culling off, every lane walks every daughter).
 //  k_nav_safety      the navigator's isotropic safety (section 3) per point;
 //  k_nav_locate      the daughter holding each point (localization);
 //  k_build_tiles     expands a host-sorted basket list into tiles of at most
