@@ -108,7 +108,7 @@ static_assert(sizeof(CullBlock) == 1024, "CullBlock layout");
 struct alignas(16) VolumeRec {
     ShapeRec mother;
     int32_t nd;     // number of daughters
-    int32_t first;  // index of daughter 0 in the daughter and culling tables
+    int32_t first;  // index of daughter 0 in the daughter table
     const PconRec *pcon;  // the mother's polycone sections (device), or NULL
     double bound_r;       // radius of a sphere about the origin holding the mother
     // the culling tests' coordinates: lengths times cull_s = kCullR / bound_r
@@ -1375,7 +1375,9 @@ __device__ __forceinline__ void nav_batch(const DaughterRec *__restrict__ dau,
 //    exact for it; a line that meets a sphere up to L behind its start
 //    passes as well.
 //  - A daughter whose centre or radius is over kCullMax (out of the mother's
-//    reach) always passes.
+//    reach) always passes. The radii that the volume's bounds (cull_back, the
+//    safety's) are formed from are those within kCullMax, told by the same
+//    product of doubles.
 // A track that starts outside the mother has step 0 from the mother, which
 // no daughter can beat: it is left out, so every start is within 256.
 typedef _Float16 half8v __attribute__((ext_vector_type(8)));
@@ -1427,12 +1429,13 @@ __device__ __forceinline__ uint4v cull_operand(const VolumeRec &v, const Daughte
         tx = (float)(cx * s);
         ty = (float)(cy * s);
         tz = (float)(cz * s);
-        r = (float)(D.cull_r * s);
+        const double rs = D.cull_r * s;
+        r = (float)rs;
         const float tt = fmaf(tz, tz, fmaf(ty, ty, tx * tx));
         const float reach = kCullR + v.cull_back;
         n = fmaf(-0x1p-15f, fmaf(reach, reach, tt), fmaf(-r, r, tt));
         const bool near = s > 0.0 && fabsf(tx) <= kCullMax && fabsf(ty) <= kCullMax && fabsf(tz) <= kCullMax &&
-                          r <= v.cull_back;
+                          rs <= (double)kCullMax;
         if (!near) {  // (or not a number): always passes
             tx = ty = tz = r = 0.0f;
             n = -kCullFar;
