@@ -628,7 +628,7 @@ int geo_geometry_create(const geo_volume_desc *v, int32_t nvol, geo_geometry **o
     if (!dau.empty()) {
         e = hipMemcpy(g->d_dau, dau.data(), sizeof(DaughterRec) * dau.size(), hipMemcpyHostToDevice);
         if (e != hipSuccess) return cleanup(hip_fail(e, "hipMemcpy daughters"));
-        e = launch_cull_blocks(g->d_vols, nvol, max_nd, g->d_dau, g->d_cull, nullptr);
+        e = launch_cull_blocks(g->d_vols, nvol, nblocks, g->d_dau, g->d_cull, nullptr);
         if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
         if (e != hipSuccess) return cleanup(hip_fail(e, "culling blocks"));
     }

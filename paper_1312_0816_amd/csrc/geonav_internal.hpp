@@ -89,8 +89,8 @@ inline int backward_rows(int64_t n) {
 constexpr size_t kScratchDoubles = (size_t)kBackwardMaxBlocks * 3 * 64;  // 3 MiB
 hipError_t scratch_partials(double **out);
 
-// Writes the culling blocks of nvol volumes (of at most max_nd > 0 daughters).
-hipError_t launch_cull_blocks(const VolumeRec *vols, int nvol, int max_nd, const DaughterRec *dau, CullBlock *out,
+// Writes the nblocks > 0 culling blocks of nvol volumes.
+hipError_t launch_cull_blocks(const VolumeRec *vols, int nvol, int nblocks, const DaughterRec *dau, CullBlock *out,
                               hipStream_t st);
 
 // shift_buf: room for the volume's culling blocks moved by the offsets,

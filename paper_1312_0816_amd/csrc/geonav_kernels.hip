@@ -639,28 +639,36 @@ int batched_grid(int waves_per_simd, int num_cus, int64_t ntiles) {
 }
 
 // ------------------------------------------------------------------ adjoint
-// Culling blocks from the daughter records: blockIdx.y is the volume (of
-// vols), blockIdx.x its block, one wavefront each. HAS_OFFS false: into the
-// geometry's table; true: one volume's, moved by this call's daughter
-// offsets, into a buffer of its own (for the adjoint's forward). The tests'
-// centre T + offset is rounded once more than the T of the evaluation, far
-// inside the culling radius's enlargement of 1e-6 relative + 1e-6.
+// Culling blocks from the daughter records, one wavefront each. HAS_OFFS false:
+// block blockIdx.x of the geometry's table, which is of the last volume whose
+// first block is not past it (the blocks run through the volumes in order; one
+// grid dimension, whose limit no geometry reaches, and no workgroup without
+// work where the volumes' counts differ). HAS_OFFS true: one volume's (vols),
+// moved by this call's daughter offsets, into a buffer of its own (for the
+// adjoint's forward). The tests' centre T + offset is rounded once more than
+// the T of the evaluation, far inside the culling radius's enlargement of 1e-6
+// relative + 1e-6.
 template <bool HAS_OFFS>
-__global__ __launch_bounds__(64) void k_cull_blocks(const VolumeRec *__restrict__ vols,
+__global__ __launch_bounds__(64) void k_cull_blocks(const VolumeRec *__restrict__ vols, int nvol,
                                                     const DaughterRec *__restrict__ dau_all,
                                                     const double *__restrict__ offs, CullBlock *__restrict__ out) {
-    const VolumeRec &v = vols[blockIdx.y];
-    const int k0 = (int)blockIdx.x * kCullBlock, lane = (int)threadIdx.x;
-    if (k0 >= v.nd) return;
-    CullBlock *blocks = HAS_OFFS ? out : out + v.first_block;
-    *reinterpret_cast<uint4v *>(blocks[blockIdx.x].a[lane]) =
-        cull_operand<HAS_OFFS>(v, dau_all + v.first, offs, k0, lane);
+    const int block = (int)blockIdx.x, lane = (int)threadIdx.x;
+    int lo = 0;
+    if (!HAS_OFFS) {
+        for (int hi = nvol; hi - lo > 1;) {
+            const int mid = lo + (hi - lo) / 2;
+            if (vols[mid].first_block <= block) lo = mid;
+            else hi = mid;
+        }
+    }
+    const VolumeRec &v = vols[lo];
+    const int k0 = (block - (HAS_OFFS ? 0 : v.first_block)) * kCullBlock;
+    *reinterpret_cast<uint4v *>(out[block].a[lane]) = cull_operand<HAS_OFFS>(v, dau_all + v.first, offs, k0, lane);
 }
 
-hipError_t launch_cull_blocks(const VolumeRec *vols, int nvol, int max_nd, const DaughterRec *dau, CullBlock *out,
+hipError_t launch_cull_blocks(const VolumeRec *vols, int nvol, int nblocks, const DaughterRec *dau, CullBlock *out,
                               hipStream_t st) {
-    const dim3 grid((max_nd + kCullBlock - 1) / kCullBlock, nvol);
-    hipLaunchKernelGGL(k_cull_blocks<false>, grid, dim3(64), 0, st, vols, dau, nullptr, out);
+    hipLaunchKernelGGL(k_cull_blocks<false>, dim3(nblocks), dim3(64), 0, st, vols, nvol, dau, nullptr, out);
     return hipGetLastError();
 }
 
@@ -924,7 +932,7 @@ hipError_t launch_backward(const VolumeRec *vol, const DaughterRec *dau_all, con
         const CullBlock *shifted = nullptr;
         if (cull && offs && shift_buf && nd > 0 && t.n > 0) {
             // (the kernel takes the geometry's daughter table)
-            hipLaunchKernelGGL(k_cull_blocks<true>, dim3((nd + kCullBlock - 1) / kCullBlock), dim3(64), 0, st, vol,
+            hipLaunchKernelGGL(k_cull_blocks<true>, dim3((nd + kCullBlock - 1) / kCullBlock), dim3(64), 0, st, vol, 1,
                                dau_all, offs, shift_buf);
             shifted = shift_buf;
         }

@@ -1,5 +1,6 @@
 """Culling at the ends of its range: daughters whose radii lie around the
-largest that the half-precision tests take."""
+largest that the half-precision tests take, and geometries of very many
+volumes."""
 import numpy as np
 import pytest
 
@@ -59,3 +60,30 @@ def test_safety_radii_around_the_largest(gv, radius):
     for a_, b_ in zip(out[True], out[False]):
         assert np.abs(b_ - nearest).max() < 1e-9
         assert np.array_equal(a_, b_)
+
+
+@pytest.mark.gpu
+def test_many_volumes(gv):
+    """70,001 volumes of none, one or 33 daughters (more than one dimension of
+    a grid takes): each volume's culling blocks are its own."""
+    import torch
+    nvol = 70001
+    rng = np.random.default_rng(4)
+    none = W.Volume(W.BOX, np.array([10.0, 10.0, 10.0, 0.0, 0.0]))
+    one = [_placed((10.0, 10.0, 10.0), [(W.BOX, [0.2, 0.2, 0.2], tuple(rng.uniform(-8, 8, 3)))]) for _ in range(7)]
+    many = _placed((10.0, 10.0, 10.0), [(W.BOX, [0.2, 0.2, 0.2], tuple(rng.uniform(-8, 8, 3))) for _ in range(33)])
+    vols = [none if i % 5 == 3 else (many if i % 1000 == 999 else one[i % 7]) for i in range(nvol)]
+    vols[-3:] = [many, none, one[0]]
+    g = gv.Geometry(vols)
+    t = torch.from_numpy(W.tracks_uniform_in_mother(rng, one[0], 40)).cuda()
+    o, d = t[:3].contiguous(), t[3:].contiguous()
+    for v in (0, 1, 3, 999, 65535, 65536, 69999, nvol - 3, nvol - 2, nvol - 1):
+        out = {}
+        for cull in (True, False):
+            g.culling = cull
+            res = [*gv.geo_navigate_basket(g, v, o, d), gv.geo_navigate_safety(g, v, o), gv.geo_locate(g, v, o)]
+            res += list(gv.geo_navigate_batched(g, [v], [0], [40], t))
+            out[cull] = [x.cpu().numpy() for x in res if x is not None]
+        for a, b in zip(out[True], out[False]):
+            assert np.array_equal(a, b)
+    g.close()
