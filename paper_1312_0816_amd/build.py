@@ -11,6 +11,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libgeonav.so")
 SOURCES = ["geonav_kernels.hip", "geonav_abi.cpp"]
+PARTS = {"geonav_kernels.hip": 5}  # objects a source is compiled to, by its sections (GEONAV_PART)
 HEADERS = ["geonav_device.hpp", "geonav_internal.hpp"]
 
 ARCH = os.environ.get("GEONAV_ARCH", "gfx950")
@@ -26,17 +27,25 @@ FLAGS = [
 
 
 def build(verbose: bool = False) -> str:
-    """Compile every source and link libgeonav.so (always rebuilds)."""
-    objs = []
+    """Compile every source, the objects side by side, and link libgeonav.so
+    (always rebuilds)."""
+    objs, cmds = [], []
     bdir = os.path.join(PKG, "_build")
     os.makedirs(bdir, exist_ok=True)
     for src in SOURCES:
-        obj = os.path.join(bdir, os.path.splitext(src)[0] + ".o")
-        cmd = ["hipcc", "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj] + FLAGS
-        if verbose:
-            print(" ".join(cmd), flush=True)
-        subprocess.run(cmd, check=True)
-        objs.append(obj)
+        parts = PARTS.get(src, 0)
+        for part in range(1, parts + 1) if parts else [0]:
+            obj = os.path.join(bdir, os.path.splitext(src)[0] + (str(part) if part else "") + ".o")
+            cmd = ["hipcc", "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj] + FLAGS
+            cmds.append(cmd + ([f"-DGEONAV_PART={part}"] if part else []))
+            objs.append(obj)
+            if verbose:
+                print(" ".join(cmds[-1]), flush=True)
+    procs = [subprocess.Popen(cmd) for cmd in cmds]
+    codes = [p.wait() for p in procs]  # (all of them, so that none outlives a failure)
+    for cmd, code in zip(cmds, codes):
+        if code:
+            raise subprocess.CalledProcessError(code, cmd)
     tmp = LIB + ".tmp"
     cmd = ["hipcc", "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp] + objs
     if verbose:

@@ -28,6 +28,12 @@
 
 #include "geonav_internal.hpp"
 
+// The build compiles this file's sections, GEONAV_PART 1 to 5, side by side.
+#ifndef GEONAV_PART
+#define GEONAV_PART 0
+#endif
+#define GN_PART(p) (GEONAV_PART == 0 || GEONAV_PART == (p))
+
 namespace gn {
 
 // Runs STMT with the compile-time constant KS set to the runtime kind set.
@@ -45,6 +51,7 @@ namespace gn {
         }                                                   \
     } while (0)
 
+#if GN_PART(1)
 // ------------------------------------------------------------ shape queries
 // A polycone's sections come by value with the arguments (`pc`, unused for
 // the other kinds).
@@ -215,7 +222,9 @@ hipError_t launch_shape_query(const ShapeRec &s, const PconRec &pc, int query, c
             return launch_shape_kind<kPcons>(s, pc, query, t, out, st);
     }
 }
+#endif
 
+#if GN_PART(2)
 // ---------------------------------------------------------- basket navigator
 // With culling, one wavefront takes U rounds of 64 tracks (compacted
 // evaluation; more tracks per wavefront fill more lanes of each batch of
@@ -313,7 +322,9 @@ hipError_t launch_nav_basket(const VolumeRec *vol, const DaughterRec *dau, const
     }
     return hipGetLastError();
 }
+#endif
 
+#if GN_PART(1)
 // -------------------------------------------------- safety and locate
 // The safety takes one round of 64 points per wavefront (four rounds with a
 // queue run when it is full: 76.1 against 75.6 us at 2^22 points of the toy
@@ -431,7 +442,9 @@ hipError_t launch_nav_locate(const VolumeRec *vol, const DaughterRec *dau, const
     else GN_KSET(kset, (launch_locate_variant<false, KS>(vol, dau, cul, t, offs, out, st)));
     return hipGetLastError();
 }
+#endif
 
+#if GN_PART(3) || GN_PART(5)
 // ------------------------------------------------------------------ batched
 // A tile holds at most 64 * U tracks of one volume: U rounds of one track
 // per lane, so the volume and its daughters are uniform over the wavefront.
@@ -552,6 +565,48 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 5
                                    (int)(threadIdx.x & 63), &scr[CULL ? (threadIdx.x >> 6) : 0]);
 }
 
+template <bool PERSISTENT, int U, bool CULL, bool COUNT, int KSET>
+static const void *pick_mode() {
+    if constexpr (PERSISTENT) return reinterpret_cast<const void *>(&k_nav_persistent<U, CULL, COUNT, KSET>);
+    else return reinterpret_cast<const void *>(&k_nav_tiles<U, CULL, COUNT, KSET>);
+}
+
+template <bool PERSISTENT, bool CULL, bool COUNT, int KSET>
+static const void *pick_u(int U) {
+    switch (U) {
+        case 1: return pick_mode<PERSISTENT, 1, CULL, COUNT, KSET>();
+        case 2: return pick_mode<PERSISTENT, 2, CULL, COUNT, KSET>();
+        case 4: return pick_mode<PERSISTENT, 4, CULL, COUNT, KSET>();
+        default: return pick_mode<PERSISTENT, 8, CULL, COUNT, KSET>();
+    }
+}
+
+// The census variants (instrumentation, not timed) exist for the full kind
+// set only.
+template <bool PERSISTENT>
+static const void *pick_kernel(int tracks_per_lane, bool cull, bool count, int kset) {
+    const void *k = nullptr;
+    if (count) {
+        k = cull ? pick_u<PERSISTENT, true, true, kSetAll>(tracks_per_lane)
+                 : pick_u<PERSISTENT, false, true, kSetAll>(tracks_per_lane);
+    } else if (cull) {
+        GN_KSET(kset, (k = pick_u<PERSISTENT, true, false, KS>(tracks_per_lane)));
+    } else {
+        GN_KSET(kset, (k = pick_u<PERSISTENT, false, false, KS>(tracks_per_lane)));
+    }
+    return k;
+}
+
+const void *persistent_kernel(int tracks_per_lane, bool cull, bool count, int kset);
+#endif
+
+#if GN_PART(5)
+const void *persistent_kernel(int tracks_per_lane, bool cull, bool count, int kset) {
+    return pick_kernel<true>(tracks_per_lane, cull, count, kset);
+}
+#endif
+
+#if GN_PART(3)
 // Expands the (cost-sorted) basket list into tiles of at most tile_n tracks:
 // basket b owns tiles [tile_start[b], tile_start[b + 1]). The baskets are
 // split into one contiguous run per wavefront (ceil(nb / waves) baskets, so
@@ -597,35 +652,9 @@ __global__ __launch_bounds__(kBlock) void k_build_tiles(BuildTilesArgs a) {
     }
 }
 
-template <int U, bool CULL, bool COUNT, int KSET>
-static const void *pick_mode(bool persistent) {
-    return persistent ? reinterpret_cast<const void *>(&k_nav_persistent<U, CULL, COUNT, KSET>)
-                      : reinterpret_cast<const void *>(&k_nav_tiles<U, CULL, COUNT, KSET>);
-}
-
-template <bool CULL, bool COUNT, int KSET>
-static const void *pick_u(int U, bool persistent) {
-    switch (U) {
-        case 1: return pick_mode<1, CULL, COUNT, KSET>(persistent);
-        case 2: return pick_mode<2, CULL, COUNT, KSET>(persistent);
-        case 4: return pick_mode<4, CULL, COUNT, KSET>(persistent);
-        default: return pick_mode<8, CULL, COUNT, KSET>(persistent);
-    }
-}
-
-// The census variants (instrumentation, not timed) exist for the full kind
-// set only.
 const void *batched_kernel(int tracks_per_lane, bool cull, bool persistent, bool count, int kset) {
-    const void *k = nullptr;
-    if (count) {
-        k = cull ? pick_u<true, true, kSetAll>(tracks_per_lane, persistent)
-                 : pick_u<false, true, kSetAll>(tracks_per_lane, persistent);
-    } else if (cull) {
-        GN_KSET(kset, (k = pick_u<true, false, KS>(tracks_per_lane, persistent)));
-    } else {
-        GN_KSET(kset, (k = pick_u<false, false, KS>(tracks_per_lane, persistent)));
-    }
-    return k;
+    return persistent ? persistent_kernel(tracks_per_lane, cull, count, kset)
+                      : pick_kernel<false>(tracks_per_lane, cull, count, kset);
 }
 
 const void *build_tiles_kernel() { return reinterpret_cast<const void *>(&k_build_tiles); }
@@ -637,7 +666,9 @@ int batched_grid(int waves_per_simd, int num_cus, int64_t ntiles) {
     if (waves_per_simd > 0) return num_cus * waves_per_simd;
     return (int)((ntiles + kBlock / 64 - 1) / (kBlock / 64));
 }
+#endif
 
+#if GN_PART(4)
 // ------------------------------------------------------------------ adjoint
 // Culling blocks from the daughter records, one wavefront each. HAS_OFFS false:
 // block blockIdx.x of the geometry's table, which is of the last volume whose
@@ -987,5 +1018,6 @@ hipError_t scratch_partials(double **out) {
     *out = g_scratch_ptr[dev];
     return hipSuccess;
 }
+#endif
 
 }  // namespace gn
