@@ -489,9 +489,10 @@ __device__ __forceinline__ void run_tile(const Tile &tl, const VolumeRec *__rest
 // spread over kQueues addresses instead of contending on one. A wavefront
 // drains the queue of its workgroup's XCD slot (blockIdx mod kQueues) first,
 // then the others in turn; it exits once every queue's cursor has passed the
-// queue's length, so every wavefront terminates.
+// queue's length, so every wavefront terminates. (Every kind, 4 rounds, 4 wavefronts
+// per SIMD: compiled for 5, which spills here, 178 us, for 4 150.)
 template <int U, bool CULL, bool COUNT, int KSET>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 5 : 1))) void k_nav_persistent(const VolumeRec *__restrict__ vols,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!CULL ? 1 : U == 1 ? 5 : 4))) void k_nav_persistent(const VolumeRec *__restrict__ vols,
                                                            const DaughterRec *__restrict__ dau_all,
                                                            const CullBlock *__restrict__ cul_all,
                                                            const Tile *__restrict__ tiles,
@@ -519,11 +520,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 5
 
 // Hardware-scheduled form: one wavefront per tile, workgroups dispatched in
 // tile order (same parameters as the persistent form; `cursors` unused).
-// Registers as in the basket navigator. (512 baskets of 64 volumes, three
-// pools in turn, with the tile expansion: 96 us with FP64 culling tests, 79.8
-// at 4 wavefronts per SIMD, 76.9 at 5.)
+// Registers as in the basket navigator, 5 wavefronts per SIMD, but for tiles of 2
+// rounds, which spill there (4.4 M tracks in 512 baskets: 99 at 5, 79 us at 4; every
+// kind 163 and 115). (Of 4 rounds, three pools in turn, with the tile expansion: 96
+// us with FP64 culling tests, 79.8 at 4 wavefronts per SIMD, 76.9 at 5.)
 template <int U, bool CULL, bool COUNT, int KSET>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 5 : 1))) void k_nav_tiles(const VolumeRec *__restrict__ vols,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!CULL ? 1 : U == 2 ? 4 : 5))) void k_nav_tiles(const VolumeRec *__restrict__ vols,
                                                       const DaughterRec *__restrict__ dau_all,
                                                       const CullBlock *__restrict__ cul_all,
                                                       const Tile *__restrict__ tiles, int32_t ntiles,
