@@ -427,13 +427,19 @@ void destroy_graph(geo_geometry *g) {
 
 // Volumes of at most this many daughters take all of them in lockstep: a
 // basket through the navigator (2^22 tracks, one daughter: 41.7 us, culled
-// 43.5; 4: 71.5 and 48.9), the safety (2^20 points, 4 daughters: 13.1 us,
-// culled 13.5).
-constexpr int kBasketAll = 1, kSafetyAll = 4;
+// 43.5; 3: 55.3 and 42.5), a smaller one of fewer than kBasketFew tracks (two
+// daughters: 300,000 tracks 5.7 us, culled 6.8, 40,000 3.6 and 4.7; 2^20 16.9 and
+// 15.0), the safety (2^20 points, 4 daughters: 13.1 us, culled 13.5).
+constexpr int kBasketAll = 1, kBasketAllFew = 2, kSafetyAll = 4;
+constexpr int64_t kBasketFew = (int64_t)1 << 19;
 
 // Whether a call on n tracks of one volume culls.
 bool culls(const geo_geometry *g, int volume, int64_t n) {
     return g->cull && (!g->h_vols[volume].dense || n <= kDenseFew);
+}
+
+bool basket_culls(const geo_geometry *g, int volume, int64_t n) {
+    return culls(g, volume, n) && g->h_vols[volume].nd > (n < kBasketFew ? kBasketAllFew : kBasketAll);
 }
 
 const CullBlock *volume_blocks(const geo_geometry *g, int volume) {
@@ -699,7 +705,7 @@ int geo_navigate_basket(const geo_geometry *g, int32_t volume, geo_tracks t, con
     hipError_t e = launch_nav_basket(g->d_vols + volume, g->d_dau ? g->d_dau + first : nullptr,
                                      volume_blocks(g, volume), to_dev(t),
                                      g->h_vols[volume].nd > 0 ? offsets : nullptr, step, hit, hitpt,
-                                     culls(g, volume, t.n) && g->h_vols[volume].nd > kBasketAll,
+                                     basket_culls(g, volume, t.n),
                                      g->vol_kset[volume], stream);
     if (e != hipSuccess) return hip_fail(e, "navigator launch");
     return GEO_OK;
@@ -797,7 +803,7 @@ int geo_locate(const geo_geometry *g, int32_t volume, geo_tracks t, const double
     if (rc || t.n == 0) return rc;
     const int first = g->h_vols[volume].first;
     hipError_t e = launch_nav_locate(g->d_vols + volume, g->d_dau ? g->d_dau + first : nullptr,
-                                     volume_blocks(g, volume), to_dev(t),
+                                     volume_blocks(g, volume), g->h_vols[volume].nd, to_dev(t),
                                      g->h_vols[volume].nd > 0 ? offsets : nullptr, where, culls(g, volume, t.n),
                                      g->vol_kset[volume], stream);
     if (e != hipSuccess) return hip_fail(e, "locate launch");

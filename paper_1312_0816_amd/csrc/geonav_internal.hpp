@@ -22,7 +22,7 @@ hipError_t launch_nav_safety(const VolumeRec *vol, const DaughterRec *dau, const
                              const TracksDev &t, const double *offs, double *out, bool cull,
                              int kset, hipStream_t st);
 hipError_t launch_nav_locate(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul,
-                             const TracksDev &t, const double *offs, int32_t *out, bool cull,
+                             int nd, const TracksDev &t, const double *offs, int32_t *out, bool cull,
                              int kset, hipStream_t st);
 
 // Tile queues of the persistent batched kernel: one per XCD, cursors 256 B

@@ -424,19 +424,20 @@ hipError_t launch_nav_safety(const VolumeRec *vol, const DaughterRec *dau, const
     return hipGetLastError();
 }
 
-// Localizations of at least kLocateWide points run kLocateRounds rounds of 64
-// per wavefront, still about 3000 wavefronts; smaller ones one round. (Toy
-// detector, three sets in turn, one round / four: 2^22 points 35.4 / 29.1 us,
-// 10^6 10.1 / 9.4; every kind 2^20 13.9 / 12.4. 37 us and 17.8 with FP64 culling
-// tests.)
+// Localizations of at least kLocateWide points in volumes of kLocateWideNd
+// daughters or more run kLocateRounds rounds of 64 per wavefront, still about 3000
+// wavefronts; smaller ones one round. (Toy detector, three sets in turn, one round /
+// four: 2^22 points 35.4 / 29.1 us, 10^6 10.1 / 9.4; every kind 2^20 13.9 / 12.4. 37 us
+// and 17.8 with FP64 culling tests. 8 daughters, one set, 2^20 6.0 / 7.0, 16 6.0 / 7.0;
+// six sets, 2^21 15.8 / 15.3 and 15.5 / 14.9.)
 constexpr int64_t kLocateWide = (int64_t)3 << 18;
-constexpr int kLocateRounds = 4;
+constexpr int kLocateRounds = 4, kLocateWideNd = 12;
 
 hipError_t launch_nav_locate(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul,
-                             const TracksDev &t, const double *offs, int32_t *out, bool cull,
+                             int nd, const TracksDev &t, const double *offs, int32_t *out, bool cull,
                              int kset, hipStream_t st) {
     if (t.n == 0) return hipSuccess;
-    if (cull && t.n >= kLocateWide)
+    if (cull && t.n >= kLocateWide && nd >= kLocateWideNd)
         GN_KSET(kset, (launch_locate_variant<true, KS, kLocateRounds>(vol, dau, cul, t, offs, out, st)));
     else if (cull) GN_KSET(kset, (launch_locate_variant<true, KS>(vol, dau, cul, t, offs, out, st)));
     else GN_KSET(kset, (launch_locate_variant<false, KS>(vol, dau, cul, t, offs, out, st)));
