@@ -1569,7 +1569,16 @@ __device__ __forceinline__ unsigned int cull_mask(const uint4v &a, const CullTra
     return left <= 16 ? cull_mask_of<8>(a, c) : cull_mask_of<16>(a, c);
 }
 
-// Navigates the tracks base + u * STRIDE + lane (u < U, index below `count` > 0
+struct Track {
+    double x, y, z, ux, uy, uz;
+};
+// Where the (up to four) rounds of an adjoint workgroup's wavefront start.
+struct Rounds {
+    int odd, pair;
+    __device__ __forceinline__ int at(int u) const { return (u & 1) * odd + (u >> 1) * pair; }
+};
+
+// Navigates the tracks base + u * 64 + lane (u < U, index below `count` > 0
 // past base) of one volume, leaving each track's step (as a key) and hit
 // index in S; with SURF, the hit slot also carries the surface that set the
 // step (for the adjoint). Each round's tracks are requested a round ahead
@@ -1583,20 +1592,17 @@ __device__ __forceinline__ unsigned int cull_mask(const uint4v &a, const CullTra
 // or the blocks of this call's offsets); else they are formed from the
 // daughter records and the offsets, once per wavefront for the first block
 // and once per round for the others.
-struct Track {
-    double x, y, z, ux, uy, uz;
-};
 //
-// STRIDE is the distance of the rounds' first tracks (64: a tile of
-// consecutive tracks); `count` then counts the tracks from base to the end
-// of the last round.
+// With TILE the rounds follow one another; else round u starts rounds.at(u)
+// tracks past base, and `count` counts the tracks from base on.
 template <int U, bool HAS_OFFS, bool COUNT, int KSET, bool SURF = true, bool FINAL = true, bool TABLE = !HAS_OFFS,
-          int STRIDE = 64>
+          bool TILE = true>
 __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const DaughterRec *__restrict__ dau,
                                                 const CullBlock *__restrict__ cul,
                                                 const double *__restrict__ offs, const TracksDev &t,
                                                 int64_t base, int count, NavScratch<U> &S, int lane,
-                                                unsigned long long *census = nullptr) {
+                                                unsigned long long *census = nullptr,
+                                                const Rounds &rounds = Rounds{0, 0}) {
     int qn = 0;  // queue length (uniform)
     const int nd = v.nd;
     const TileTracks tt = tile_tracks(t, base);
@@ -1604,13 +1610,13 @@ __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const Daught
         if (TABLE) return *reinterpret_cast<const uint4v *>(cul[k0 / kCullBlock].a[lane]);
         return cull_operand<HAS_OFFS>(v, dau, offs, k0, lane);
     };
-    auto place = [](int j) { return STRIDE == 64 ? j : (j >> 6) * STRIDE + (j & 63); };
-    auto load = [&](int j) -> Track {  // (a lane past the end: the last track)
-        const int at = place(j);
+    auto place = [&](int j, int u) { return TILE ? j : rounds.at(u) + (j & 63); };  // (track j, of round u)
+    auto load = [&](int j, int u) -> Track {  // (a lane past the end: the last track)
+        const int at = place(j, u);
         const unsigned int ju = (unsigned int)(at < count ? at : count - 1);
         return Track{at32(tt.x, ju), at32(tt.y, ju), at32(tt.z, ju), at32(tt.ux, ju), at32(tt.uy, ju), at32(tt.uz, ju)};
     };
-    Track next = load(lane);
+    Track next = load(lane, 0);
     uint4v first = {};
     if (nd > 0) first = operand(0);
     constexpr bool SECOND = NavScratch<U>::kSecond && KSET == kSetBasic;
@@ -1618,12 +1624,13 @@ __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const Daught
     if (SECOND && nd > kCullBlock) *reinterpret_cast<uint4v *>(S.second[lane]) = operand(kCullBlock);
 #pragma unroll 1
     for (int u = 0; u < U; ++u) {
-        if (u * STRIDE >= count) break;
+        if (TILE && u * 64 >= count) break;
         const int j = u * 64 + lane;
-        const bool act = place(j) < count;
+        const bool act = place(j, u) < count;
         uint4v a = first;
         Track p = next;
-        if (U > 1 && (u + 1) * STRIDE < count && u + 1 < U) next = load(j + 64);
+        if (U > 1 && (!TILE || (u + 1) * 64 < count) && u + 1 < U) next = load(j + 64, u + 1);
+        if (!TILE && rounds.at(u) >= count) continue;
         int sid;
         const double ms = mother_step<SURF, KSET>(v, p.x, p.y, p.z, p.ux, p.uy, p.uz, sid);
         lds_store(&S.key[j], mother_key(ms));
@@ -1677,8 +1684,8 @@ __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const Daught
                     // to 91 VGPRs
                     int again = j;
                     asm volatile("" : "+v"(again));
-                    p = load(again);
-                    if (U > 1) next = load(again + 64);
+                    p = load(again, u);
+                    if (U > 1) next = load(again + 64, u + 1);
                     if (TABLE) first = operand(0);
                     if (U == 1 || k0 + kCullBlock < nd)
                         cull_tracks(v, p.x, p.y, p.z, p.ux, p.uy, p.uz, on, c);

@@ -718,16 +718,19 @@ hipError_t launch_cull_blocks(const VolumeRec *vols, int nvol, int nblocks, cons
 // itself) and written once. With TABLE the forward's culling operands are
 // read from `cul`: the volume's, or with offsets those k_cull_blocks moved.
 //
-// A workgroup takes U passes of 256 tracks at a time: each wavefront navigates
-// its 64 tracks of all of them in one go, so that a batch of queued pairs
-// holds U times as many, then the passes are differentiated one by one.
+// Row b of the partial sums is that of the passes (of 256 tracks) b, b + rows,
+// b + 2 rows, ..., added in that order, whatever CULL and U: the sums' bits do
+// not depend on them. A workgroup takes U passes at a time: each wavefront
+// navigates its 64 tracks of all of them in one go, so that a batch of queued pairs
+// holds U times as many, then the passes are differentiated one by one. They are U
+// >> log_each rows' first 1 << log_each passes, or one row's next U (log_each 2).
 template <bool HAS_OFFS, bool CULL, int KSET, bool TABLE, int U>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 4 : 1))) void k_nav_backward(
     const VolumeRec *__restrict__ vol, const DaughterRec *__restrict__ dau,
     const CullBlock *__restrict__ cul, TracksDev t, const double *__restrict__ offs,
     const double *__restrict__ gstep,
     const double *__restrict__ ghit, double *__restrict__ g_o, double *__restrict__ g_d,
-    double *__restrict__ partial, bool lds_acc) {
+    double *__restrict__ partial, bool lds_acc, int rows, int log_each) {
     __shared__ double s_g[3][kBlock];
     __shared__ NavScratch<U> scr[CULL ? kBlock / 64 : 1];
     // [3 nd] doubles of the row's accumulator when lds_acc, then 4 nd + nd + 1
@@ -737,16 +740,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 4
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int nd = vol->nd;
     const int nj = 3 * nd;
-    double *prow = partial ? partial + (size_t)blockIdx.x * nj : nullptr;
-    double *acc_row = lds_acc ? s_dyn : prow;  // each entry j is thread (j mod kBlock)'s alone
     int *s_bins = reinterpret_cast<int *>(s_dyn + (lds_acc ? nj : 0));
-    if (prow)
-        for (int j = tid; j < nj; j += kBlock) acc_row[j] = 0.0;
     const int64_t n = t.n;
-    for (int64_t pass = (int64_t)blockIdx.x * U; pass * kBlock < n;
-         pass += pass % U + 1 < U ? 1 : ((int64_t)gridDim.x - 1) * U + 1) {
-        const int u = (int)(pass % U);
-        const int64_t base = pass * kBlock;
+    const int npass = (int)((n + kBlock - 1) / kBlock);  // (n < 2^39)
+    // `u`: the pass's place among those navigated together
+    auto differentiate = [&](int pass, int u, double *acc_row) {
+        const int64_t base = (int64_t)pass * kBlock;
         const int64_t i = base + tid;
         int h = -2;
         double gdx = 0.0, gdy = 0.0, gdz = 0.0;
@@ -755,10 +754,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 4
             // compacted navigator
             const int64_t wbase = base + wave * 64;
             if (u == 0 && wbase < n) {
-                constexpr int most = (U - 1) * kBlock + 64;
-                const int cnt = n - wbase < most ? (int)(n - wbase) : most;
-                nav_compact_core<U, HAS_OFFS, false, KSET, true, true, TABLE, kBlock>(*vol, dau, cul, offs, t, wbase,
-                                                                                      cnt, scr[wave], lane);
+                // (a row's passes are `rows` passes apart)
+                const Rounds rounds = log_each == 0   ? Rounds{kBlock, 2 * kBlock}
+                                      : log_each == 1 ? Rounds{rows * kBlock, kBlock}
+                                                      : Rounds{rows * kBlock, 2 * rows * kBlock};
+                const int64_t most = (U == 1 ? 0 : rounds.at(U - 1)) + 64;
+                const int cnt = (int)(n - wbase < most ? n - wbase : most);
+                nav_compact_core<U, HAS_OFFS, false, KSET, true, true, TABLE, U == 1>(*vol, dau, cul, offs, t, wbase, cnt,
+                                                                                      scr[wave], lane, nullptr, rounds);
             }
         }
         if (i < n) {
@@ -829,7 +832,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 4
             gdy = -c * dsy;
             gdz = -c * dsz;
         }
-        if (prow) {
+        if (partial) {
             // Offset gradient of the workgroup's tracks per daughter: a
             // stable counting sort of the contributions by hit daughter,
             // then each (daughter, component) sums its run in track order,
@@ -894,9 +897,36 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 4
             }
             __syncthreads();
         }
+    };
+    // A row of partial sums starts at zero; each of its entries j is thread
+    // (j mod kBlock)'s alone.
+    auto start = [&](double *acc_row) {
+        if (partial)
+            for (int j = tid; j < nj; j += kBlock) acc_row[j] = 0.0;
+    };
+    auto finish = [&](int row) {
+        if (partial && lds_acc)
+            for (int j = tid; j < nj; j += kBlock) partial[(size_t)row * nj + j] = s_dyn[j];
+    };
+    auto acc_of = [&](int row) { return lds_acc || !partial ? s_dyn : partial + (size_t)row * nj; };
+    // U >> log_each rows of 1 << log_each passes, one after the other; or one row
+    // with all its passes
+    const bool whole = U == 1 || log_each == 2;
+    int row = (int)blockIdx.x * (whole ? 1 : U >> log_each);
+    double *acc_row = acc_of(row);
+    start(acc_row);
+    for (int pass = row, u = 0, q = 0;;) {
+        if (pass < npass) differentiate(pass, u, acc_row);
+        u = (u + 1) % U;
+        pass += rows;
+        if (whole ? pass < npass : ++q < 1 << log_each) continue;
+        finish(row);
+        if (whole || u == 0 || ++row >= rows) return;
+        acc_row = acc_of(row);
+        start(acc_row);
+        pass = row;
+        q = 0;
     }
-    if (prow && lds_acc)
-        for (int j = tid; j < nj; j += kBlock) prow[j] = acc_row[j];
 }
 
 // out[j] = sum over workgroups b of partial[b][j], in a fixed order.
@@ -919,40 +949,37 @@ __global__ __launch_bounds__(kBlock) void k_reduce_partials(const double *__rest
 constexpr int kBackwardLdsAcc = 256;
 
 template <bool CULL, int KSET, int U>
-static void launch_backward_variant(int nblocks, int nd, const VolumeRec *vol, const DaughterRec *dau,
+static void launch_backward_variant(int rows, int nd, const VolumeRec *vol, const DaughterRec *dau,
                                     const CullBlock *cul, const TracksDev &t, const double *offs, const double *gstep,
                                     const double *ghit, double *g_o, double *g_d, double *part,
                                     const CullBlock *shifted, hipStream_t st) {
     // the offset-gradient sort's counts and runs; the row's accumulator in
     // LDS up to kBackwardLdsAcc daughters (6 KB)
     const bool lds_acc = part && nd <= kBackwardLdsAcc;
+    const int64_t npass = (t.n + kBlock - 1) / kBlock;
+    if (!part && U > 1) rows = (int)npass;  // (no sums: the passes in order)
+    const int log_each = U == 1 || npass <= rows ? 0 : npass <= 2 * (int64_t)rows ? 1 : 2;
+    const int own = U >> log_each, nblocks = (rows + own - 1) / own;
     const size_t dyn = (lds_acc ? sizeof(double) * 3 * (size_t)nd : 0) + sizeof(int) * (size_t)(5 * nd + 1);
     if (offs && CULL && shifted)
         hipLaunchKernelGGL((k_nav_backward<true, CULL, KSET, CULL, U>), dim3(nblocks), dim3(kBlock), dyn, st, vol,
-                           dau, shifted, t, offs, gstep, ghit, g_o, g_d, part, lds_acc);
+                           dau, shifted, t, offs, gstep, ghit, g_o, g_d, part, lds_acc, rows, log_each);
     else if (offs)
         hipLaunchKernelGGL((k_nav_backward<true, CULL, KSET, false, U>), dim3(nblocks), dim3(kBlock), dyn, st, vol,
-                           dau, cul, t, offs, gstep, ghit, g_o, g_d, part, lds_acc);
+                           dau, cul, t, offs, gstep, ghit, g_o, g_d, part, lds_acc, rows, log_each);
     else
         hipLaunchKernelGGL((k_nav_backward<false, CULL, KSET, true, U>), dim3(nblocks), dim3(kBlock), dyn, st, vol,
-                           dau, cul, t, offs, gstep, ghit, g_o, g_d, part, lds_acc);
+                           dau, cul, t, offs, gstep, ghit, g_o, g_d, part, lds_acc, rows, log_each);
 }
 
 // Passes that a workgroup takes at a time: kBackwardRounds from the sizes on
 // at which the fuller batches gain more than the fewer workgroups lose, for
 // volumes of box, tube and cone, and sooner where a batch runs more kinds'
-// code. (us, one pass / four: toy detector 2^20 tracks 66.2 / 53.1, 800k 44.3 /
-// 45.2, 450k 32 / 34; every kind 2^20 118.8 / 72.4, 450k 58 / 48.5, 300k 47.8 /
-// 48.)
+// code. (us, one pass / four: toy detector 600k tracks 35.9 / 36.2, 2^20 50.1 / 46.1;
+// every kind 350k 47.2 / 47.2, 400k 50 / 48. Every daughter walked: one pass.)
 constexpr int kBackwardRounds = 4;
 static bool backward_wide(int64_t n, int kset) {
-    return n >= (kset == kSetBasic ? (int64_t)1 << 20 : (int64_t)7 << 16);
-}
-
-static int backward_blocks(int64_t n, int kset) {
-    const int64_t per = backward_wide(n, kset) ? (int64_t)kBlock * kBackwardRounds : kBlock;
-    const int64_t need = (n + per - 1) / per;
-    return (int)(need < kBackwardMaxBlocks ? (need > 0 ? need : 1) : kBackwardMaxBlocks);
+    return n >= (kset == kSetBasic ? (int64_t)5 << 17 : (int64_t)11 << 15);
 }
 
 hipError_t launch_backward(const VolumeRec *vol, const DaughterRec *dau_all, const DaughterRec *dau,
@@ -960,7 +987,7 @@ hipError_t launch_backward(const VolumeRec *vol, const DaughterRec *dau_all, con
                            const TracksDev &t, const double *offs, const double *gstep,
                            const double *ghit, double *g_o, double *g_d, double *partial,
                            double *g_off, bool cull, int kset, CullBlock *shift_buf, hipStream_t st) {
-    const int nblocks = backward_blocks(t.n, kset);
+    const int rows = backward_rows(t.n);
     double *part = (g_off && nd > 0) ? partial : nullptr;
     if (t.n > 0 || part) {
         const CullBlock *shifted = nullptr;
@@ -972,18 +999,17 @@ hipError_t launch_backward(const VolumeRec *vol, const DaughterRec *dau_all, con
         }
         const bool wide = backward_wide(t.n, kset);
 #define GN_BACKWARD(CULL, U) \
-    GN_KSET(kset, (launch_backward_variant<CULL, KS, U>(nblocks, nd, vol, dau, cul, t, offs, gstep, ghit, g_o, g_d, \
-                                                        part, CULL ? shifted : nullptr, st)))
+    GN_KSET(kset, (launch_backward_variant<CULL, KS, U>(rows, nd, vol, dau, cul, t, offs, gstep, ghit, g_o, g_d, \
+                                                        part, shifted, st)))
         if (cull && wide) GN_BACKWARD(true, kBackwardRounds);
         else if (cull) GN_BACKWARD(true, 1);
-        else if (wide) GN_BACKWARD(false, kBackwardRounds);
         else GN_BACKWARD(false, 1);
 #undef GN_BACKWARD
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     if (part) {
-        hipLaunchKernelGGL(k_reduce_partials, dim3(3 * nd), dim3(kBlock), 0, st, part, nblocks, 3 * nd,
+        hipLaunchKernelGGL(k_reduce_partials, dim3(3 * nd), dim3(kBlock), 0, st, part, rows, 3 * nd,
                            g_off);
         return hipGetLastError();
     }
