@@ -4,7 +4,6 @@
 // launch-shape autotuner and error reporting.
 #include <algorithm>
 #include <chrono>
-#include <cfloat>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -306,6 +305,60 @@ double mother_area(const geo_shape &s) {
     return 2 * M_PI * r * (r + h);
 }
 
+// Volume of the same.
+double mother_volume(const geo_shape &s) {
+    const double *p = s.par;
+    switch (s.kind) {
+        case GEO_BOX: return 8 * p[0] * p[1] * p[2];
+        case GEO_TUBE:
+        case GEO_TUBS: return 2 * M_PI * p[1] * p[1] * p[2];
+        case GEO_CONE:
+        case GEO_CONS: return 2 * M_PI * p[0] * std::max(p[2], p[4]) * std::max(p[2], p[4]);
+    }
+    const int nz = (int)p[2];
+    double r = 0;
+    for (int j = 0; j < nz; ++j) r = std::max(r, p[5 + 3 * j]);
+    return M_PI * r * r * (p[3 * nz] - p[3]);
+}
+
+// Daughters that one round of 64 points tests at little cost.
+constexpr int kRoundsFew = 11;
+
+// How the tasks on volume r cull: what a line or a point meets of the daughters
+// decides which tests and whether any.
+void choose_culling(VolumeRec &r, const DaughterRec *dau, const geo_shape &mother, bool basic) {
+    if (r.nd == 0) return;
+    // A line through a convex mother meets a sphere inside it with the ratio of
+    // their surfaces as probability, a point is in it with that of their volumes.
+    // The more of the daughters (ratios of the mean daughter) a track meets, the
+    // more pairs are queued, until walking all daughters in lockstep costs less.
+    // The lines are where two forms crossed, for boxes, tubes and cones and for
+    // more kinds (whose batches run more code), with 8, 32 and 64 daughters, 2^20
+    // tracks (us: matrix cores, FP64, lockstep):
+    //   navigator, 32 daughters, ratio 0.03  41  50 140; 0.06  73  66 140;
+    //                                  0.15 176 119 140; 0.20 229 149 140;
+    //     every kind             0.03 150 146 271; 0.06 296 219; 0.10 493 291 271;
+    //   localization, ratio of surfaces 0.06 16.7 22 41; 0.10 25 21.5; 0.20 57 36; 0.30 94 54 42;
+    //     every kind             0.06 38 39 71; 0.10 68 63; 0.15 112 85 73;
+    //     8 daughters 0.10 11.2 11.7, every kind 19.4 26;
+    //   safety (matrix cores, lockstep) 0.10 67 86; 0.20 85 86; 0.30 100 86;
+    //     every kind             0.01 133 228; 0.03 235 228; 0.06 ~285 228.
+    // The adjoint's lines are the navigator's.
+    double met = 0, held = 0;
+    for (int k = 0; k < r.nd; ++k) {
+        const double rk = dau[k].cull_r;
+        met += std::min(1.0, 4 * M_PI * rk * rk / mother_area(mother)) / r.nd;
+        held += std::min(1.0, 4 * M_PI / 3 * rk * rk * rk / mother_volume(mother)) / r.nd;
+    }
+    if (met > (basic ? 0.045 : 0.027)) r.exact |= kLineTasks;
+    if (held > (basic ? 0.034 : 0.026) * (r.nd > kRoundsFew ? 1 : 2)) r.exact |= kLocateTask;
+    r.rounds = r.nd > kRoundsFew || held * r.nd > 0.02;
+    if (met > (basic ? 0.16 : 0.08)) r.dense |= kLineTasks;
+    if (held > (basic ? 0.124 : 0.044)) r.dense |= kLocateTask;
+    if (met > (basic ? 0.17 : 0.04)) r.dense |= kSafetyTask;
+    if (met > 0.015) r.crowded = 1;
+}
+
 int check_rotation(const double *r, const char *what) {
     for (int i = 0; i < 9; ++i)
         if (!std::isfinite(r[i])) return fail(GEO_ERR_INVALID_ARG, "%s: non-finite rotation", what);
@@ -375,6 +428,7 @@ struct geo_geometry {
     int tracks_per_lane = 4;
     int waves_per_simd = 0;  // hardware-scheduled until geo_autotune picks
     bool use_graph = false;  // batched kernels as two launches until geo_autotune picks
+    bool any_tests = false;         // a volume has kAnyTests for its lines
     bool cull = true;               // wavefront bounding-sphere culling in the navigators
     // Basket lists are staged in a ring of mapped pinned host buffers that the
     // tile-expansion kernel reads directly (no copy node). The ring holds
@@ -433,14 +487,20 @@ void destroy_graph(geo_geometry *g) {
 constexpr int kBasketAll = 1, kBasketAllFew = 2, kSafetyAll = 4;
 constexpr int64_t kBasketFew = (int64_t)1 << 19;
 
-// Whether a call on n tracks of one volume culls.
-bool culls(const geo_geometry *g, int volume, int64_t n) {
-    return g->cull && (!g->h_vols[volume].dense || n <= kDenseFew);
+// How a call on n tracks of one volume culls.
+int tests(const geo_geometry *g, int volume, int64_t n, int task) {
+    const VolumeRec &v = g->h_vols[volume];
+    if (!g->cull) return kNoTests;
+    const int others = v.exact & task ? kAnyTests : kMatrixTests;
+    if (!(v.dense & task)) return others;
+    if (task == kLineTasks && n <= kFewLines) return kMatrixTests;
+    return n <= (task == kLineTasks ? kFewExact : kFewPoints) ? kAnyTests : kNoTests;
 }
-
-bool basket_culls(const geo_geometry *g, int volume, int64_t n) {
-    return culls(g, volume, n) && g->h_vols[volume].nd > (n < kBasketFew ? kBasketAllFew : kBasketAll);
+int basket_tests(const geo_geometry *g, int volume, int64_t n) {
+    const int nd = g->h_vols[volume].nd;
+    return nd <= (n < kBasketFew ? kBasketAllFew : kBasketAll) ? (int)kNoTests : tests(g, volume, n, kLineTasks);
 }
+int batched_tests(const geo_geometry *g) { return !g->cull ? kNoTests : g->any_tests ? kAnyTests : kMatrixTests; }
 
 const CullBlock *volume_blocks(const geo_geometry *g, int volume) {
     return g->d_cull ? g->d_cull + g->h_vols[volume].first_block : nullptr;
@@ -477,6 +537,7 @@ int geo_geometry_create(const geo_volume_desc *v, int32_t nvol, geo_geometry **o
     std::vector<VolumeRec> vols(nvol);
     std::vector<DaughterRec> dau;
     int nblocks = 0;  // culling blocks
+    bool any_tests = false;
     // polycone sections, and which record points at each: volume index
     // (mother) or -1 - daughter index
     std::vector<PconRec> pcons;
@@ -568,21 +629,8 @@ int geo_geometry_create(const geo_volume_desc *v, int32_t nvol, geo_geometry **o
         r.safe_q = (float)(safe_q < 0 ? -1.0 : safe_q * (1 + 1e-6) + 1e-6);
         r.near_r = (float)(back * (1 + 1e-6) + 1e-6);
         r.near_r2 = (float)(back * back + wide);
-        // A line through a convex mother meets a sphere inside it with the
-        // ratio of their surfaces as probability. Where that is a third of
-        // the daughters or more, walking all of them in lockstep costs less
-        // than queueing the pairs that pass: about 150 VALU instructions per
-        // 64 tracks and daughter, against 260 for the tests and 450 per 64
-        // pairs run in batches of mixed kinds. (The paper's toy detector,
-        // whose 8 daughters meet 4.3 lines in the mean: 132 against 216 us
-        // at 2^22 tracks; the toy detector of 32, 0.14 in the mean: 52
-        // against 510.)
-        double met = 0.0;
-        for (int k = 0; k < r.nd; ++k) {
-            const double rk = dau[(size_t)r.first + k].cull_r;
-            met += std::min(1.0, 4 * M_PI * rk * rk / mother_area(d.mother));
-        }
-        r.dense = r.nd > 0 && 3.0 * met >= r.nd;
+        choose_culling(r, dau.data() + r.first, d.mother, vol_kset[iv] == kSetBasic);
+        any_tests |= ((r.exact | r.dense) & kLineTasks) != 0;
         r.first_block = nblocks;
         nblocks += (r.nd + kCullBlock - 1) / kCullBlock;
     }
@@ -601,6 +649,7 @@ int geo_geometry_create(const geo_volume_desc *v, int32_t nvol, geo_geometry **o
     g->device_name = prop.gcnArchName;
     g->nvol = nvol;
     g->max_nd = max_nd;
+    g->any_tests = any_tests;
     g->h_vols = vols;
     g->vol_kset = vol_kset;
     g->kset = *std::max_element(vol_kset.begin(), vol_kset.end());
@@ -705,7 +754,7 @@ int geo_navigate_basket(const geo_geometry *g, int32_t volume, geo_tracks t, con
     hipError_t e = launch_nav_basket(g->d_vols + volume, g->d_dau ? g->d_dau + first : nullptr,
                                      volume_blocks(g, volume), to_dev(t),
                                      g->h_vols[volume].nd > 0 ? offsets : nullptr, step, hit, hitpt,
-                                     basket_culls(g, volume, t.n),
+                                     basket_tests(g, volume, t.n),
                                      g->vol_kset[volume], stream);
     if (e != hipSuccess) return hip_fail(e, "navigator launch");
     return GEO_OK;
@@ -729,7 +778,7 @@ int geo_navigate_backward(const geo_geometry *g, int32_t volume, geo_tracks t, c
     hipError_t e = launch_backward(g->d_vols + volume, g->d_dau, g->d_dau ? g->d_dau + first : nullptr,
                                    volume_blocks(g, volume), nd, to_dev(t),
                                    nd > 0 ? offsets : nullptr, gstep, ghit, g_o, g_d, g->d_partial,
-                                   nd > 0 ? g_off : nullptr, culls(g, volume, t.n), g->vol_kset[volume], g->d_shift, stream);
+                                   nd > 0 ? g_off : nullptr, tests(g, volume, t.n, kLineTasks), g->vol_kset[volume], g->d_shift, stream);
     if (e != hipSuccess) return hip_fail(e, "adjoint launch");
     return GEO_OK;
 }
@@ -763,7 +812,7 @@ int geo_navigate_backward_noalloc(const geo_geometry *g, int32_t volume, geo_tra
     hipError_t e = launch_backward(g->d_vols + volume, g->d_dau, g->d_dau ? g->d_dau + first : nullptr,
                                    volume_blocks(g, volume), nd, to_dev(t),
                                    nd > 0 ? offsets : nullptr, gstep, ghit, g_o, g_d, part,
-                                   nd > 0 ? g_off : nullptr, culls(g, volume, t.n), g->vol_kset[volume], nullptr, stream);
+                                   nd > 0 ? g_off : nullptr, tests(g, volume, t.n, kLineTasks), g->vol_kset[volume], nullptr, stream);
     if (e != hipSuccess) return hip_fail(e, "adjoint launch");
     return GEO_OK;
 }
@@ -791,7 +840,7 @@ int geo_navigate_safety(const geo_geometry *g, int32_t volume, geo_tracks t, con
     hipError_t e = launch_nav_safety(g->d_vols + volume, g->d_dau ? g->d_dau + first : nullptr,
                                      volume_blocks(g, volume), g->h_vols[volume].nd, to_dev(t),
                                      g->h_vols[volume].nd > 0 ? offsets : nullptr, safety,
-                                     culls(g, volume, t.n) && g->h_vols[volume].nd > kSafetyAll,
+                                     g->h_vols[volume].nd > kSafetyAll ? tests(g, volume, t.n, kSafetyTask) : (int)kNoTests,
                                      g->vol_kset[volume], stream);
     if (e != hipSuccess) return hip_fail(e, "safety launch");
     return GEO_OK;
@@ -803,8 +852,8 @@ int geo_locate(const geo_geometry *g, int32_t volume, geo_tracks t, const double
     if (rc || t.n == 0) return rc;
     const int first = g->h_vols[volume].first;
     hipError_t e = launch_nav_locate(g->d_vols + volume, g->d_dau ? g->d_dau + first : nullptr,
-                                     volume_blocks(g, volume), g->h_vols[volume].nd, to_dev(t),
-                                     g->h_vols[volume].nd > 0 ? offsets : nullptr, where, culls(g, volume, t.n),
+                                     volume_blocks(g, volume), g->h_vols[volume].rounds != 0, to_dev(t),
+                                     g->h_vols[volume].nd > 0 ? offsets : nullptr, where, tests(g, volume, t.n, kLocateTask),
                                      g->vol_kset[volume], stream);
     if (e != hipSuccess) return hip_fail(e, "locate launch");
     return GEO_OK;
@@ -946,7 +995,7 @@ int launch_batched(geo_geometry *g, const geo_basket *b, int32_t nb, const geo_t
         GN_HIP(hipLaunchKernel(build_tiles_kernel(), dim3(kBuildTilesBlocks), dim3(kBlock), bargs, 0, stream));
         const bool kt = g->ktime && !census;
         if (kt) GN_HIP(hipEventRecord(g->kt_before, stream));
-        GN_HIP(hipLaunchKernel(batched_kernel(U, g->cull, persistent, census != nullptr, g->kset), dim3(grid),
+        GN_HIP(hipLaunchKernel(batched_kernel(U, batched_tests(g), persistent, census != nullptr, g->kset), dim3(grid),
                                dim3(kBlock), pargs, 0, stream));
         if (kt) {
             GN_HIP(hipEventRecord(g->kt_after, stream));
@@ -960,7 +1009,7 @@ int launch_batched(geo_geometry *g, const geo_basket *b, int32_t nb, const geo_t
     kb.blockDim = dim3(kBlock);
     kb.kernelParams = bargs;
     hipKernelNodeParams kn = {};
-    kn.func = const_cast<void *>(batched_kernel(U, g->cull, persistent, false, g->kset));
+    kn.func = const_cast<void *>(batched_kernel(U, batched_tests(g), persistent, false, g->kset));
     kn.gridDim = dim3(grid);
     kn.blockDim = dim3(kBlock);
     kn.kernelParams = pargs;

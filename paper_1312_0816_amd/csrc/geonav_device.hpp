@@ -84,26 +84,34 @@ struct alignas(16) DaughterRec {
 };
 static_assert(sizeof(DaughterRec) == 368, "DaughterRec layout");
 
-// Tracks up to which a dense volume (VolumeRec.dense) is culled all the same:
-// their pairs fill one or two batches, and each daughter walked in lockstep
-// would be a step of a serial chain for the few lanes. (The paper's toy
-// detector, 8 daughters, us per call of 8, 16, 24, 32, 64 tracks: navigator in
-// lockstep 7.2 7.3 7.3 7.3 7.1, culled 5.0 6.4 6.7 7.6 11.1; adjoint 8.7 and 6.4
-// 7.9 8.1 9.1 12.6; safety 5.4 and 4.2 4.6 4.6 5.2 6.8.)
-constexpr int kDenseFew = 24;
+// Tasks of few tracks on a volume that is walked in lockstep (VolumeRec.dense) are
+// culled all the same: each daughter in lockstep would be a step of a serial
+// chain for the few lanes. Lines up to kFewLines tracks by the tests on the matrix
+// cores, up to kFewExact by those in FP64 (whose pairs come daughter by
+// daughter); points up to kFewPoints by those in FP64. (The paper's toy detector,
+// 8 daughters, us per call. Navigator of 16, 20, 24, 32, 48 tracks: matrix cores 4.7
+// 6.4 6.6 7.5 9; FP64 4.9 6.0 6.4 6.6 7.7; lockstep 7.0 throughout. Safety of 16, 24,
+// 32, 48: 3.8 4.4 5.2 6; 3.5 4.2 4.6 5.0; lockstep 5.2.)
+constexpr int kFewLines = 16, kFewExact = 40, kFewPoints = 48;
 
-// Culling block: the daughters' operand of the culling tests, which run on
-// the matrix cores (see "Culling" below), for up to kCullBlock daughters of a
-// volume: 8 half-precision entries of each wavefront lane, in the layout of
-// the A operand of a 32 x 32 x 16 product. Written by cull_operand.
+// Culling block: the daughters' operands of the culling tests, for up to
+// kCullBlock daughters of a volume. The tests run on the matrix cores (see
+// "Culling" below): 8 half-precision entries of each wavefront lane, in the layout
+// of the A operand of a 32 x 32 x 16 product (a); or in FP64 (see exact_row).
 constexpr int kCullBlock = 32;
 // the mother's bounding radius in the tests' units, the largest coordinate of
 // a daughter's centre they take, and a constant beyond every product
 constexpr float kCullR = 256.0f, kCullMax = 512.0f, kCullFar = 3.8e6f;
 struct alignas(16) CullBlock {
     unsigned int a[64][4];
+    double exact[kCullBlock][4];
 };
-static_assert(sizeof(CullBlock) == 1024, "CullBlock layout");
+static_assert(sizeof(CullBlock) == 2048, "CullBlock layout");
+
+// How a kernel culls: not at all; by the tests on the matrix cores; or as the volume
+// asks (VolumeRec.exact): those kernels hold both forms, and what they add would
+// cost the others registers.
+enum : int { kNoTests = 0, kMatrixTests = 1, kAnyTests = 2 };
 
 struct alignas(16) VolumeRec {
     ShapeRec mother;
@@ -117,7 +125,10 @@ struct alignas(16) VolumeRec {
     double cull_s;
     float cull_back;
     int32_t first_block;  // index of the volume's first culling block
-    int32_t dense;        // most lines meet most culling spheres: culled up to kDenseFew tracks only
+    int32_t exact;        // the tasks that take the tests in FP64
+    int32_t dense;        // the tasks that walk all daughters in lockstep
+    int32_t crowded;      // the safety queues its pairs daughter by daughter
+    int32_t rounds;       // large localizations take several rounds per wavefront
     // the safety's bound from the nearest culling sphere (see the compacted
     // safety), in the tests' units: of the daughters whose Safety at distance
     // |w| > r is at most sqrt(|w|^2 + c), the largest r^2 + c; of the others,
@@ -127,7 +138,8 @@ struct alignas(16) VolumeRec {
     // of its daughter is at most |w| + r)
     float near_r, near_r2;
 };
-static_assert(sizeof(VolumeRec) == 304, "VolumeRec layout");
+static_assert(sizeof(VolumeRec) == 320, "VolumeRec layout");
+enum : int32_t { kLineTasks = 1, kLocateTask = 2, kSafetyTask = 4 };  // of VolumeRec.exact and dense
 
 struct TracksDev {
     const double *x, *y, *z, *ux, *uy, *uz;
@@ -222,7 +234,8 @@ __device__ __forceinline__ double root_up(double A, double B, double C, double s
 // +-(a few ulps of B^2), whose square root would move both roots by about
 // sqrt(eps) t0. Within kSnap B^2 of zero the discriminant is taken as 0, and
 // the formulas above then give t0 = C / (-B) = -B / A to rounding.
-constexpr double kSnap = 64.0 * 2.220446049250313e-16;
+constexpr double kEps = 2.220446049250313e-16;  // of doubles
+constexpr double kSnap = 64.0 * kEps;
 __device__ __forceinline__ double disc_sqrt(double disc, double B) {
     return disc > kSnap * (B * B) ? fsqrt(disc) : 0.0;
 }
@@ -1196,6 +1209,7 @@ __device__ __forceinline__ void nav_track(const VolumeRec &v, const DaughterRec 
 // of the queue and the minima is the wavefront's own, whose LDS instructions
 // execute in program order, so no barrier is needed.
 constexpr int kQueueCap = 64;
+constexpr int kListCap = 256;  // pairs of a round, 64 for each of the four daughters tested together at least
 template <int U>
 struct NavScratch {
     unsigned long long key[U * 64];   // running minimum per track: key of the step
@@ -1521,8 +1535,9 @@ __device__ __forceinline__ void cull_tracks(const VolumeRec &v, double x, double
     const float px = fmaf(back, ex, (float)(x * s));
     const float py = fmaf(back, ey, (float)(y * s));
     const float pz = fmaf(back, ez, (float)(z * s));
+    const float pp = fmaf(pz, pz, fmaf(py, py, px * px));
     CullVector split;
-    cull_columns(px, py, pz, fmaf(pz, pz, fmaf(py, py, px * px)), 0x54005400u, split, c.p);
+    cull_columns(px, py, pz, pp, 0x54005400u, split, c.p);
     cull_columns(0.5f * ex, 0.5f * ey, 0.5f * ez, fmaf(pz, ez, fmaf(py, ey, px * ex)), 0u, split, c.e);
 }
 
@@ -1595,14 +1610,12 @@ struct Rounds {
 //
 // With TILE the rounds follow one another; else round u starts rounds.at(u)
 // tracks past base, and `count` counts the tracks from base on.
-template <int U, bool HAS_OFFS, bool COUNT, int KSET, bool SURF = true, bool FINAL = true, bool TABLE = !HAS_OFFS,
-          bool TILE = true>
+template <int U, bool HAS_OFFS, bool COUNT, int KSET, bool SURF, bool FINAL, bool TABLE, bool TILE>
 __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const DaughterRec *__restrict__ dau,
                                                 const CullBlock *__restrict__ cul,
                                                 const double *__restrict__ offs, const TracksDev &t,
-                                                int64_t base, int count, NavScratch<U> &S, int lane,
-                                                unsigned long long *census = nullptr,
-                                                const Rounds &rounds = Rounds{0, 0}) {
+                                                int64_t base, int count, const Rounds &rounds, NavScratch<U> &S,
+                                                int lane, unsigned long long *census) {
     int qn = 0;  // queue length (uniform)
     const int nd = v.nd;
     const TileTracks tt = tile_tracks(t, base);
@@ -1697,6 +1710,224 @@ __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const Daught
     return qn;
 }
 
+// ------------------------------------------------- culling in FP64
+// Row of daughter k: its centre T (moved by the offset) and the threshold of
+// the expanded test, which evaluates the squared distance from T to the
+// half-line less |T|^2 as |p|^2 - 2 p.T - b^2, b = min((p - T).e, 0): every term is
+// at most (|p| + |T|)^2, so its rounding is below 16 eps (2 R + 2 |T|)^2 for a
+// start inside the mother (R its bounding radius).
+template <bool HAS_OFFS>
+__device__ __forceinline__ void exact_row(const VolumeRec &v, const DaughterRec *__restrict__ dau,
+                                          const double *__restrict__ offs, int k, double *row) {
+    if (k >= v.nd) {  // never passes
+        row[0] = row[1] = row[2] = 0.0;
+        row[3] = -__builtin_inf();
+        return;
+    }
+    const DaughterRec &D = dau[k];
+    double cx = D.tr[0], cy = D.tr[1], cz = D.tr[2];
+    if (HAS_OFFS) {
+        cx += offs[3 * k + 0];
+        cy += offs[3 * k + 1];
+        cz += offs[3 * k + 2];
+    }
+    const double tt = fma(cz, cz, fma(cy, cy, cx * cx));
+    const double span = fma(2.0, fsqrt(tt), 3.0 * v.bound_r);
+    row[0] = cx;
+    row[1] = cy;
+    row[2] = cz;
+    row[3] = fma(64.0 * kEps * span, span, fma(D.cull_r, D.cull_r, -tt));
+}
+
+// What the tests take of a track: e = d / |d| (0 for a zero direction, or one whose
+// |d|^2 overflows: the start point is tested), p.e, |p|^2 and -2 p.
+struct ExactTrack {
+    double ex, ey, ez, pe, pp, mx, my, mz;
+};
+__device__ __forceinline__ ExactTrack exact_track(double x, double y, double z, double ux, double uy, double uz) {
+    ExactTrack t;
+    const double dd = fma(uz, uz, fma(uy, uy, ux * ux));
+    const double il = (dd > 0.0 && dd < __builtin_inf()) ? rsqrt_fine(dd) : 0.0;
+    t.ex = ux * il;
+    t.ey = uy * il;
+    t.ez = uz * il;
+    t.pe = fma(z, t.ez, fma(y, t.ey, x * t.ex));
+    t.pp = fma(z, z, fma(y, y, x * x));
+    t.mx = -2.0 * x;
+    t.my = -2.0 * y;
+    t.mz = -2.0 * z;
+    return t;
+}
+
+// The lanes that pass daughters g to g + 3: a track's half-line meets the culling
+// sphere (kLineTests), it holds the point (kHoldTests), or comes nearer to it than
+// `reach` (kNearTests). A lane that is left out has |p|^2 = inf and passes none.
+// The rows are loaded together (scalar loads), the four tests independent.
+// Without TABLE w = p - T - offset is formed explicitly, as the evaluation forms it.
+enum : int { kLineTests, kHoldTests, kNearTests };
+template <int WHAT, bool HAS_OFFS, bool TABLE>
+__device__ __forceinline__ void exact_tests(const ExactTrack &t, const CullBlock *__restrict__ cul,
+                                            const DaughterRec *__restrict__ dau, const double *__restrict__ offs,
+                                            int g, int nd, double x, double y, double z, double reach,
+                                            unsigned long long (&pass)[4]) {
+    double r[4][5], o[4][3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int k = g + i < nd ? g + i : 0;
+        if (TABLE) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) r[i][c] = cul[g / kCullBlock].exact[g % kCullBlock + i][c];
+            if (WHAT == kNearTests) r[i][4] = dau[k].cull_r;
+        } else {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                r[i][c] = dau[k].tr[c];
+                o[i][c] = HAS_OFFS ? offs[3 * k + c] : 0.0;
+            }
+            r[i][3] = dau[k].cull_r;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        double f, b = 0.0, lim;
+        if (TABLE) {
+            f = fma(r[i][2], t.mz, fma(r[i][1], t.my, fma(r[i][0], t.mx, t.pp)));
+            if (WHAT == kLineTests) b = fma(-r[i][2], t.ez, fma(-r[i][1], t.ey, fma(-r[i][0], t.ex, t.pe)));
+            // (|w| < reach + r: r^2 and the shift are in the row)
+            lim = WHAT == kNearTests ? fma(r[i][4], 2.0 * reach, r[i][3]) + reach * reach : r[i][3];
+        } else {
+            const double wx = x - r[i][0] - o[i][0], wy = y - r[i][1] - o[i][1], wz = z - r[i][2] - o[i][2];
+            f = fma(wz, wz, fma(wy, wy, wx * wx));
+            if (WHAT == kLineTests) b = fma(wz, t.ez, fma(wy, t.ey, wx * t.ex));
+            lim = WHAT == kNearTests ? r[i][3] + reach : r[i][3];
+            lim = fma(lim, lim, 64.0 * kEps * f);
+        }
+        if (WHAT == kLineTests) {
+            b = fmin(b, 0.0);
+            f = fma(-b, b, f);
+        }
+        pass[i] = __builtin_amdgcn_ballot_w64(TABLE ? f <= lim : f <= lim && t.pp < __builtin_inf());
+        if (!TABLE && g + i >= nd) pass[i] = 0ull;
+    }
+}
+
+// The navigator of nav_compact_core with these tests, four daughters at a time,
+// for volumes with many pairs per track. A round's pairs go into a list
+// ((daughter << 6) | lane), daughter by daughter, and from there to the queue with
+// their tracks, which are read again (just read: cache hits): a batch then holds
+// few daughters, whose records its lanes share, and runs few kinds' code. (The
+// queue of nav_compact_core takes each lane's lowest daughter, which fills it in
+// fewer steps but mixes the daughters, and its moved starts let large spheres
+// behind a start pass. 32 daughters whose spheres meet 3, 10, 20 % of the lines, 2^20
+// tracks, nav_compact_core / here: boxes, tubes and cones 41 / 50, 117 / 89, 229 / 149
+// us; every kind 150 / 146, 493 / 291, 975 / 431.) What is left of the list at the end
+// of a round stays queued.
+template <int U, bool HAS_OFFS, bool COUNT, int KSET, bool SURF, bool FINAL, bool TABLE, bool TILE>
+__device__ __forceinline__ int nav_exact_core(const VolumeRec &v, const DaughterRec *__restrict__ dau,
+                                              const CullBlock *__restrict__ cul, const double *__restrict__ offs,
+                                              const TracksDev &t, int64_t base, int count, const Rounds &rounds,
+                                              NavScratch<U> &S, unsigned short *list, int lane,
+                                              unsigned long long *census) {
+    int qn = 0;  // queue length (uniform)
+    const int nd = v.nd;
+    const TileTracks tt = tile_tracks(t, base);
+    auto load = [&](int j, int u) -> Track {  // (a lane past the end: the last track)
+        const int at = TILE ? j : rounds.at(u) + (j & 63);
+        const unsigned int ju = (unsigned int)(at < count ? at : count - 1);
+        return Track{at32(tt.x, ju), at32(tt.y, ju), at32(tt.z, ju), at32(tt.ux, ju), at32(tt.uy, ju), at32(tt.uz, ju)};
+    };
+#pragma unroll 1
+    for (int u = 0; u < U; ++u) {
+        const int start = TILE ? u * 64 : rounds.at(u);
+        if (start >= count) continue;
+        const int j = u * 64 + lane;
+        const bool act = start + lane < count;
+        Track p = load(j, u);
+        int sid;
+        const double ms = mother_step<SURF, KSET>(v, p.x, p.y, p.z, p.ux, p.uy, p.uz, sid);
+        lds_store(&S.key[j], mother_key(ms));
+        lds_store(&S.hit[j], hit_pack(-1, sid));
+        if (COUNT) {
+            const int n = __popcll(__builtin_amdgcn_ballot_w64(act));
+            if (lane == 0) {
+                atomicAdd(&census[kCensusTracks], (unsigned long long)n);
+                atomicAdd(&census[kCensusCull], (unsigned long long)n * (unsigned long long)nd);
+            }
+        }
+        const bool on = act && ms > 0.0;
+        if (__builtin_amdgcn_ballot_w64(on) == 0ull) continue;
+        auto constants = [&]() {
+            ExactTrack c = exact_track(p.x, p.y, p.z, p.ux, p.uy, p.uz);
+            if (!on) c.pp = __builtin_inf();
+            return c;
+        };
+        ExactTrack c = constants();
+        int ln = 0;  // pairs in the list
+        for (int g = 0;; g += 4) {
+            unsigned long long pass[4] = {0ull, 0ull, 0ull, 0ull};
+            int more = 0;
+            if (g < nd) {
+                exact_tests<kLineTests, HAS_OFFS, TABLE>(c, cul, dau, offs, g, nd, p.x, p.y, p.z, 0.0, pass);
+                if (((pass[0] | pass[1]) | (pass[2] | pass[3])) == 0ull) continue;
+                more = __popcll(pass[0]) + __popcll(pass[1]) + __popcll(pass[2]) + __popcll(pass[3]);
+            }
+            if (g >= nd || ln + more > kListCap) {
+                for (int lt = 0; lt < ln;) {
+                    const int n = ln - lt < kQueueCap - qn ? ln - lt : kQueueCap - qn;
+                    if (lane >= qn && lane < qn + n) {
+                        const unsigned int e = list[lt + lane - qn];
+                        const int je = u * 64 + (int)(e & 63u);
+                        const Track q = load(je, u);
+                        S.pair[lane] = ((e >> 6) << 10) | (unsigned int)je;
+                        S.x[lane] = q.x;
+                        S.y[lane] = q.y;
+                        S.z[lane] = q.z;
+                        S.ux[lane] = q.ux;
+                        S.uy[lane] = q.uy;
+                        S.uz[lane] = q.uz;
+                    }
+                    qn += n;
+                    lt += n;
+                    if (qn == kQueueCap) {
+                        nav_batch<U, HAS_OFFS, COUNT, KSET, SURF>(dau, offs, S, kQueueCap, lane, census);
+                        qn = 0;
+                    }
+                }
+                ln = 0;
+                if (g >= nd) break;
+                int again = j;
+                asm volatile("" : "+v"(again));  // (see nav_compact_core)
+                p = load(again, u);
+                c = constants();
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (__builtin_amdgcn_inverse_ballot_w64(pass[i]))
+                    list[ln + lanes_below(pass[i])] = (unsigned short)(((g + i) << 6) | lane);
+                ln += __popcll(pass[i]);
+            }
+        }
+    }
+    if (FINAL && qn > 0) nav_batch<U, HAS_OFFS, COUNT, KSET, SURF>(dau, offs, S, qn, lane, census);
+    return qn;
+}
+
+// The form that TESTS (kMatrixTests or kAnyTests) and the volume call for; `exact`:
+// in FP64, with kAnyTests.
+template <int U, bool HAS_OFFS, bool COUNT, int KSET, int TESTS, bool SURF = true, bool FINAL = true,
+          bool TABLE = !HAS_OFFS, bool TILE = true>
+__device__ __forceinline__ int nav_core(const VolumeRec &v, const DaughterRec *__restrict__ dau,
+                                        const CullBlock *__restrict__ cul, const double *__restrict__ offs,
+                                        const TracksDev &t, int64_t base, int count, NavScratch<U> &S,
+                                        unsigned short *list, bool exact, int lane,
+                                        unsigned long long *census = nullptr, const Rounds &rounds = Rounds{0, 0}) {
+    if (TESTS == kAnyTests && exact)
+        return nav_exact_core<U, HAS_OFFS, COUNT, KSET, SURF, FINAL, TABLE, TILE>(v, dau, cul, offs, t, base, count,
+                                                                                 rounds, S, list, lane, census);
+    return nav_compact_core<U, HAS_OFFS, COUNT, KSET, SURF, FINAL, TABLE, TILE>(v, dau, cul, offs, t, base, count,
+                                                                               rounds, S, lane, census);
+}
+
 // Writes step, hit and (when HITPT) the hit point of the tile's tracks
 // from their running minima.
 template <int U, bool HITPT>
@@ -1723,15 +1954,15 @@ __device__ __forceinline__ void nav_write(const NavScratch<U> &S, const TracksDe
 }
 
 // The navigator of one wavefront's tile, writing its outputs.
-template <int U, bool HAS_OFFS, bool HITPT, bool COUNT, int KSET>
+template <int U, bool HAS_OFFS, bool HITPT, bool COUNT, int KSET, int TESTS>
 __device__ __forceinline__ void nav_compact(const VolumeRec &v, const DaughterRec *__restrict__ dau,
                                             const CullBlock *__restrict__ cul,
                                             const double *__restrict__ offs, const TracksDev &t,
-                                            int64_t base, int count, NavScratch<U> &S, int lane,
-                                            double *__restrict__ step, int32_t *__restrict__ hit,
+                                            int64_t base, int count, NavScratch<U> &S, unsigned short *list,
+                                            bool exact, int lane, double *__restrict__ step, int32_t *__restrict__ hit,
                                             double *__restrict__ hitpt,
                                             unsigned long long *census = nullptr) {
-    nav_compact_core<U, HAS_OFFS, COUNT, KSET, false>(v, dau, cul, offs, t, base, count, S, lane, census);
+    nav_core<U, HAS_OFFS, COUNT, KSET, TESTS, false>(v, dau, cul, offs, t, base, count, S, list, exact, lane, census);
     nav_write<U, HITPT>(S, t, base, count, lane, step, hit, hitpt);
 }
 
@@ -1851,18 +2082,18 @@ __device__ __forceinline__ void pool_flush(const DaughterRec *__restrict__ dau_a
 // The navigator of the W tiles of a workgroup (wavefront `wave` holds
 // `count` tracks from `base` of volume v (culling blocks `cul`); count may be 0, the wavefront then only taking part in the pooled flush),
 // the last flush pooled over the workgroup when `shared`.
-template <int U, int W, bool HAS_OFFS, bool HITPT, int KSET>
+template <int U, int W, bool HAS_OFFS, bool HITPT, int KSET, int TESTS>
 __device__ __forceinline__ void nav_compact_pooled(const VolumeRec &v, const DaughterRec *__restrict__ dau_all,
                                                    const CullBlock *__restrict__ cul, int first,
                                                    const double *__restrict__ offs, const TracksDev &t,
                                                    int64_t base, int count, NavScratch<U> *scr,
-                                                   PoolInfo<W> &P, bool shared, int wave, int lane,
+                                                   unsigned short *list, PoolInfo<W> &P, bool shared, int wave, int lane,
                                                    double *__restrict__ step, int32_t *__restrict__ hit,
                                                    double *__restrict__ hitpt) {
     int qn = 0;
     if (count > 0)
-        qn = nav_compact_core<U, HAS_OFFS, false, KSET, false, false>(v, dau_all + first, cul, offs, t, base,
-                                                                     count, scr[wave], lane);
+        qn = nav_core<U, HAS_OFFS, false, KSET, TESTS, false, false>(v, dau_all + first, cul, offs, t, base, count,
+                                                                    scr[wave], list, (v.exact & kLineTasks) != 0, lane);
     pool_flush<U, W, HAS_OFFS, KSET, false>(dau_all, offs, scr, P, shared, wave, first, qn, lane);
     nav_write<U, HITPT>(scr[wave], t, base, count, lane, step, hit, hitpt);
 }
@@ -2107,12 +2338,11 @@ template <int MODE, typename Operand>
 __device__ __forceinline__ void point_tests(const VolumeRec &v, double x, double y, double z, double reach,
                                             const uint4v &a, Operand operand, float &f, PointTests &T) {
     const int nd = v.nd;
-    const double s = v.cull_s;
-    const float px = (float)(x * s), py = (float)(y * s), pz = (float)(z * s);
+    const float px = (float)(x * v.cull_s), py = (float)(y * v.cull_s), pz = (float)(z * v.cull_s);
     const float pp = fmaf(pz, pz, fmaf(py, py, px * px));
     CullVector split;
     cull_columns(px, py, pz, pp, 0x54005400u, split, T.col);
-    f = MODE == 0 ? (float)(reach * s) : 0.0f;
+    f = MODE == 0 ? (float)(reach * v.cull_s) : 0.0f;
     if (MODE == 0 && nd >= kNearest) {
         int g[2] = {0x7f000000, 0x7f000000};  // as integers: any negative result stays the smallest
         uint4v b = a;
@@ -2174,6 +2404,7 @@ __device__ __forceinline__ void safety_compact(const VolumeRec &v, const Daughte
     const double reach = any_safety<KSET>(v.mother, v.pcon, x, y, z);
     lds_store(&S.key[lane], step_key(reach));
     int qn = 0;
+    bool by_daughter = POOL && v.crowded;
     Records::ready();
     if (nd > 0 && count > 0) {
         PointTests T;
@@ -2183,19 +2414,41 @@ __device__ __forceinline__ void safety_compact(const VolumeRec &v, const Daughte
             unsigned int m = point_mask(a, T, nd - k0);
             if (!act) m = 0u;
             if (k0 + kCullBlock < nd) a = operand(k0 + kCullBlock);
-            for (;;) {  // each lane with a daughter left appends its lowest
-                const unsigned long long more = __builtin_amdgcn_ballot_w64(m != 0u);
-                if (more == 0ull) break;
+            // each lane with a daughter left appends its lowest; in a crowded
+            // volume, and where the queue will be too long to be pooled, the
+            // lanes with the lowest lane's do: a batch then holds few daughters
+            // (a lane's pairs are counted up to four). Every kind, 2^20 points:
+            // 32 daughters whose spheres meet 3 % of the lines 365 to 234 us, in
+            // a mother 30 times the detector's size 660 to 329.
+            if (POOL) {
+                const int c = __popc(m);
+                int n = qn;
+#pragma unroll
+                for (int q = 1; q <= 4; ++q) n += __popcll(__builtin_amdgcn_ballot_w64(c >= q));
+                by_daughter = by_daughter || n > kPointPool;
+            }
+            for (;;) {
+                unsigned long long now = __builtin_amdgcn_ballot_w64(m != 0u);
+                if (now == 0ull) break;
                 if (qn > kPointQueue - 64) {
                     point_flush<HAS_OFFS, KSET>(recs, offs, S, qn, lane);
                     qn = 0;
                 }
-                if (m != 0u) {
-                    const int k = k0 + __builtin_ctz(m);
-                    S.queue[qn + lanes_below(more)] = ((unsigned int)k << 10) | (unsigned int)lane;
+                if (POOL && by_daughter) {
+                    const unsigned int bit =
+                        (unsigned int)__builtin_amdgcn_readlane((int)(m & (0u - m)), __ffsll((long long)now) - 1);
+                    now = __builtin_amdgcn_ballot_w64((m & bit) != 0u);
+                    if ((m & bit) != 0u)
+                        S.queue[qn + lanes_below(now)] =
+                            ((unsigned int)(k0 + __builtin_ctz(bit)) << 10) | (unsigned int)lane;
+                    m &= ~bit;
+                } else {
+                    if (m != 0u)
+                        S.queue[qn + lanes_below(now)] =
+                            ((unsigned int)(k0 + __builtin_ctz(m)) << 10) | (unsigned int)lane;
                     m &= m - 1u;
                 }
-                qn += __popcll(more);
+                qn += __popcll(now);
             }
         }
     }
@@ -2314,6 +2567,88 @@ __device__ __forceinline__ void locate_compact(const VolumeRec &v, const Daughte
             const int w = lds_load(&S.hit[j]);
             at32(out + base, (unsigned int)j) = w != 0x7fffffff ? w : -1;
         }
+    }
+}
+
+// Both with the tests in FP64, one round of 64 points per wavefront: the pairs are
+// listed daughter by daughter and read their points from the wavefront's copy.
+struct ExactPoints {
+    unsigned long long key[64];       // the safety's running minima, or
+    int hit[64];                      // the localization's (see LocateScratch)
+    unsigned int list[2 * kListCap];  // (daughter << 6) | point
+    double x[64], y[64], z[64];
+};
+template <bool SAFETY, bool HAS_OFFS, int KSET, typename Out>
+__device__ __forceinline__ void points_exact(const VolumeRec &v, const DaughterRec *__restrict__ dau,
+                                             const CullBlock *__restrict__ cul, const double *__restrict__ offs,
+                                             const TracksDev &t, int64_t base, int count, ExactPoints &S, int lane,
+                                             Out *__restrict__ out) {
+    const int nd = v.nd;
+    const bool act = lane < count;
+    const int64_t i = base + (act ? lane : 0);
+    const double x = t.x[i], y = t.y[i], z = t.z[i];
+    lds_store(&S.x[lane], x);
+    lds_store(&S.y[lane], y);
+    lds_store(&S.z[lane], z);
+    double reach = 0.0;
+    bool test = act;
+    if (SAFETY) {
+        reach = any_safety<KSET>(v.mother, v.pcon, x, y, z);
+        lds_store(&S.key[lane], step_key(reach));
+    } else {
+        const bool in_m = any_contains<KSET>(v.mother, v.pcon, x, y, z);
+        lds_store(&S.hit[lane], in_m ? 0x7fffffff : -2);
+        test = act && in_m;
+    }
+    if (__builtin_amdgcn_ballot_w64(test) != 0ull) {
+        ExactTrack c = exact_track(x, y, z, 0.0, 0.0, 0.0);
+        if (!test) c.pp = __builtin_inf();
+        int ln = 0;
+        for (int g = 0;; g += 4) {
+            if (g >= nd || ln > kListCap) {
+                for (int e0 = 0; e0 < ln; e0 += 64) {
+                    if (e0 + lane < ln) {
+                        const unsigned int e = S.list[e0 + lane];
+                        const int j = (int)(e & 63u), k = (int)(e >> 6);
+                        const DaughterRec &D = dau[k];
+                        double wx = lds_load(&S.x[j]) - D.tr[0], wy = lds_load(&S.y[j]) - D.tr[1],
+                               wz = lds_load(&S.z[j]) - D.tr[2];
+                        if (HAS_OFFS) {
+                            wx -= offs[3 * k + 0];
+                            wy -= offs[3 * k + 1];
+                            wz -= offs[3 * k + 2];
+                        }
+                        const double *R = D.rot;
+                        const double lx = fma(R[6], wz, fma(R[3], wy, R[0] * wx));
+                        const double ly = fma(R[7], wz, fma(R[4], wy, R[1] * wx));
+                        const double lz = fma(R[8], wz, fma(R[5], wy, R[2] * wx));
+                        if (SAFETY)
+                            __hip_atomic_fetch_min(&S.key[j], step_key(any_safety<KSET>(D.shape, D.pcon, lx, ly, lz)),
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                        else if (any_contains<KSET>(D.shape, D.pcon, lx, ly, lz))
+                            __hip_atomic_fetch_min(&S.hit[j], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                    }
+                }
+                ln = 0;
+                if (g >= nd) break;
+            }
+            unsigned long long pass[4];
+            exact_tests<SAFETY ? kNearTests : kHoldTests, HAS_OFFS, !HAS_OFFS>(c, cul, dau, offs, g, nd, x, y, z, reach, pass);
+            if (((pass[0] | pass[1]) | (pass[2] | pass[3])) == 0ull) continue;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (__builtin_amdgcn_inverse_ballot_w64(pass[q]))
+                    S.list[ln + lanes_below(pass[q])] = (unsigned int)(((g + q) << 6) | lane);
+                ln += __popcll(pass[q]);
+            }
+        }
+    }
+    if (!act) return;
+    if (SAFETY) {
+        out[base + lane] = key_step(lds_load(&S.key[lane]));
+    } else {
+        const int w = lds_load(&S.hit[lane]);
+        out[base + lane] = w != 0x7fffffff ? w : -1;
     }
 }
 

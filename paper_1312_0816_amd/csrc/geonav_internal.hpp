@@ -16,13 +16,13 @@ hipError_t launch_shape_query(const ShapeRec &s, const PconRec &pc, int query, c
 
 hipError_t launch_nav_basket(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul,
                              const TracksDev &t, const double *offs, double *step, int32_t *hit,
-                             double *hitpt, bool cull, int kset, hipStream_t st);
+                             double *hitpt, int tests, int kset, hipStream_t st);
 
 hipError_t launch_nav_safety(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul, int nd,
-                             const TracksDev &t, const double *offs, double *out, bool cull,
+                             const TracksDev &t, const double *offs, double *out, int tests,
                              int kset, hipStream_t st);
 hipError_t launch_nav_locate(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul,
-                             int nd, const TracksDev &t, const double *offs, int32_t *out, bool cull,
+                             bool rounds, const TracksDev &t, const double *offs, int32_t *out, int tests,
                              int kset, hipStream_t st);
 
 // Tile queues of the persistent batched kernel: one per XCD, cursors 256 B
@@ -69,7 +69,7 @@ constexpr int kBuildTilesBlocks = 256;
 // persistent: k_nav_persistent, else k_nav_tiles (one wavefront per tile);
 // count: the variant that fills the work census; kset: the kinds the
 // geometry holds (kSetBasic, kSetSeg or kSetAll).
-const void *batched_kernel(int tracks_per_lane, bool cull, bool persistent, bool count, int kset);
+const void *batched_kernel(int tracks_per_lane, int tests, bool persistent, bool count, int kset);
 const void *build_tiles_kernel();
 // Workgroups of a batched launch: num_cus * waves_per_simd (persistent) or
 // one wavefront per tile (waves_per_simd == 0).
@@ -101,6 +101,6 @@ hipError_t launch_backward(const VolumeRec *vol, const DaughterRec *dau_all, con
                            const CullBlock *cul, int nd,
                            const TracksDev &t, const double *offs, const double *gstep,
                            const double *ghit, double *g_o, double *g_d, double *partial,
-                           double *g_off, bool cull, int kset, CullBlock *shift_buf, hipStream_t st);
+                           double *g_off, int tests, int kset, CullBlock *shift_buf, hipStream_t st);
 
 }  // namespace gn

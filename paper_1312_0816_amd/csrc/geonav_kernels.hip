@@ -18,8 +18,9 @@
 //                    of many volumes in one launch, one wavefront per tile;
 //  k_nav_persistent  the same with a machine-sized grid whose wavefronts
 //                    pull tiles from per-XCD queues;
-//  k_cull_blocks     the daughters' operands of the culling tests, for a
-//                    geometry or moved by one adjoint call's offsets;
+//  k_cull_blocks     the daughters' operands of the culling tests (matrix cores
+//                    and FP64), for a geometry or moved by one adjoint
+//                    call's offsets;
 //  k_nav_backward    adjoint of the navigator (recompute + implicit-function
 //                    gradient of the surface that set the step) with
 //                    per-workgroup partial sums of the offset gradient;
@@ -237,37 +238,41 @@ hipError_t launch_shape_query(const ShapeRec &s, const PconRec &pc, int query, c
 // FP64 culling tests / these tests at 4 / at 5: toy detector 84.6 / 62 / 59.4,
 // every kind 112 / 87 / 83, 8 daughters 60.3 / 58.8 / 56.4, 64 131 / 89 / 85;
 // 300007 tracks of every kind, one round, 19.5 / 20.5 / 15.8.
-template <bool HAS_OFFS, bool HITPT, bool CULL, int KSET, int U = 1>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 5 : 1))) void k_nav_basket(const VolumeRec *__restrict__ vol,
+template <bool HAS_OFFS, bool HITPT, int TESTS, int KSET, int U = 1>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TESTS ? 5 : 1))) void k_nav_basket(const VolumeRec *__restrict__ vol,
                                                        const DaughterRec *__restrict__ dau,
                                                        const CullBlock *__restrict__ cul,
                                                        TracksDev t, const double *__restrict__ offs,
                                                        double *__restrict__ step,
                                                        int32_t *__restrict__ hit,
                                                        double *__restrict__ hitpt) {
-    if constexpr (CULL && KSET != kSetBasic) {
+    if constexpr (TESTS != kNoTests && KSET != kSetBasic) {
         // volumes of more kinds: the workgroup's wavefronts pool their last
         // flush (a wavefront past the basket's end takes part with no tracks)
         __shared__ NavScratch<U> scr[kBlock / 64];
+        __shared__ unsigned short list[TESTS == kAnyTests ? kBlock / 64 : 1][TESTS == kAnyTests ? kListCap : 1];
         __shared__ PoolInfo<kBlock / 64> pool;
         const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // (uniform)
         const int64_t base = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * 64 * U;
         const int64_t left = t.n - base;
         const int count = left <= 0 ? 0 : (left < 64 * U ? (int)left : 64 * U);
-        nav_compact_pooled<U, kBlock / 64, HAS_OFFS, HITPT, KSET>(*vol, dau, cul, 0, offs, t, base, count, scr,
-                                                                  pool, true, wave, (int)(threadIdx.x & 63),
+        nav_compact_pooled<U, kBlock / 64, HAS_OFFS, HITPT, KSET, TESTS>(*vol, dau, cul, 0, offs, t, base, count, scr,
+                                                                  list[TESTS == kAnyTests ? wave : 0], pool, true, wave, (int)(threadIdx.x & 63),
                                                                   step, hit, hitpt);
         return;
     }
-    if constexpr (CULL) {
+    if constexpr (TESTS != kNoTests) {
         // (box, tube and cone only: pooling gains nothing measurable)
         __shared__ NavScratch<U> scr[kBlock / 64];
+        __shared__ unsigned short list[TESTS == kAnyTests ? kBlock / 64 : 1][TESTS == kAnyTests ? kListCap : 1];
         const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // (uniform)
         const int64_t base = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * 64 * U;
         if (base >= t.n) return;
         const int count = t.n - base < 64 * U ? (int)(t.n - base) : 64 * U;
-        nav_compact<U, HAS_OFFS, HITPT, false, KSET>(*vol, dau, cul, offs, t, base, count, scr[wave],
-                                                     (int)(threadIdx.x & 63), step, hit, hitpt);
+        nav_compact<U, HAS_OFFS, HITPT, false, KSET, TESTS>(*vol, dau, cul, offs, t, base, count, scr[wave],
+                                                            list[TESTS == kAnyTests ? wave : 0],
+                                                            (vol->exact & kLineTasks) != 0, (int)(threadIdx.x & 63),
+                                                            step, hit, hitpt);
         return;
     }
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -287,17 +292,17 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 5
     }
 }
 
-template <bool CULL, int KSET, int U = 1>
+template <int TESTS, int KSET, int U = 1>
 static void launch_basket_variant(dim3 grid, const VolumeRec *vol, const DaughterRec *dau,
                                   const CullBlock *cul, const TracksDev &t, const double *offs, double *step, int32_t *hit,
                                   double *hitpt, hipStream_t st) {
     const dim3 block(kBlock);
     if (offs) {
-        if (hitpt) hipLaunchKernelGGL((k_nav_basket<true, true, CULL, KSET, U>), grid, block, 0, st, vol, dau, cul, t, offs, step, hit, hitpt);
-        else hipLaunchKernelGGL((k_nav_basket<true, false, CULL, KSET, U>), grid, block, 0, st, vol, dau, cul, t, offs, step, hit, hitpt);
+        if (hitpt) hipLaunchKernelGGL((k_nav_basket<true, true, TESTS, KSET, U>), grid, block, 0, st, vol, dau, cul, t, offs, step, hit, hitpt);
+        else hipLaunchKernelGGL((k_nav_basket<true, false, TESTS, KSET, U>), grid, block, 0, st, vol, dau, cul, t, offs, step, hit, hitpt);
     } else {
-        if (hitpt) hipLaunchKernelGGL((k_nav_basket<false, true, CULL, KSET, U>), grid, block, 0, st, vol, dau, cul, t, offs, step, hit, hitpt);
-        else hipLaunchKernelGGL((k_nav_basket<false, false, CULL, KSET, U>), grid, block, 0, st, vol, dau, cul, t, offs, step, hit, hitpt);
+        if (hitpt) hipLaunchKernelGGL((k_nav_basket<false, true, TESTS, KSET, U>), grid, block, 0, st, vol, dau, cul, t, offs, step, hit, hitpt);
+        else hipLaunchKernelGGL((k_nav_basket<false, false, TESTS, KSET, U>), grid, block, 0, st, vol, dau, cul, t, offs, step, hit, hitpt);
     }
 }
 
@@ -309,17 +314,19 @@ constexpr int64_t kBasketWide = (int64_t)1 << 20;
 
 hipError_t launch_nav_basket(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul,
                              const TracksDev &t, const double *offs, double *step, int32_t *hit,
-                             double *hitpt, bool cull, int kset, hipStream_t st) {
+                             double *hitpt, int tests, int kset, hipStream_t st) {
     if (t.n == 0) return hipSuccess;
-    const dim3 grid((unsigned)((t.n + kBlock - 1) / kBlock));
-    if (cull && t.n >= kBasketWide) {
-        const dim3 grid4((unsigned)((t.n + 4 * kBlock - 1) / (4 * kBlock)));
-        GN_KSET(kset, (launch_basket_variant<true, KS, 4>(grid4, vol, dau, cul, t, offs, step, hit, hitpt, st)));
-    } else if (cull) {
-        GN_KSET(kset, (launch_basket_variant<true, KS>(grid, vol, dau, cul, t, offs, step, hit, hitpt, st)));
-    } else {
-        GN_KSET(kset, (launch_basket_variant<false, KS>(grid, vol, dau, cul, t, offs, step, hit, hitpt, st)));
-    }
+    const bool wide = tests != kNoTests && t.n >= kBasketWide;
+    const int64_t per = (int64_t)kBlock * (wide ? 4 : 1);
+    const dim3 grid((unsigned)((t.n + per - 1) / per));
+#define GN_BASKET(TESTS, U) \
+    GN_KSET(kset, (launch_basket_variant<TESTS, KS, U>(grid, vol, dau, cul, t, offs, step, hit, hitpt, st)))
+    if (tests == kNoTests) GN_BASKET(kNoTests, 1);
+    else if (tests == kAnyTests && wide) GN_BASKET(kAnyTests, 4);
+    else if (tests == kAnyTests) GN_BASKET(kAnyTests, 1);
+    else if (wide) GN_BASKET(kMatrixTests, 4);
+    else GN_BASKET(kMatrixTests, 1);
+#undef GN_BASKET
     return hipGetLastError();
 }
 #endif
@@ -333,13 +340,23 @@ hipError_t launch_nav_basket(const VolumeRec *vol, const DaughterRec *dau, const
 // the workgroup copies the daughters' records into its LDS first. 2^22 points,
 // three sets in turn, with FP64 culling tests 110 us, now 60.5; of every kind
 // 364, now 181.
-template <bool HAS_OFFS, bool CULL, int KSET, bool TABLE>
+template <bool HAS_OFFS, int TESTS, int KSET, bool TABLE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_nav_safety(const VolumeRec *__restrict__ vol,
                                                        const DaughterRec *__restrict__ dau,
                                                        const CullBlock *__restrict__ cul, TracksDev t,
                                                        const double *__restrict__ offs,
                                                        double *__restrict__ out) {
-    if constexpr (CULL) {
+    if constexpr (TESTS == kAnyTests) {
+        __shared__ ExactPoints scr[kBlock / 64];
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // (uniform)
+        const int64_t base = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * 64;
+        if (base >= t.n) return;
+        const int count = t.n - base < 64 ? (int)(t.n - base) : 64;
+        points_exact<true, HAS_OFFS, KSET>(*vol, dau, cul, offs, t, base, count, scr[wave], (int)(threadIdx.x & 63),
+                                           out);
+        return;
+    }
+    if constexpr (TESTS == kMatrixTests) {
         constexpr bool POOL = KSET != kSetBasic;
         __shared__ PointScratch scr[kBlock / 64];
         __shared__ PointPool<kBlock / 64> pool;
@@ -365,20 +382,28 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     out[i] = nav_safety<HAS_OFFS, KSET>(*vol, dau, offs, t.x[i], t.y[i], t.z[i]);
 }
 
-template <bool HAS_OFFS, bool CULL, int KSET, int U = 1>
+template <bool HAS_OFFS, int TESTS, int KSET, int U = 1>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_nav_locate(const VolumeRec *__restrict__ vol,
                                                        const DaughterRec *__restrict__ dau,
                                                        const CullBlock *__restrict__ cul, TracksDev t,
                                                        const double *__restrict__ offs,
                                                        int32_t *__restrict__ out) {
-    if constexpr (CULL) {
+    if constexpr (TESTS != kNoTests) {
         __shared__ LocateScratch<U> scr[kBlock / 64];
         const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // (uniform)
         const int64_t base = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * (64 * U);
         if (base >= t.n) return;
         const int count = t.n - base < 64 * U ? (int)(t.n - base) : 64 * U;
-        locate_compact<HAS_OFFS, KSET, U>(*vol, dau, cul, offs, t, base, count, scr[wave], (int)(threadIdx.x & 63),
-                                          out);
+        const int lane = (int)(threadIdx.x & 63);
+        if constexpr (TESTS == kAnyTests) {
+            static_assert(U == 1, "one round of 64 points in FP64");
+            __shared__ ExactPoints exact[kBlock / 64];
+            if (vol->exact & kLocateTask) {
+                points_exact<false, HAS_OFFS, KSET>(*vol, dau, cul, offs, t, base, count, exact[wave], lane, out);
+                return;
+            }
+        }
+        locate_compact<HAS_OFFS, KSET, U>(*vol, dau, cul, offs, t, base, count, scr[wave], lane, out);
         return;
     }
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -386,24 +411,24 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     out[i] = nav_locate<HAS_OFFS, KSET>(*vol, dau, offs, t.x[i], t.y[i], t.z[i]);
 }
 
-template <bool CULL, int KSET, bool TABLE = false>
+template <int TESTS, int KSET, bool TABLE = false>
 static void launch_safety_variant(dim3 grid, const VolumeRec *vol, const DaughterRec *dau,
                                   const CullBlock *cul, int nd, const TracksDev &t, const double *offs,
                                   double *out, hipStream_t st) {
     const size_t lds = TABLE ? (size_t)nd * LdsRecords<KSET>::Q * 16 : 0;
     if (offs)
-        hipLaunchKernelGGL((k_nav_safety<true, CULL, KSET, TABLE>), grid, dim3(kBlock), lds, st, vol, dau, cul, t, offs, out);
+        hipLaunchKernelGGL((k_nav_safety<true, TESTS, KSET, TABLE>), grid, dim3(kBlock), lds, st, vol, dau, cul, t, offs, out);
     else
-        hipLaunchKernelGGL((k_nav_safety<false, CULL, KSET, TABLE>), grid, dim3(kBlock), lds, st, vol, dau, cul, t, offs, out);
+        hipLaunchKernelGGL((k_nav_safety<false, TESTS, KSET, TABLE>), grid, dim3(kBlock), lds, st, vol, dau, cul, t, offs, out);
 }
 
-template <bool CULL, int KSET, int U = 1>
+template <int TESTS, int KSET, int U = 1>
 static void launch_locate_variant(const VolumeRec *vol, const DaughterRec *dau,
                                   const CullBlock *cul, const TracksDev &t, const double *offs,
                                   int32_t *out, hipStream_t st) {
     const dim3 grid((unsigned)((t.n + kBlock * U - 1) / (kBlock * U)));
-    if (offs) hipLaunchKernelGGL((k_nav_locate<true, CULL, KSET, U>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
-    else hipLaunchKernelGGL((k_nav_locate<false, CULL, KSET, U>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
+    if (offs) hipLaunchKernelGGL((k_nav_locate<true, TESTS, KSET, U>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
+    else hipLaunchKernelGGL((k_nav_locate<false, TESTS, KSET, U>), grid, dim3(kBlock), 0, st, vol, dau, cul, t, offs, out);
 }
 
 // Volumes of up to kSafetyTable daughters (20 to 24 KB of records in LDS, four
@@ -413,34 +438,41 @@ static void launch_locate_variant(const VolumeRec *vol, const DaughterRec *dau,
 constexpr int kSafetyTable = 64;
 
 hipError_t launch_nav_safety(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul, int nd,
-                             const TracksDev &t, const double *offs, double *out, bool cull,
+                             const TracksDev &t, const double *offs, double *out, int tests,
                              int kset, hipStream_t st) {
     if (t.n == 0) return hipSuccess;
     const dim3 grid((unsigned)((t.n + kBlock - 1) / kBlock));
-    if (cull && nd <= kSafetyTable)
-        GN_KSET(kset, (launch_safety_variant<true, KS, true>(grid, vol, dau, cul, nd, t, offs, out, st)));
-    else if (cull) GN_KSET(kset, (launch_safety_variant<true, KS>(grid, vol, dau, cul, nd, t, offs, out, st)));
-    else GN_KSET(kset, (launch_safety_variant<false, KS>(grid, vol, dau, cul, nd, t, offs, out, st)));
+#define GN_SAFETY(TESTS, TABLE) \
+    GN_KSET(kset, (launch_safety_variant<TESTS, KS, TABLE>(grid, vol, dau, cul, nd, t, offs, out, st)))
+    if (tests == kNoTests) GN_SAFETY(kNoTests, false);
+    else if (tests == kAnyTests) GN_SAFETY(kAnyTests, false);
+    else if (nd <= kSafetyTable) GN_SAFETY(kMatrixTests, true);
+    else GN_SAFETY(kMatrixTests, false);
+#undef GN_SAFETY
     return hipGetLastError();
 }
 
-// Localizations of at least kLocateWide points in volumes of kLocateWideNd
-// daughters or more run kLocateRounds rounds of 64 per wavefront, still about 3000
-// wavefronts; smaller ones one round. (Toy detector, three sets in turn, one round /
-// four: 2^22 points 35.4 / 29.1 us, 10^6 10.1 / 9.4; every kind 2^20 13.9 / 12.4. 37 us
-// and 17.8 with FP64 culling tests. 8 daughters, one set, 2^20 6.0 / 7.0, 16 6.0 / 7.0;
-// six sets, 2^21 15.8 / 15.3 and 15.5 / 14.9.)
+// Localizations of at least kLocateWide points in volumes of enough daughters, or whose
+// points are in enough of their spheres (VolumeRec.rounds), run kLocateRounds rounds of
+// 64 per wavefront, still about 3000 wavefronts; the others one round. (Toy detector,
+// three sets in turn, one round / four: 2^22 points 35.4 / 29.1 us, 10^6 10.1 / 9.4; every
+// kind 2^20 13.9 / 12.4. 37 us and 17.8 with FP64 culling tests. 8 daughters, one set, 2^20
+// 6.0 / 7.0, 16 6.0 / 7.0; six sets, 2^21 15.8 / 15.3 and 15.5 / 14.9. 8 large daughters
+// that hold 6 % of the points, 2^20 9.8 / 8.4, every kind 16.3 / 12.3.)
 constexpr int64_t kLocateWide = (int64_t)3 << 18;
-constexpr int kLocateRounds = 4, kLocateWideNd = 12;
+constexpr int kLocateRounds = 4;
 
 hipError_t launch_nav_locate(const VolumeRec *vol, const DaughterRec *dau, const CullBlock *cul,
-                             int nd, const TracksDev &t, const double *offs, int32_t *out, bool cull,
+                             bool rounds, const TracksDev &t, const double *offs, int32_t *out, int tests,
                              int kset, hipStream_t st) {
     if (t.n == 0) return hipSuccess;
-    if (cull && t.n >= kLocateWide && nd >= kLocateWideNd)
-        GN_KSET(kset, (launch_locate_variant<true, KS, kLocateRounds>(vol, dau, cul, t, offs, out, st)));
-    else if (cull) GN_KSET(kset, (launch_locate_variant<true, KS>(vol, dau, cul, t, offs, out, st)));
-    else GN_KSET(kset, (launch_locate_variant<false, KS>(vol, dau, cul, t, offs, out, st)));
+    const bool wide = t.n >= kLocateWide && rounds;
+#define GN_LOCATE(TESTS, U) GN_KSET(kset, (launch_locate_variant<TESTS, KS, U>(vol, dau, cul, t, offs, out, st)))
+    if (tests == kNoTests) GN_LOCATE(kNoTests, 1);
+    else if (tests == kAnyTests) GN_LOCATE(kAnyTests, 1);
+    else if (wide) GN_LOCATE(kMatrixTests, kLocateRounds);
+    else GN_LOCATE(kMatrixTests, 1);
+#undef GN_LOCATE
     return hipGetLastError();
 }
 #endif
@@ -451,19 +483,21 @@ hipError_t launch_nav_locate(const VolumeRec *vol, const DaughterRec *dau, const
 // per lane, so the volume and its daughters are uniform over the wavefront.
 // Tiles come in order of decreasing per-track cost (the host sorts the
 // baskets by daughter count; k_build_tiles expands them in that order).
-template <int U, bool CULL, bool COUNT, int KSET>
+template <int U, int TESTS, bool COUNT, int KSET>
 __device__ __forceinline__ void run_tile(const Tile &tl, const VolumeRec *__restrict__ vols,
                                          const DaughterRec *__restrict__ dau_all,
                                          const CullBlock *__restrict__ cul_all, const TracksDev &t,
                                          double *__restrict__ step, int32_t *__restrict__ hit,
                                          unsigned long long *census, int lane,
-                                         NavScratch<U> *scr) {
+                                         NavScratch<U> *scr, unsigned short *list) {
     const VolumeRec &v = vols[tl.volume];
     const DaughterRec *dau = dau_all + v.first;
-    if constexpr (CULL) {
-        if (!v.dense || tl.count <= kDenseFew) {
-            nav_compact<U, false, false, COUNT, KSET>(v, dau, cul_all + v.first_block, nullptr, t, tl.offset,
-                                                      tl.count, *scr, lane, step, hit, nullptr, census);
+    if constexpr (TESTS != kNoTests) {
+        const bool dense = TESTS == kAnyTests && (v.dense & kLineTasks);
+        if (!dense || tl.count <= kFewExact) {
+            const bool exact = dense ? tl.count > kFewLines : (v.exact & kLineTasks) != 0;
+            nav_compact<U, false, false, COUNT, KSET, TESTS>(v, dau, cul_all + v.first_block, nullptr, t, tl.offset,
+                                                             tl.count, *scr, list, exact, lane, step, hit, nullptr, census);
             return;
         }
     }
@@ -492,8 +526,8 @@ __device__ __forceinline__ void run_tile(const Tile &tl, const VolumeRec *__rest
 // then the others in turn; it exits once every queue's cursor has passed the
 // queue's length, so every wavefront terminates. (Every kind, 4 rounds, 4 wavefronts
 // per SIMD: compiled for 5, which spills here, 178 us, for 4 150.)
-template <int U, bool CULL, bool COUNT, int KSET>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!CULL ? 1 : U == 1 ? 5 : 4))) void k_nav_persistent(const VolumeRec *__restrict__ vols,
+template <int U, int TESTS, bool COUNT, int KSET>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!TESTS ? 1 : U == 1 ? 5 : 4))) void k_nav_persistent(const VolumeRec *__restrict__ vols,
                                                            const DaughterRec *__restrict__ dau_all,
                                                            const CullBlock *__restrict__ cul_all,
                                                            const Tile *__restrict__ tiles,
@@ -502,8 +536,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!CULL ? 
                                                            int32_t *__restrict__ hit,
                                                            unsigned long long *census) {
     const int lane = threadIdx.x & 63;
-    __shared__ NavScratch<U> scr[CULL ? kBlock / 64 : 1];
-    NavScratch<U> *my = &scr[CULL ? (threadIdx.x >> 6) : 0];
+    __shared__ NavScratch<U> scr[TESTS ? kBlock / 64 : 1];
+    __shared__ unsigned short list[TESTS == kAnyTests ? kBlock / 64 : 1][TESTS == kAnyTests ? kListCap : 1];
+    NavScratch<U> *my = &scr[TESTS ? (threadIdx.x >> 6) : 0];
+    const int wave = (int)(threadIdx.x >> 6);
     const int home = (int)(blockIdx.x % kQueues);
     for (int qq = 0; qq < kQueues; ++qq) {
         const int q = (home + qq) % kQueues;
@@ -513,8 +549,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!CULL ? 
             if (lane == 0) id = atomicAdd(&cursors[q * kQueueStride], 1u);
             id = (unsigned int)__builtin_amdgcn_readfirstlane((int)id);
             if (id >= count) break;
-            run_tile<U, CULL, COUNT, KSET>(tiles[q + kQueues * (int64_t)id], vols, dau_all, cul_all, t,
-                                           step, hit, census, lane, my);
+            run_tile<U, TESTS, COUNT, KSET>(tiles[q + kQueues * (int64_t)id], vols, dau_all, cul_all, t,
+                                           step, hit, census, lane, my, list[TESTS == kAnyTests ? wave : 0]);
         }
     }
 }
@@ -525,8 +561,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!CULL ? 
 // rounds, which spill there (4.4 M tracks in 512 baskets: 99 at 5, 79 us at 4; every
 // kind 163 and 115). (Of 4 rounds, three pools in turn, with the tile expansion: 96
 // us with FP64 culling tests, 79.8 at 4 wavefronts per SIMD, 76.9 at 5.)
-template <int U, bool CULL, bool COUNT, int KSET>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!CULL ? 1 : U == 2 ? 4 : 5))) void k_nav_tiles(const VolumeRec *__restrict__ vols,
+template <int U, int TESTS, bool COUNT, int KSET>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!TESTS ? 1 : U == 2 ? 4 : 5))) void k_nav_tiles(const VolumeRec *__restrict__ vols,
                                                       const DaughterRec *__restrict__ dau_all,
                                                       const CullBlock *__restrict__ cul_all,
                                                       const Tile *__restrict__ tiles, int32_t ntiles,
@@ -535,9 +571,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!CULL ? 
                                                       int32_t *__restrict__ hit,
                                                       unsigned long long *census) {
     (void)cursors;
-    __shared__ NavScratch<U> scr[CULL ? kBlock / 64 : 1];
-    const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)));
-    if constexpr (CULL && !COUNT && KSET != kSetBasic) {
+    __shared__ NavScratch<U> scr[TESTS ? kBlock / 64 : 1];
+    __shared__ unsigned short list[TESTS == kAnyTests ? kBlock / 64 : 1][TESTS == kAnyTests ? kListCap : 1];
+    const int wave = (int)(threadIdx.x >> 6);
+    const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kBlock / 64) + wave));
+    if constexpr (TESTS != kNoTests && !COUNT && KSET != kSetBasic) {
         // volumes of more kinds: the workgroup's wavefronts pool their last
         // flush when their four tiles belong to one volume (work of about
         // the same length: tiles of one volume come together in the cost
@@ -552,60 +590,62 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(!CULL ? 
         tl.offset = 0;
         if (w < ntiles) tl = tiles[w];
         const VolumeRec &v = vols[tl.volume];
-        if (v.dense) {  // (all four of a shared workgroup)
+        if (TESTS == kAnyTests && (v.dense & kLineTasks)) {  // (all four of a shared workgroup)
             if (w < ntiles)
-                run_tile<U, false, false, KSET>(tl, vols, dau_all, cul_all, t, step, hit, nullptr,
-                                                (int)(threadIdx.x & 63), nullptr);
+                run_tile<U, TESTS, false, KSET>(tl, vols, dau_all, cul_all, t, step, hit, nullptr,
+                                                (int)(threadIdx.x & 63), &scr[wave], list[TESTS == kAnyTests ? wave : 0]);
             return;
         }
-        nav_compact_pooled<U, kBlock / 64, false, false, KSET>(v, dau_all, cul_all + v.first_block, v.first, nullptr, t, tl.offset,
-                                                               tl.count, scr, pool, shared, (int)(threadIdx.x >> 6),
+        nav_compact_pooled<U, kBlock / 64, false, false, KSET, TESTS>(v, dau_all, cul_all + v.first_block, v.first, nullptr, t, tl.offset,
+                                                               tl.count, scr, list[TESTS == kAnyTests ? wave : 0], pool, shared, wave,
                                                                (int)(threadIdx.x & 63), step, hit, nullptr);
         return;
     }
     if (w >= ntiles) return;
-    run_tile<U, CULL, COUNT, KSET>(tiles[w], vols, dau_all, cul_all, t, step, hit, census,
-                                   (int)(threadIdx.x & 63), &scr[CULL ? (threadIdx.x >> 6) : 0]);
+    run_tile<U, TESTS, COUNT, KSET>(tiles[w], vols, dau_all, cul_all, t, step, hit, census,
+                                   (int)(threadIdx.x & 63), &scr[TESTS ? wave : 0], list[TESTS == kAnyTests ? wave : 0]);
 }
 
-template <bool PERSISTENT, int U, bool CULL, bool COUNT, int KSET>
+template <bool PERSISTENT, int U, int TESTS, bool COUNT, int KSET>
 static const void *pick_mode() {
-    if constexpr (PERSISTENT) return reinterpret_cast<const void *>(&k_nav_persistent<U, CULL, COUNT, KSET>);
-    else return reinterpret_cast<const void *>(&k_nav_tiles<U, CULL, COUNT, KSET>);
+    if constexpr (PERSISTENT) return reinterpret_cast<const void *>(&k_nav_persistent<U, TESTS, COUNT, KSET>);
+    else return reinterpret_cast<const void *>(&k_nav_tiles<U, TESTS, COUNT, KSET>);
 }
 
-template <bool PERSISTENT, bool CULL, bool COUNT, int KSET>
+template <bool PERSISTENT, int TESTS, bool COUNT, int KSET>
 static const void *pick_u(int U) {
     switch (U) {
-        case 1: return pick_mode<PERSISTENT, 1, CULL, COUNT, KSET>();
-        case 2: return pick_mode<PERSISTENT, 2, CULL, COUNT, KSET>();
-        case 4: return pick_mode<PERSISTENT, 4, CULL, COUNT, KSET>();
-        default: return pick_mode<PERSISTENT, 8, CULL, COUNT, KSET>();
+        case 1: return pick_mode<PERSISTENT, 1, TESTS, COUNT, KSET>();
+        case 2: return pick_mode<PERSISTENT, 2, TESTS, COUNT, KSET>();
+        case 4: return pick_mode<PERSISTENT, 4, TESTS, COUNT, KSET>();
+        default: return pick_mode<PERSISTENT, 8, TESTS, COUNT, KSET>();
     }
 }
 
 // The census variants (instrumentation, not timed) exist for the full kind
 // set only.
 template <bool PERSISTENT>
-static const void *pick_kernel(int tracks_per_lane, bool cull, bool count, int kset) {
+static const void *pick_kernel(int tracks_per_lane, int tests, bool count, int kset) {
     const void *k = nullptr;
     if (count) {
-        k = cull ? pick_u<PERSISTENT, true, true, kSetAll>(tracks_per_lane)
-                 : pick_u<PERSISTENT, false, true, kSetAll>(tracks_per_lane);
-    } else if (cull) {
-        GN_KSET(kset, (k = pick_u<PERSISTENT, true, false, KS>(tracks_per_lane)));
+        k = tests ? pick_u<PERSISTENT, kAnyTests, true, kSetAll>(tracks_per_lane)
+                  : pick_u<PERSISTENT, kNoTests, true, kSetAll>(tracks_per_lane);
+    } else if (tests == kAnyTests) {
+        GN_KSET(kset, (k = pick_u<PERSISTENT, kAnyTests, false, KS>(tracks_per_lane)));
+    } else if (tests) {
+        GN_KSET(kset, (k = pick_u<PERSISTENT, kMatrixTests, false, KS>(tracks_per_lane)));
     } else {
-        GN_KSET(kset, (k = pick_u<PERSISTENT, false, false, KS>(tracks_per_lane)));
+        GN_KSET(kset, (k = pick_u<PERSISTENT, kNoTests, false, KS>(tracks_per_lane)));
     }
     return k;
 }
 
-const void *persistent_kernel(int tracks_per_lane, bool cull, bool count, int kset);
+const void *persistent_kernel(int tracks_per_lane, int tests, bool count, int kset);
 #endif
 
 #if GN_PART(5)
-const void *persistent_kernel(int tracks_per_lane, bool cull, bool count, int kset) {
-    return pick_kernel<true>(tracks_per_lane, cull, count, kset);
+const void *persistent_kernel(int tracks_per_lane, int tests, bool count, int kset) {
+    return pick_kernel<true>(tracks_per_lane, tests, count, kset);
 }
 #endif
 
@@ -655,9 +695,9 @@ __global__ __launch_bounds__(kBlock) void k_build_tiles(BuildTilesArgs a) {
     }
 }
 
-const void *batched_kernel(int tracks_per_lane, bool cull, bool persistent, bool count, int kset) {
-    return persistent ? persistent_kernel(tracks_per_lane, cull, count, kset)
-                      : pick_kernel<false>(tracks_per_lane, cull, count, kset);
+const void *batched_kernel(int tracks_per_lane, int tests, bool persistent, bool count, int kset) {
+    return persistent ? persistent_kernel(tracks_per_lane, tests, count, kset)
+                      : pick_kernel<false>(tracks_per_lane, tests, count, kset);
 }
 
 const void *build_tiles_kernel() { return reinterpret_cast<const void *>(&k_build_tiles); }
@@ -698,6 +738,7 @@ __global__ __launch_bounds__(64) void k_cull_blocks(const VolumeRec *__restrict_
     const VolumeRec &v = vols[lo];
     const int k0 = (block - (HAS_OFFS ? 0 : v.first_block)) * kCullBlock;
     *reinterpret_cast<uint4v *>(out[block].a[lane]) = cull_operand<HAS_OFFS>(v, dau_all + v.first, offs, k0, lane);
+    if (lane < kCullBlock) exact_row<HAS_OFFS>(v, dau_all + v.first, offs, k0 + lane, out[block].exact[lane]);
 }
 
 hipError_t launch_cull_blocks(const VolumeRec *vols, int nvol, int nblocks, const DaughterRec *dau, CullBlock *out,
@@ -719,20 +760,21 @@ hipError_t launch_cull_blocks(const VolumeRec *vols, int nvol, int nblocks, cons
 // read from `cul`: the volume's, or with offsets those k_cull_blocks moved.
 //
 // Row b of the partial sums is that of the passes (of 256 tracks) b, b + rows,
-// b + 2 rows, ..., added in that order, whatever CULL and U: the sums' bits do
+// b + 2 rows, ..., added in that order, whatever the tests and U: the sums' bits do
 // not depend on them. A workgroup takes U passes at a time: each wavefront
 // navigates its 64 tracks of all of them in one go, so that a batch of queued pairs
 // holds U times as many, then the passes are differentiated one by one. They are U
 // >> log_each rows' first 1 << log_each passes, or one row's next U (log_each 2).
-template <bool HAS_OFFS, bool CULL, int KSET, bool TABLE, int U>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 4 : 1))) void k_nav_backward(
+template <bool HAS_OFFS, int TESTS, int KSET, bool TABLE, int U>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TESTS ? 4 : 1))) void k_nav_backward(
     const VolumeRec *__restrict__ vol, const DaughterRec *__restrict__ dau,
     const CullBlock *__restrict__ cul, TracksDev t, const double *__restrict__ offs,
     const double *__restrict__ gstep,
     const double *__restrict__ ghit, double *__restrict__ g_o, double *__restrict__ g_d,
     double *__restrict__ partial, bool lds_acc, int rows, int log_each) {
     __shared__ double s_g[3][kBlock];
-    __shared__ NavScratch<U> scr[CULL ? kBlock / 64 : 1];
+    __shared__ NavScratch<U> scr[TESTS ? kBlock / 64 : 1];
+    __shared__ unsigned short list[TESTS == kAnyTests ? kBlock / 64 : 1][TESTS == kAnyTests ? kListCap : 1];
     // [3 nd] doubles of the row's accumulator when lds_acc, then 4 nd + nd + 1
     // ints (see below)
     extern __shared__ double s_dyn[];
@@ -749,7 +791,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 4
         const int64_t i = base + tid;
         int h = -2;
         double gdx = 0.0, gdy = 0.0, gdz = 0.0;
-        if constexpr (CULL) {
+        if constexpr (TESTS != kNoTests) {
             // the forward steps and hits of the next U passes by the
             // compacted navigator
             const int64_t wbase = base + wave * 64;
@@ -760,8 +802,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 4
                                                       : Rounds{rows * kBlock, 2 * rows * kBlock};
                 const int64_t most = (U == 1 ? 0 : rounds.at(U - 1)) + 64;
                 const int cnt = (int)(n - wbase < most ? n - wbase : most);
-                nav_compact_core<U, HAS_OFFS, false, KSET, true, true, TABLE, U == 1>(*vol, dau, cul, offs, t, wbase, cnt,
-                                                                                      scr[wave], lane, nullptr, rounds);
+                nav_core<U, HAS_OFFS, false, KSET, TESTS, true, true, TABLE, U == 1>(
+                    *vol, dau, cul, offs, t, wbase, cnt, scr[wave], list[TESTS == kAnyTests ? wave : 0],
+                    (vol->exact & kLineTasks) != 0, lane, nullptr, rounds);
             }
         }
         if (i < n) {
@@ -769,7 +812,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(CULL ? 4
             const double ux = t.ux[i], uy = t.uy[i], uz = t.uz[i];
             double best;
             int sid;
-            if constexpr (CULL) {
+            if constexpr (TESTS != kNoTests) {
                 // the step, the winner and the surface that set its step, as
                 // the compacted navigator left them
                 best = key_step(lds_load(&scr[wave].key[u * 64 + lane]));
@@ -948,7 +991,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_partials(const double *__rest
 
 constexpr int kBackwardLdsAcc = 256;
 
-template <bool CULL, int KSET, int U>
+template <int TESTS, int KSET, int U>
 static void launch_backward_variant(int rows, int nd, const VolumeRec *vol, const DaughterRec *dau,
                                     const CullBlock *cul, const TracksDev &t, const double *offs, const double *gstep,
                                     const double *ghit, double *g_o, double *g_d, double *part,
@@ -961,14 +1004,14 @@ static void launch_backward_variant(int rows, int nd, const VolumeRec *vol, cons
     const int log_each = U == 1 || npass <= rows ? 0 : npass <= 2 * (int64_t)rows ? 1 : 2;
     const int own = U >> log_each, nblocks = (rows + own - 1) / own;
     const size_t dyn = (lds_acc ? sizeof(double) * 3 * (size_t)nd : 0) + sizeof(int) * (size_t)(5 * nd + 1);
-    if (offs && CULL && shifted)
-        hipLaunchKernelGGL((k_nav_backward<true, CULL, KSET, CULL, U>), dim3(nblocks), dim3(kBlock), dyn, st, vol,
+    if (offs && TESTS && shifted)
+        hipLaunchKernelGGL((k_nav_backward<true, TESTS, KSET, TESTS != kNoTests, U>), dim3(nblocks), dim3(kBlock), dyn, st, vol,
                            dau, shifted, t, offs, gstep, ghit, g_o, g_d, part, lds_acc, rows, log_each);
     else if (offs)
-        hipLaunchKernelGGL((k_nav_backward<true, CULL, KSET, false, U>), dim3(nblocks), dim3(kBlock), dyn, st, vol,
+        hipLaunchKernelGGL((k_nav_backward<true, TESTS, KSET, false, U>), dim3(nblocks), dim3(kBlock), dyn, st, vol,
                            dau, cul, t, offs, gstep, ghit, g_o, g_d, part, lds_acc, rows, log_each);
     else
-        hipLaunchKernelGGL((k_nav_backward<false, CULL, KSET, true, U>), dim3(nblocks), dim3(kBlock), dyn, st, vol,
+        hipLaunchKernelGGL((k_nav_backward<false, TESTS, KSET, true, U>), dim3(nblocks), dim3(kBlock), dyn, st, vol,
                            dau, cul, t, offs, gstep, ghit, g_o, g_d, part, lds_acc, rows, log_each);
 }
 
@@ -986,24 +1029,26 @@ hipError_t launch_backward(const VolumeRec *vol, const DaughterRec *dau_all, con
                            const CullBlock *cul, int nd,
                            const TracksDev &t, const double *offs, const double *gstep,
                            const double *ghit, double *g_o, double *g_d, double *partial,
-                           double *g_off, bool cull, int kset, CullBlock *shift_buf, hipStream_t st) {
+                           double *g_off, int tests, int kset, CullBlock *shift_buf, hipStream_t st) {
     const int rows = backward_rows(t.n);
     double *part = (g_off && nd > 0) ? partial : nullptr;
     if (t.n > 0 || part) {
         const CullBlock *shifted = nullptr;
-        if (cull && offs && shift_buf && nd > 0 && t.n > 0) {
+        if (tests && offs && shift_buf && nd > 0 && t.n > 0) {
             // (the kernel takes the geometry's daughter table)
             hipLaunchKernelGGL(k_cull_blocks<true>, dim3((nd + kCullBlock - 1) / kCullBlock), dim3(64), 0, st, vol, 1,
                                dau_all, offs, shift_buf);
             shifted = shift_buf;
         }
         const bool wide = backward_wide(t.n, kset);
-#define GN_BACKWARD(CULL, U) \
-    GN_KSET(kset, (launch_backward_variant<CULL, KS, U>(rows, nd, vol, dau, cul, t, offs, gstep, ghit, g_o, g_d, \
+#define GN_BACKWARD(TESTS, U) \
+    GN_KSET(kset, (launch_backward_variant<TESTS, KS, U>(rows, nd, vol, dau, cul, t, offs, gstep, ghit, g_o, g_d, \
                                                         part, shifted, st)))
-        if (cull && wide) GN_BACKWARD(true, kBackwardRounds);
-        else if (cull) GN_BACKWARD(true, 1);
-        else GN_BACKWARD(false, 1);
+        if (tests == kMatrixTests && wide) GN_BACKWARD(kMatrixTests, kBackwardRounds);
+        else if (tests == kMatrixTests) GN_BACKWARD(kMatrixTests, 1);
+        else if (tests == kAnyTests && wide) GN_BACKWARD(kAnyTests, kBackwardRounds);
+        else if (tests == kAnyTests) GN_BACKWARD(kAnyTests, 1);
+        else GN_BACKWARD(kNoTests, 1);
 #undef GN_BACKWARD
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
