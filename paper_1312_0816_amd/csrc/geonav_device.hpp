@@ -97,20 +97,24 @@ constexpr int kFewLines = 16, kFewExact = 40, kFewPoints = 48;
 // Culling block: the daughters' operands of the culling tests, for up to
 // kCullBlock daughters of a volume. The tests run on the matrix cores (see
 // "Culling" below): 8 half-precision entries of each wavefront lane, in the layout
-// of the A operand of a 32 x 32 x 16 product (a); or in FP64 (see exact_row).
+// of the A operand of a 32 x 32 x 16 product, in the units of the lines and of the
+// localization (a) and in those of the safety (near); or in FP64 (see exact_row).
 constexpr int kCullBlock = 32;
-// the mother's bounding radius in the tests' units, the largest coordinate of
-// a daughter's centre they take, and a constant beyond every product
-constexpr float kCullR = 256.0f, kCullMax = 512.0f, kCullFar = 3.8e6f;
+// the radius of the sphere that bounds the starts in the tests' units, the largest
+// coordinate of a daughter's centre they take, and constants beyond every product:
+// of a daughter past the last (or, negative, one that always passes), and of a
+// track that meets none
+constexpr float kCullR = 256.0f, kCullMax = 512.0f, kCullFar = 3.8e6f, kCullMiss = 2.0e6f;
 struct alignas(16) CullBlock {
-    unsigned int a[64][4];
+    unsigned int a[64][4], near[64][4];
     double exact[kCullBlock][4];
 };
-static_assert(sizeof(CullBlock) == 2048, "CullBlock layout");
+static_assert(sizeof(CullBlock) == 3072, "CullBlock layout");
 
-// How a kernel culls: not at all; by the tests on the matrix cores; or as the volume
-// asks (VolumeRec.exact): those kernels hold both forms, and what they add would
-// cost the others registers.
+// How a kernel culls: not at all; by the tests on the matrix cores in the mother's
+// units; or as the volume asks (VolumeRec.exact, moved): those kernels hold every
+// form, and what they add would cost the others registers (the branch on moved
+// alone 6 % of the navigator of every kind at 2^22 tracks, 70.3 to 74.4 us).
 enum : int { kNoTests = 0, kMatrixTests = 1, kAnyTests = 2 };
 
 struct alignas(16) VolumeRec {
@@ -119,11 +123,16 @@ struct alignas(16) VolumeRec {
     int32_t first;  // index of daughter 0 in the daughter table
     const PconRec *pcon;  // the mother's polycone sections (device), or NULL
     double bound_r;       // radius of a sphere about the origin holding the mother
-    // the culling tests' coordinates: lengths times cull_s = kCullR / bound_r
-    // (0 when that is not a normal number), and the length, in those units,
-    // by which a track's start is moved back for its test
-    double cull_s;
-    float cull_back;
+    // The culling tests' coordinates. The unit comes from the mother's bounding
+    // radius: lengths times near_s = kCullR / bound_r (0 when that is not a
+    // normal number). Where the daughters are too small for it (moved), the lines
+    // and the localization take theirs from the sphere about (cx, cy, cz) that
+    // holds the daughters: lengths times cull_s, kCullR the square root of out2
+    // there; else cull_s = near_s and the centre is the origin.
+    double near_s, cull_s, cx, cy, cz, out2;
+    // the lengths, in those units, by which a start is moved back for its test
+    float near_back, cull_back;
+    int32_t moved;
     int32_t first_block;  // index of the volume's first culling block
     int32_t exact;        // the tasks that take the tests in FP64
     int32_t dense;        // the tasks that walk all daughters in lockstep
@@ -138,7 +147,7 @@ struct alignas(16) VolumeRec {
     // of its daughter is at most |w| + r)
     float near_r, near_r2;
 };
-static_assert(sizeof(VolumeRec) == 320, "VolumeRec layout");
+static_assert(sizeof(VolumeRec) == 368, "VolumeRec layout");
 enum : int32_t { kLineTasks = 1, kLocateTask = 2, kSafetyTask = 4 };  // of VolumeRec.exact and dense
 
 struct TracksDev {
@@ -1374,8 +1383,9 @@ __device__ __forceinline__ void nav_batch(const DaughterRec *__restrict__ dau,
 // The test is a filter: a pair that passes is evaluated in FP64, a pair that
 // is dropped must be one whose half-line misses the sphere. So every error
 // of the filter goes one way:
-//  - Lengths are taken in units where the mother's bounding radius is
-//    kCullR = 256, and every factor as two half-precision pieces (round
+//  - Lengths are taken in units where the sphere that bounds the starts (the
+//    mother's, or the daughters', see VolumeRec) has the radius kCullR = 256, and
+//    every factor as two half-precision pieces (round
 //    toward zero, 21 bits) whose products are exact in the FP32 accumulator,
 //    the product of two second pieces left out.
 //  - r^2 is widened by delta = 2^-15 ((256 + L)^2 + |T|^2), L the shift
@@ -1394,7 +1404,15 @@ __device__ __forceinline__ void nav_batch(const DaughterRec *__restrict__ dau,
 //    safety's) are formed from are those within kCullMax, told by the same
 //    product of doubles.
 // A track that starts outside the mother has step 0 from the mother, which
-// no daughter can beat: it is left out, so every start is within 256.
+// no daughter can beat: it is left out, so every start is within 256. With the
+// daughters' sphere a start outside it is where its line enters it.
+//
+// The widening delta is at least two units squared: the tests take a daughter for
+// a sphere of 1.4 units or more. In the mother's units that is 0.55 % of its
+// radius, and a detector in a mother 30 times its size passed 1.45 pairs per track
+// for 0.135 (2^22 tracks 164 us; in a mother of its own size 49.5, and with the
+// daughters' units here 50.9). Volumes that lose that much take the daughters'
+// units, and where those do not resolve them either, the tests in FP64.
 typedef _Float16 half8v __attribute__((ext_vector_type(8)));
 typedef float float16v __attribute__((ext_vector_type(16)));
 typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
@@ -1424,7 +1442,7 @@ __device__ __forceinline__ void half_split(float a, float b, unsigned int &hi, u
 // Row 8 i + 4 h + j (i, j < 4, h < 2) holds the daughter whose mask bit
 // cull_merge makes of lane half h and result 4 i + j: the block's first 16
 // daughters are in the last 8 results of the lanes.
-template <bool HAS_OFFS>
+template <bool HAS_OFFS, bool NEAR = false>  // NEAR: in the safety's units
 __device__ __forceinline__ uint4v cull_operand(const VolumeRec &v, const DaughterRec *__restrict__ dau,
                                                const double *__restrict__ offs, int k0, int lane) {
     const int row = lane & 31;
@@ -1440,17 +1458,20 @@ __device__ __forceinline__ uint4v cull_operand(const VolumeRec &v, const Daughte
             cy += offs[3 * k + 1];
             cz += offs[3 * k + 2];
         }
-        const double s = v.cull_s;
-        tx = (float)(cx * s);
-        ty = (float)(cy * s);
-        tz = (float)(cz * s);
+        const double s = NEAR ? v.near_s : v.cull_s;
+        const float back = NEAR ? v.near_back : v.cull_back;
+        tx = (float)((NEAR ? cx : cx - v.cx) * s);
+        ty = (float)((NEAR ? cy : cy - v.cy) * s);
+        tz = (float)((NEAR ? cz : cz - v.cz) * s);
         const double rs = D.cull_r * s;
         r = (float)rs;
         const float tt = fmaf(tz, tz, fmaf(ty, ty, tx * tx));
-        const float reach = kCullR + v.cull_back;
+        const float reach = kCullR + back;
         n = fmaf(-0x1p-15f, fmaf(reach, reach, tt), fmaf(-r, r, tt));
-        const bool near = s > 0.0 && fabsf(tx) <= kCullMax && fabsf(ty) <= kCullMax && fabsf(tz) <= kCullMax &&
-                          rs <= (double)kCullMax;
+        bool near = s > 0.0 && fabsf(tx) <= kCullMax && fabsf(ty) <= kCullMax && fabsf(tz) <= kCullMax &&
+                    rs <= (double)kCullMax;
+        // (within the sphere that the starts are moved to)
+        if (!NEAR && v.moved) near = __builtin_amdgcn_sqrtf(tt) + r <= kCullR - 0.125f;
         if (!near) {  // (or not a number): always passes
             tx = ty = tz = r = 0.0f;
             n = -kCullFar;
@@ -1507,10 +1528,34 @@ struct CullTracks {
     uint4v p[2], e[2];
 };
 
+// A start relative to the centre of the sphere that holds the daughters, if that is
+// outside the sphere where its half-line enters it; true if it never does (the
+// start is then the centre, and the caller lets no daughter of the sphere pass).
+// In FP64: the sphere holds the culling spheres with 0.1 units to spare, 51 units^2
+// of a line's squared distance, and the rounding of the discriminant is below 4 eps
+// times the squared distance of the start, 4 units^2 at the farthest, 2^26 units.
+__device__ __forceinline__ bool cull_enter(const VolumeRec &v, double &x, double &y, double &z, double ux, double uy,
+                                           double uz) {
+    x -= v.cx;
+    y -= v.cy;
+    z -= v.cz;
+    const double dd = fma(uz, uz, fma(uy, uy, ux * ux));
+    const double b = fma(z, uz, fma(y, uy, x * ux));
+    const double g = fma(z, z, fma(y, y, x * x)) - v.out2;
+    const double disc = fma(b, b, -g * dd);
+    const bool out = g > 0.0, miss = out && !(b < 0.0 && disc >= 0.0);
+    const double t = out && !miss ? fdiv(g, fsqrt(disc) - b) : 0.0;
+    x = miss ? 0.0 : fma(t, ux, x);
+    y = miss ? 0.0 : fma(t, uy, y);
+    z = miss ? 0.0 : fma(t, uz, z);
+    return miss;
+}
+
 // Starts moved back by v.cull_back along the unit direction. A zero
 // direction, or one whose |d|^2 overflows or is not a number, gives e = 0
 // (the test then takes the start point); the FP32 root serves unless a lane
 // that counts (`on`) has |d|^2 near the ends of its range.
+template <bool MOVED>
 __device__ __forceinline__ void cull_tracks(const VolumeRec &v, double x, double y, double z, double ux, double uy,
                                             double uz, bool on, CullTracks &c) {
     float ex = (float)ux, ey = (float)uy, ez = (float)uz;
@@ -1532,10 +1577,12 @@ __device__ __forceinline__ void cull_tracks(const VolumeRec &v, double x, double
     }
     const float back = -v.cull_back;
     const double s = v.cull_s;
-    const float px = fmaf(back, ex, (float)(x * s));
-    const float py = fmaf(back, ey, (float)(y * s));
-    const float pz = fmaf(back, ez, (float)(z * s));
-    const float pp = fmaf(pz, pz, fmaf(py, py, px * px));
+    bool miss = false;
+    if (MOVED && v.moved) miss = cull_enter(v, x, y, z, ux, uy, uz);
+    const float px = fmaf(back, ex, (float)(x * s)), py = fmaf(back, ey, (float)(y * s)),
+                pz = fmaf(back, ez, (float)(z * s));
+    float pp = fmaf(pz, pz, fmaf(py, py, px * px));
+    if (MOVED && miss) pp = kCullMiss;
     CullVector split;
     cull_columns(px, py, pz, pp, 0x54005400u, split, c.p);
     cull_columns(0.5f * ex, 0.5f * ey, 0.5f * ez, fmaf(pz, ez, fmaf(py, ey, px * ex)), 0u, split, c.e);
@@ -1610,7 +1657,9 @@ struct Rounds {
 //
 // With TILE the rounds follow one another; else round u starts rounds.at(u)
 // tracks past base, and `count` counts the tracks from base on.
-template <int U, bool HAS_OFFS, bool COUNT, int KSET, bool SURF, bool FINAL, bool TABLE, bool TILE>
+//
+// With MOVED the volume's units may be moved ones.
+template <int U, bool HAS_OFFS, bool COUNT, int KSET, bool SURF, bool FINAL, bool TABLE, bool TILE, bool MOVED>
 __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const DaughterRec *__restrict__ dau,
                                                 const CullBlock *__restrict__ cul,
                                                 const double *__restrict__ offs, const TracksDev &t,
@@ -1660,7 +1709,7 @@ __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const Daught
         const bool on = act && ms > 0.0;
         if (nd == 0 || __builtin_amdgcn_ballot_w64(on) == 0ull) continue;
         CullTracks c;
-        cull_tracks(v, p.x, p.y, p.z, p.ux, p.uy, p.uz, on, c);
+        cull_tracks<MOVED>(v, p.x, p.y, p.z, p.ux, p.uy, p.uz, on, c);
         for (int k0 = 0; k0 < nd; k0 += kCullBlock) {
             if (SECOND && k0 == kCullBlock) {
                 a = *reinterpret_cast<const uint4v *>(S.second[lane]);
@@ -1701,7 +1750,7 @@ __device__ __forceinline__ int nav_compact_core(const VolumeRec &v, const Daught
                     if (U > 1) next = load(again + 64, u + 1);
                     if (TABLE) first = operand(0);
                     if (U == 1 || k0 + kCullBlock < nd)
-                        cull_tracks(v, p.x, p.y, p.z, p.ux, p.uy, p.uz, on, c);
+                        cull_tracks<MOVED>(v, p.x, p.y, p.z, p.ux, p.uy, p.uz, on, c);
                 }
             }
         }
@@ -1924,8 +1973,8 @@ __device__ __forceinline__ int nav_core(const VolumeRec &v, const DaughterRec *_
     if (TESTS == kAnyTests && exact)
         return nav_exact_core<U, HAS_OFFS, COUNT, KSET, SURF, FINAL, TABLE, TILE>(v, dau, cul, offs, t, base, count,
                                                                                  rounds, S, list, lane, census);
-    return nav_compact_core<U, HAS_OFFS, COUNT, KSET, SURF, FINAL, TABLE, TILE>(v, dau, cul, offs, t, base, count,
-                                                                               rounds, S, lane, census);
+    return nav_compact_core<U, HAS_OFFS, COUNT, KSET, SURF, FINAL, TABLE, TILE, TESTS == kAnyTests>(
+        v, dau, cul, offs, t, base, count, rounds, S, lane, census);
 }
 
 // Writes step, hit and (when HITPT) the hit point of the tile's tracks
@@ -2334,15 +2383,27 @@ struct PointTests {
 // MODE 0: with the mother's Safety `reach`, less the bound of the nearest
 // sphere; f receives the length tested with. `a` is the first block's operand,
 // operand(k0) the others'.
-template <int MODE, typename Operand>
+template <int MODE, bool MOVED, typename Operand>
 __device__ __forceinline__ void point_tests(const VolumeRec &v, double x, double y, double z, double reach,
                                             const uint4v &a, Operand operand, float &f, PointTests &T) {
     const int nd = v.nd;
-    const float px = (float)(x * v.cull_s), py = (float)(y * v.cull_s), pz = (float)(z * v.cull_s);
-    const float pp = fmaf(pz, pz, fmaf(py, py, px * px));
+    const double s = MODE == 0 ? v.near_s : v.cull_s;
+    const bool moved = MOVED && v.moved;
+    float miss = 0.0f;
+    if (moved) {  // (a point outside the daughters' sphere is in none)
+        x -= v.cx;
+        y -= v.cy;
+        z -= v.cz;
+        if (!(fma(z, z, fma(y, y, x * x)) <= v.out2)) {
+            x = y = z = 0.0;
+            miss = kCullMiss;
+        }
+    }
+    const float px = (float)(x * s), py = (float)(y * s), pz = (float)(z * s);
+    const float pp = fmaf(pz, pz, fmaf(py, py, MOVED ? fmaf(px, px, miss) : px * px));
     CullVector split;
     cull_columns(px, py, pz, pp, 0x54005400u, split, T.col);
-    f = MODE == 0 ? (float)(reach * v.cull_s) : 0.0f;
+    f = MODE == 0 ? (float)(reach * v.near_s) : 0.0f;
     if (MODE == 0 && nd >= kNearest) {
         int g[2] = {0x7f000000, 0x7f000000};  // as integers: any negative result stays the smallest
         uint4v b = a;
@@ -2361,8 +2422,8 @@ __device__ __forceinline__ void point_tests(const VolumeRec &v, double x, double
         const uint2v own = __builtin_amdgcn_permlane32_swap((unsigned int)g[0], (unsigned int)g[1], false, false);
         f = fminf(f, nearest_bound(v, __int_as_float(min((int)own.x, (int)own.y))));
     }
-    const float lim = kCullR + v.cull_back;
-    T.near = pp <= lim * lim && f <= lim;  // (false if not a number)
+    const float lim = kCullR + (MODE == 0 ? v.near_back : v.cull_back);
+    T.near = moved || (pp <= lim * lim && f <= lim);  // (false if not a number)
     if (MODE == 0) cull_columns(split, fmaf(-f, f, pp), f, T.col);
 }
 // Mask of the block's daughters that pass (left: daughters from its first on).
@@ -2390,8 +2451,8 @@ __device__ __forceinline__ void safety_compact(const VolumeRec &v, const Daughte
     PointScratch &S = scr[wave];
     const int nd = v.nd;
     auto operand = [&](int k0) -> uint4v {
-        if (!HAS_OFFS) return *reinterpret_cast<const uint4v *>(cul[k0 / kCullBlock].a[lane]);
-        return cull_operand<HAS_OFFS>(v, dau, offs, k0, lane);
+        if (!HAS_OFFS) return *reinterpret_cast<const uint4v *>(cul[k0 / kCullBlock].near[lane]);
+        return cull_operand<HAS_OFFS, true>(v, dau, offs, k0, lane);
     };
     uint4v a = {};
     if (nd > 0) a = operand(0);
@@ -2409,7 +2470,7 @@ __device__ __forceinline__ void safety_compact(const VolumeRec &v, const Daughte
     if (nd > 0 && count > 0) {
         PointTests T;
         float f;
-        point_tests<0>(v, x, y, z, reach, a, operand, f, T);
+        point_tests<0, false>(v, x, y, z, reach, a, operand, f, T);
         for (int k0 = 0; k0 < nd; k0 += kCullBlock) {
             unsigned int m = point_mask(a, T, nd - k0);
             if (!act) m = 0u;
@@ -2490,7 +2551,7 @@ __device__ __forceinline__ void locate_batch(const DaughterRec *__restrict__ dau
             __hip_atomic_fetch_min(&S.hit[j], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     }
 }
-template <bool HAS_OFFS, int KSET, int U>
+template <bool HAS_OFFS, int KSET, int U, bool MOVED>
 __device__ __forceinline__ void locate_compact(const VolumeRec &v, const DaughterRec *__restrict__ dau,
                                                const CullBlock *__restrict__ cul,
                                                const double *__restrict__ offs, const TracksDev &t,
@@ -2525,7 +2586,7 @@ __device__ __forceinline__ void locate_compact(const VolumeRec &v, const Daughte
         if (nd == 0 || __builtin_amdgcn_ballot_w64(on) == 0ull) continue;
         PointTests T;
         float f;
-        point_tests<1>(v, p.x, p.y, p.z, 0.0, first, operand, f, T);
+        point_tests<1, MOVED>(v, p.x, p.y, p.z, 0.0, first, operand, f, T);
         uint4v a = first;
         for (int k0 = 0; k0 < nd; k0 += kCullBlock) {
             if (k0 > 0) {

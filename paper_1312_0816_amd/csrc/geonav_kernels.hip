@@ -403,7 +403,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 return;
             }
         }
-        locate_compact<HAS_OFFS, KSET, U>(*vol, dau, cul, offs, t, base, count, scr[wave], lane, out);
+        locate_compact<HAS_OFFS, KSET, U, TESTS == kAnyTests>(*vol, dau, cul, offs, t, base, count, scr[wave], lane, out);
         return;
     }
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -738,6 +738,8 @@ __global__ __launch_bounds__(64) void k_cull_blocks(const VolumeRec *__restrict_
     const VolumeRec &v = vols[lo];
     const int k0 = (block - (HAS_OFFS ? 0 : v.first_block)) * kCullBlock;
     *reinterpret_cast<uint4v *>(out[block].a[lane]) = cull_operand<HAS_OFFS>(v, dau_all + v.first, offs, k0, lane);
+    *reinterpret_cast<uint4v *>(out[block].near[lane]) =
+        cull_operand<HAS_OFFS, true>(v, dau_all + v.first, offs, k0, lane);
     if (lane < kCullBlock) exact_row<HAS_OFFS>(v, dau_all + v.first, offs, k0 + lane, out[block].exact[lane]);
 }
 
