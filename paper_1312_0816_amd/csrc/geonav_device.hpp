@@ -122,22 +122,26 @@ struct alignas(16) VolumeRec {
     int32_t nd;     // number of daughters
     int32_t first;  // index of daughter 0 in the daughter table
     const PconRec *pcon;  // the mother's polycone sections (device), or NULL
-    double bound_r;       // radius of a sphere about the origin holding the mother
     // The culling tests' coordinates. The unit comes from the mother's bounding
     // radius: lengths times near_s = kCullR / bound_r (0 when that is not a
     // normal number). Where the daughters are too small for it (moved), the lines
     // and the localization take theirs from the sphere about (cx, cy, cz) that
     // holds the daughters: lengths times cull_s, kCullR the square root of out2
-    // there; else cull_s = near_s and the centre is the origin.
-    double near_s, cull_s, cx, cy, cz, out2;
-    // the lengths, in those units, by which a start is moved back for its test
-    float near_back, cull_back;
-    int32_t moved;
+    // there; else cull_s = near_s and the centre is the origin. near_back and
+    // cull_back are the lengths, in those units, by which a start is moved back
+    // for its test. (The navigator's are together in front: a wavefront waits
+    // for each line of 64 bytes that it takes of this record.)
+    double cull_s;
+    float cull_back;
     int32_t first_block;  // index of the volume's first culling block
     int32_t exact;        // the tasks that take the tests in FP64
     int32_t dense;        // the tasks that walk all daughters in lockstep
+    int32_t moved;
     int32_t crowded;      // the safety queues its pairs daughter by daughter
     int32_t rounds;       // large localizations take several rounds per wavefront
+    float near_back;
+    double near_s, cx, cy, cz, out2;
+    double bound_r;  // radius of a sphere about the origin holding the mother
     // the safety's bound from the nearest culling sphere (see the compacted
     // safety), in the tests' units: of the daughters whose Safety at distance
     // |w| > r is at most sqrt(|w|^2 + c), the largest r^2 + c; of the others,

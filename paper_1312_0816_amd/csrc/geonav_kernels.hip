@@ -232,8 +232,9 @@ hipError_t launch_shape_query(const ShapeRec &s, const PconRec &pc, int query, c
 // queued pairs). What bounds it is the memory's latency as much as VALU issue
 // (0.85 of the lanes' time; 4.8 TB/s of the 60 B per track on the toy
 // detector, 1 GiB copies reach 5.0), so wavefronts in flight count: all are
-// compiled for 5 per SIMD (75-96 VGPRs), which takes that nothing is kept
-// live through a full queue's batch, nor an address formed ahead of it (118
+// compiled for 5 per SIMD (75-96 VGPRs; of every kind, with 4 rounds, 12 to 36 B
+// per lane spilled, 52 in the kernels of every form), which takes that nothing is
+// kept live through a full queue's batch, nor an address formed ahead of it (118
 // VGPRs, 4 per SIMD, before). 2^22 tracks, three sets of buffers in turn (us),
 // FP64 culling tests / these tests at 4 / at 5: toy detector 84.6 / 62 / 59.4,
 // every kind 112 / 87 / 83, 8 daughters 60.3 / 58.8 / 56.4, 64 131 / 89 / 85;
