@@ -198,7 +198,8 @@ int geo_navigate_batched(geo_geometry *g, const geo_basket *baskets, int32_t nb,
  *   g_o   (double[3 * n] SoA, or NULL to skip): d/dp of sum_i gstep_i s_i + ghit_i . h_i
  *   g_d   (double[3 * n] SoA, or NULL to skip): d/dd of the same
  *   g_off (double[ndaughters * 3], or NULL to skip): d/d delta_k summed over
- *         the basket; overwritten, deterministic (fixed reduction order).
+ *         the basket; overwritten, deterministic (fixed reduction order, the
+ *         same with culling on or off and for both entry points).
  * Tracks whose step is 0 (outside the mother or inside a daughter) or that
  * never reach a boundary contribute 0. At a non-smooth point (an edge, a tie
  * between volumes) the gradient of the surface the forward pass picked is
@@ -275,15 +276,19 @@ int geo_set_batched_graph(geo_geometry *g, int32_t use_graph);
 
 /* Culling in the navigators (basket, batched, backward): a daughter is not
  * evaluated for a track whose line misses the daughter's bounding sphere
- * (radius enlarged by 1e-6 relative + 1e-6, and by the rounding of the tests,
- * which run in half precision on the matrix cores). The (track, daughter)
- * pairs that pass are queued in LDS and evaluated one pair per lane. Volumes
- * whose spheres most lines meet, and some calls on volumes of a few
- * daughters, evaluate every daughter all the same. A culled daughter could neither lower a step nor
+ * (radius enlarged by 1e-6 relative + 1e-6, and by the rounding of the tests).
+ * The (track, daughter) pairs that pass are queued in LDS and evaluated one pair
+ * per lane. The tests run in half precision on the matrix cores, in units of the
+ * mother's bounding radius / 256 or, where the daughters are small against it, of
+ * the sphere that holds them all: a sphere counts as one of 1.4 units at least.
+ * Volumes whose daughters neither resolves, or whose lines meet many of them,
+ * take tests in FP64. Volumes whose lines meet most spheres (an eighth of the
+ * daughters or so), and some calls on volumes of a few daughters, evaluate every
+ * daughter all the same. A culled daughter could neither lower a step nor
  * win a tie, so results are bit-identical with culling on or off; only the
  * work done changes. Applies likewise to geo_navigate_safety (a daughter
  * whose sphere is farther than the mother's safety or than a bound of the
- * nearest daughter's) and geo_locate (a point
+ * nearest daughter's; in the mother's units) and geo_locate (a point
  * outside the sphere). On by default. */
 int geo_set_culling(geo_geometry *g, int32_t enable);
 int geo_get_culling(const geo_geometry *g, int32_t *enabled);
