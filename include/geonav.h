@@ -282,9 +282,9 @@ int geo_set_batched_graph(geo_geometry *g, int32_t use_graph);
  * mother's bounding radius / 256 or, where the daughters are small against it, of
  * the sphere that holds them all: a sphere counts as one of 1.4 units at least.
  * Volumes whose daughters neither resolves, or whose lines meet many of them,
- * take tests in FP64. Volumes whose lines meet most spheres (an eighth of the
- * daughters or so), and some calls on volumes of a few daughters, evaluate every
- * daughter all the same. A culled daughter could neither lower a step nor
+ * take tests in FP64. Volumes where a line meets a tenth of the daughters' spheres
+ * or more in the mean (the figure depends on the task and the kinds), and some
+ * calls on volumes of a few daughters, evaluate every daughter all the same. A culled daughter could neither lower a step nor
  * win a tie, so results are bit-identical with culling on or off; only the
  * work done changes. Applies likewise to geo_navigate_safety (a daughter
  * whose sphere is farther than the mother's safety or than a bound of the
